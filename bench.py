@@ -42,7 +42,7 @@ _CSRC = "paper_1904_02863_amd/csrc/"
 _COMMON = tuple(_CSRC + f for f in ("gw_device_math.h", "gw_internal.h", "gw_template.h", "gw_phasor_table.h")) + (
     "paper_1904_02863_amd/build.py",)
 PROFILE_SOURCES = {
-    PROFILE_SUMMARY: (_CSRC + "gw_kernels.hip", _CSRC + "gw_plan.h") + _COMMON,
+    PROFILE_SUMMARY: (_CSRC + "gw_kernels.hip", _CSRC + "gw_plan.h", _CSRC + "gw_nodes.h") + _COMMON,
     WAVEFORM_PROFILE: (_CSRC + "gw_waveform.hip",) + _COMMON,
     RELBIN_PROFILE: (_CSRC + "gw_relbin.hip",) + _COMMON,
 }
@@ -110,13 +110,20 @@ PROFILED_PAIRS = 4096 * 259585
 
 def executed_flops_per_pair(precision: str, summary: str = PROFILE_SUMMARY, sources: str | None = None):
     """FP64 flops the counters saw the split-form tile loop execute per
-    (sample, bin) pair at this precision: the mean over the plans of a
-    matching summary, or None when there is none."""
+    (sample, bin) pair at this precision when every bin is summed for every
+    sample (--scatter-arrivals): the mean over the plans of a matching
+    summary, or None when there is none."""
     plans = profiled_plans(precision, summary, sources)
     if not plans:
         return None
     total = sum(measured_executed_flops(f"{precision}@{p}", summary, sources) for p in plans)
     return total / len(plans) / PROFILED_PAIRS
+
+
+def node_key(precision: str) -> str:
+    """Key of the default batch's figures in the tile kernel's counter summary:
+    its pass runs over frequency nodes, not over the bins a plan splits."""
+    return f"{precision}@nodes"
 
 
 def plan_key(precision: str, plan: dict) -> str:
@@ -149,7 +156,7 @@ def calibration_copy(mib: int, device):
     del src, dst
 
 
-def build_inputs(name: str, n_samples: int | None, spins: bool = False):
+def build_inputs(name: str, n_samples: int | None, spins: bool = False, scatter: bool = False):
     import dataclasses
 
     import numpy as np
@@ -170,6 +177,10 @@ def build_inputs(name: str, n_samples: int | None, spins: bool = False):
         rng = np.random.default_rng(11)
         w = dataclasses.replace(w, theta_inj=synth.add_spins(w.theta_inj, rng)[0],
                                 theta=synth.add_spins(w.theta, rng), n_param=w.n_param + 2)
+    if scatter:     # arrival times all over the segment: every bin is summed for every sample
+        th = np.array(w.theta)
+        th[:, 4] = np.random.default_rng(12).uniform(0.0, 1.0 / w.grid.delta_f, len(th))
+        w = dataclasses.replace(w, theta=th)
     dev = torch.device("cuda", 0)
     theta = torch.from_numpy(np.ascontiguousarray(w.theta)).to(dev)
     inj = torch.from_numpy(np.ascontiguousarray(w.theta_inj[None, :])).to(dev)
@@ -829,6 +840,9 @@ def main():
     ap.add_argument("--spins", action="store_true",
                     help="single-event workloads: aligned spins chi1, chi2 ~ U[-1, 1] on every row; "
                          "flow-mcmc: the two spin coordinates enter the likelihood")
+    ap.add_argument("--scatter-arrivals", action="store_true",
+                    help="single-event workloads: arrival times uniform over the segment, so that no frequency "
+                         "nodes apply and the tile kernel sums every bin for every sample")
     ap.add_argument("--cpu-seconds", type=float, default=15.0, help="CPU-baseline budget")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-flow", action="store_true",
@@ -866,7 +880,7 @@ def main():
     if args.workload == "bns-relbin":
         bench_relbin(args)
         return
-    w, data, psd, theta = build_inputs(args.workload, args.samples, args.spins)
+    w, data, psd, theta = build_inputs(args.workload, args.samples, args.spins, args.scatter_arrivals)
     g = w.grid
     ws = gw.Workspace(0)
     ws.reserve(g.n_bins, w.n_det, w.n_samples)
@@ -903,19 +917,20 @@ def main():
     kernel_avg_s = kernel_ms / 1e3 / max(launches, 1)
     mixed = args.precision == "mixed"
     direct = bool(args.flags & 1)
+    headline = (args.workload == "bbh-3det-128s" and args.flags == 0 and not args.spins
+                and not args.scatter_arrivals)
+    # the direct form, and batches without nodes, sum every bin for every
+    # sample; otherwise the pass runs over the batch's frequency nodes
+    every_bin = direct or args.scatter_arrivals
     flops_launch = flops_per_pair(w.n_det, mixed, direct) * w.n_samples * g.n_bins
     tally_rate = flops_launch / kernel_avg_s / 1e12
-    headline = args.workload == "bbh-3det-128s" and args.flags == 0 and not args.spins
-    # the counters hold for the plan they were taken under
-    key = plan_key(args.precision, plan)
     # FP64 flops the hardware counters saw one launch execute (FMA = 2), from
     # the committed summary of the same kernel sources; None when they changed
+    key = node_key(args.precision) if headline else plan_key(args.precision, plan)
     executed = measured_executed_flops(key) if headline else None
     source = f"executed FP64 flops from the counters in {PROFILE_SUMMARY}" if executed is not None else None
-    if executed is None and w.n_det == 3 and args.flags == 0:
-        # another batch on the same 3-detector split-form loop (other bins,
-        # samples or aligned spins, which change only the per-sample
-        # coefficients): the counted flops per (sample, bin) of that loop
+    if executed is None and args.scatter_arrivals and w.n_det == 3 and args.flags == 0:
+        # the counted flops per (sample, bin) of the split-form loop on 3 detectors
         per_pair = executed_flops_per_pair(args.precision)
         if per_pair is not None:
             executed = per_pair * w.n_samples * g.n_bins
@@ -944,16 +959,17 @@ def main():
         "roofline": {"bound": "alu", "achieved": achieved, "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / FP64_PEAK_TFLOPS if achieved is not None else None,
                      "flops_source": (source if executed is not None else
-                                      f"no counter summary of these kernel sources under plan {key} "
-                                      f"(profiled: {profiled_plans(args.precision)})"),
+                                      "no counters of this batch: its work is the frequency nodes it needs"
+                                      if not every_bin else f"no counter summary of these kernel sources for {key}"),
                      "executed_flops_per_launch": executed,
                      "issue_frac": (issue / (kernel_avg_s * 2.4e9) if issue is not None else None),
                      "traffic": measured_traffic(key) if headline else None,
                      "kernel": f"lnl_tile_kernel<{w.n_det},{'mixed' if mixed else 'fp64'}>",
                      "kernel_ms": kernel_avg_s * 1e3,
-                     # the algorithmic tally below prices the phasor at its
-                     # polynomial cost; the table phasor the kernel runs costs less
-                     "frac_tally": tally_rate / FP64_PEAK_TFLOPS, "flops_per_launch_tally": flops_launch,
+                     # what summing every bin for every sample would take by the algorithmic tally
+                     # (phasor at its polynomial cost); a rate only where the kernel does that
+                     "frac_tally": tally_rate / FP64_PEAK_TFLOPS if every_bin else None,
+                     "flops_per_launch_tally": flops_launch,
                      "flops_per_pair_tally": flops_per_pair(w.n_det, mixed, direct)},
     }
     if args.flags & 2:

@@ -17,6 +17,7 @@
 
 #include "gw_build_id.h"
 #include "gw_internal.h"
+#include "gw_nodes.h"
 #include "gw_plan.h"
 #include "gwlnl.h"
 
@@ -106,6 +107,7 @@ struct DeviceGuard {
 
 constexpr size_t kAlign = 256;
 #define GW_PI_HOST 3.141592653589793
+constexpr size_t kStaticScratchBytes = (size_t)GW_STATIC_SCRATCH_BYTES;
 constexpr unsigned kLnlFlags = GW_FLAG_DIRECT | GW_FLAG_TERM_ISCO | GW_FLAG_ADD_NORM;
 
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
@@ -260,14 +262,17 @@ gw::TilePlan plan_tiles(gw_workspace *ws, int64_t n_bins, int n_det, int64_t n_s
 // sums are carved only when the call's flags use them.
 struct LnlLayout {
     size_t tab1, tab2, dcoef, edir, vdir, qprefix, qoffsets, prep_partials, event_sums, k_limit, records, partials,
-        queue, total;
+        queue, stats, node_plan, total;
     int prep_blocks;
+    bool nodes;           // the call sums over frequency nodes (stats and node_plan are carved)
 };
 
-LnlLayout lnl_layout(int64_t n_bins, int n_det, int64_t n_samples, const gw::TilePlan &plan, unsigned flags)
+LnlLayout lnl_layout_as(int64_t n_bins, int n_det, int64_t n_samples, const gw::TilePlan &plan, unsigned flags,
+                        bool nodes)
 {
     LnlLayout l;
     Carver c;
+    l.nodes = nodes;
     const bool direct = (flags & GW_FLAG_DIRECT) != 0, isco = (flags & GW_FLAG_TERM_ISCO) != 0;
     l.prep_blocks = (int)((n_bins + gw::kBlock - 1) / gw::kBlock);
     l.tab1 = c.take(sizeof(gw::Tab1) * n_bins);
@@ -277,14 +282,35 @@ LnlLayout lnl_layout(int64_t n_bins, int n_det, int64_t n_samples, const gw::Til
     l.vdir = direct ? c.take(sizeof(double) * n_bins * n_det) : 0;
     l.qprefix = isco ? c.take(sizeof(double) * n_bins * n_det) : 0;
     l.qoffsets = isco ? c.take(sizeof(double) * (size_t)l.prep_blocks * n_det) : 0;
-    l.prep_partials = c.take(sizeof(double) * gw::kPrepPerDet * n_det * l.prep_blocks);
+    l.prep_partials = c.take(sizeof(double) * gw::kPrepPerDet * n_det *
+                             (nodes ? std::max<int64_t>(gw::node_max_chunks(n_bins), l.prep_blocks)
+                                    : (int64_t)l.prep_blocks));
     l.event_sums = c.take(sizeof(double) * gw::kEventSums);
     l.k_limit = c.take(sizeof(int64_t));
     l.records = c.take(sizeof(double) * gw::record_fields(n_det) * std::max<int64_t>(n_samples, 1));
     l.partials = c.take(sizeof(double) * (size_t)plan.n_chunks * n_samples);   // one total per chunk and sample
-    l.queue = c.take(sizeof(unsigned) * gw::kQueues);
+    l.queue = c.take(sizeof(unsigned) * 2 * gw::kQueues);
+    l.stats = nodes ? c.take(sizeof(double) * gw::kStats * (gw::node_stat_entries(n_samples) + 1)) : 0;
+    l.node_plan = nodes ? c.take(sizeof(gw::NodePlan)) : 0;
     l.total = c.offset;
     return l;
+}
+
+// The sections of a call, with those of the frequency nodes when the call
+// takes them: split form without a template end (whose samples would end between
+// nodes), and enough work (kNodeMinWork).  The nodes' sections must not
+// push a call out of the static array that fits it without them, and
+// gw_lnl_batch and gw_lnl_batch_static run the same kernels on the same call,
+// so the rule is the same for both.
+LnlLayout lnl_layout(int64_t n_bins, int n_det, int64_t n_samples, const gw::TilePlan &plan, unsigned flags)
+{
+    const LnlLayout plain = lnl_layout_as(n_bins, n_det, n_samples, plan, flags, false);
+    if (gw::tile_form(flags) != gw::kFormSplit || n_bins < gw::kNodeMinBins || n_bins > 0x7fffffffLL ||
+        (double)n_bins * (double)plan.n_groups < (double)gw::kNodeMinWork)
+        return plain;
+    const LnlLayout nodes = lnl_layout_as(n_bins, n_det, n_samples, plan, flags, true);
+    const bool leaves_array = plain.total <= kStaticScratchBytes && nodes.total > kStaticScratchBytes;
+    return leaves_array ? plain : nodes;
 }
 
 template <typename T>
@@ -335,7 +361,8 @@ int timer_stop(gw_workspace *ws, hipEvent_t stop, hipStream_t stream)
 // (ws == nullptr) every kernel is launched and nothing is timed.
 int lnl_enqueue(gw_workspace *ws, char *base, const LnlLayout &l, const gw::TilePlan &plan, const gw_grid &grid,
                 int n_det, const gw::DetGeom &geom, const gw_c128 *data, const double *psd, const double *theta,
-                int n_param, int64_t n_samples, double *lnl_out, bool mixed, unsigned flags, hipStream_t stream)
+                int n_param, int64_t n_samples, double *lnl_out, bool mixed, unsigned flags, int n_cu,
+                hipStream_t stream)
 {
     const int form = gw::tile_form(flags);
     const bool isco = (flags & GW_FLAG_TERM_ISCO) != 0;
@@ -353,6 +380,7 @@ int lnl_enqueue(gw_workspace *ws, char *base, const LnlLayout &l, const gw::Tile
     eb.sums = static_cast<double *>(sec(l.event_sums));
     eb.k_limit = static_cast<int64_t *>(sec(l.k_limit));
     eb.queue = plan.rounds > 0 ? static_cast<unsigned *>(sec(l.queue)) : nullptr;
+    eb.node_plan = l.nodes ? static_cast<gw::NodePlan *>(sec(l.node_plan)) : nullptr;
     auto *rec = static_cast<double *>(sec(l.records));
     auto *part = static_cast<double2 *>(sec(l.partials));
     hipError_t e;
@@ -368,8 +396,33 @@ int lnl_enqueue(gw_workspace *ws, char *base, const LnlLayout &l, const gw::Tile
     sp.geom = geom;
     sp.theta = theta;
     sp.records = rec;
-    if ((e = gw::launch_event_data(grid, n_det, data, psd, eb, flags, &sp, stream)) != hipSuccess)
+    if (l.nodes) {
+        // the samples first: the range of their phases decides where the nodes stand
+        auto *stats = static_cast<double *>(sec(l.stats));
+        const int64_t entries = gw::node_stat_entries(n_samples);
+        gw::NodeEvent ne;
+        ne.n_bins = grid.n_bins;
+        ne.n_det = n_det;
+        ne.f_low = grid.f_low;
+        ne.df = grid.delta_f;
+        ne.data = reinterpret_cast<const double2 *>(data);
+        ne.psd = psd;
+        ne.tab1 = eb.tab1;
+        ne.tab2 = eb.tab2;
+        ne.dcoef = eb.dcoef;
+        ne.prep = eb.prep;
+        ne.sums = eb.sums;
+        ne.stats = entries > gw::kStatEntries ? stats + entries * gw::kStats : stats;
+        ne.n_stats = entries > gw::kStatEntries ? 1 : (int)entries;
+        ne.plan = eb.node_plan;
+        if ((e = gw::launch_node_samples(grid, n_det, sp, stats, stream)) != hipSuccess)
+            return hip_fail(e, "sample prep");
+        if ((e = gw::launch_node_spread(ne, (flags & GW_FLAG_ADD_NORM) != 0, n_cu, stream)) != hipSuccess)
+            return hip_fail(e, "weighting the data onto the nodes");
+        if ((e = gw::launch_node_combine(ne, eb.queue, stream)) != hipSuccess) return hip_fail(e, "nodes");
+    } else if ((e = gw::launch_event_data(grid, n_det, data, psd, eb, flags, &sp, stream)) != hipSuccess) {
         return hip_fail(e, "event data and sample prep");
+    }
     if (form == gw::kFormSplitIsco && (e = gw::launch_isco_limit(n_samples, rec, eb.k_limit, stream)) != hipSuccess)
         return hip_fail(e, "template-end limit");
     hipEvent_t t_start = nullptr, t_stop = nullptr;
@@ -382,7 +435,7 @@ int lnl_enqueue(gw_workspace *ws, char *base, const LnlLayout &l, const gw::Tile
     if (ws) {
         if (int rc = timer_stop(ws, t_stop, stream)) return rc;
     }
-    if ((e = gw::launch_lnl_finalize(grid, n_samples, n_det, plan, part, rec, eb, flags, lnl_out, stream)) !=
+    if ((e = gw::launch_lnl_finalize(grid, n_samples, n_det, plan, mixed, part, rec, eb, flags, lnl_out, stream)) !=
         hipSuccess)
         return hip_fail(e, "lnl finalize");
     return GW_OK;
@@ -455,7 +508,7 @@ int tune_single_event(gw_workspace *ws, const gw_grid &grid, int n_det, const gw
             const LnlLayout l = lnl_layout(grid.n_bins, n_det, n_samples, plans[i], flags);
             if ((e = hipEventRecord(ev[0], stream)) != hipSuccess) { rc = hip_fail(e, "hipEventRecord"); break; }
             if ((rc = lnl_enqueue(ws, static_cast<char *>(ws->base), l, plans[i], grid, n_det, geom, data, psd, theta,
-                                  n_param, n_samples, lnl_out, mixed, flags, stream)) != GW_OK)
+                                  n_param, n_samples, lnl_out, mixed, flags, ws->n_cu, stream)) != GW_OK)
                 break;
             float ms = 0.0f;
             if ((e = hipEventRecord(ev[1], stream)) != hipSuccess || (e = hipEventSynchronize(ev[1])) != hipSuccess ||
@@ -499,7 +552,7 @@ int lnl_one_event(gw_workspace *ws, const gw_grid &grid, int n_det, const gw::De
     const LnlLayout l = lnl_layout(grid.n_bins, n_det, n_samples, plan, flags);
     if (int rc = ensure_capacity(ws, l.total, stream)) return rc;
     return lnl_enqueue(ws, static_cast<char *>(ws->base), l, plan, grid, n_det, geom, data, psd, theta, n_param,
-                       n_samples, lnl_out, mixed, flags, stream);
+                       n_samples, lnl_out, mixed, flags, ws->n_cu, stream);
 }
 
 // ------------------------------------------------------------------ allocation-free likelihood
@@ -508,7 +561,6 @@ int lnl_one_event(gw_workspace *ws, const gw_grid &grid, int n_det, const gw::De
 // itself to a kernel or a copy (in host code the name is a host-side stand-in,
 // not a device address); it uses the address hipGetSymbolAddress returns for
 // the device that is current.
-constexpr size_t kStaticScratchBytes = (size_t)GW_STATIC_SCRATCH_BYTES;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 constexpr int kStaticMaxDevices = 64;
@@ -893,8 +945,8 @@ int set_error(int code, const std::string &msg) { return fail(code, msg); }
 int check_build()
 {
     const char *mine = source_hash_api();
-    const char *units[] = {source_hash_kernels(), source_hash_flow(), source_hash_mcmc(), source_hash_pop(),
-                           source_hash_relbin(), source_hash_waveform()};
+    const char *units[] = {source_hash_kernels(), source_hash_flow(), source_hash_mcmc(), source_hash_nodes(),
+                           source_hash_pop(), source_hash_relbin(), source_hash_waveform()};
     for (const char *u : units)
         if (std::strcmp(u, mine) != 0)
             return fail(GW_EABI, std::string("the library was linked from objects compiled from different sources (") +
@@ -1008,7 +1060,10 @@ int gw_workspace_reserve(gw_workspace *ws, int64_t n_bins, int n_det, int64_t n_
         for (int mixed = 0; mixed < 2; ++mixed) {
             std::vector<gw::TilePlan> plans = tuning_candidates(ws, n_bins, n_det, n_samples, mixed != 0, form);
             plans.push_back(plan_tiles(ws, n_bins, n_det, n_samples, mixed != 0, form));
-            for (const gw::TilePlan &p : plans) need = std::max(need, lnl_layout(n_bins, n_det, n_samples, p, all_flags).total);
+            for (const gw::TilePlan &p : plans) {
+                need = std::max(need, lnl_layout_as(n_bins, n_det, n_samples, p, all_flags, false).total);
+                need = std::max(need, lnl_layout_as(n_bins, n_det, n_samples, p, 0u, true).total);
+            }
         }
     size_t wave = align_up(sizeof(gw::Tab1) * n_bins) + align_up(sizeof(gw::Tab2) * n_bins) +
                   align_up(sizeof(double) * gw::record_fields(std::max(n_det, 2)) * std::max<int64_t>(n_samples, 1));
@@ -1093,7 +1148,7 @@ int gw_lnl_batch_static(const gw_grid *grid, int n_det, const gw_detector *dets,
                                    " bytes of scratch, more than the library's static " +
                                    std::to_string(kStaticScratchBytes) + "; use gw_lnl_batch with a workspace");
     return lnl_enqueue(nullptr, d->ptr, l, plan, *grid, n_det, geom, data, psd, theta, n_param, n_samples, lnl_out,
-                       mixed, flags, stream);
+                       mixed, flags, d->n_cu, stream);
 }
 
 int gw_waveform_batch(gw_workspace *ws, const gw_grid *grid, int n_det, const gw_detector *dets,

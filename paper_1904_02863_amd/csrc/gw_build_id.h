@@ -15,6 +15,7 @@ const char *source_hash_api();
 const char *source_hash_kernels();
 const char *source_hash_flow();
 const char *source_hash_mcmc();
+const char *source_hash_nodes();
 const char *source_hash_pop();
 const char *source_hash_relbin();
 const char *source_hash_waveform();

@@ -141,6 +141,8 @@ struct EventSizes {
     int prep_blocks;
 };
 
+struct NodePlan;          // gw_nodes.h
+
 // Device buffers of one event's preparation (workspace sections).
 struct EventBuffers {
     Tab1 *tab1;
@@ -154,7 +156,8 @@ struct EventBuffers {
     int prep_blocks;      // ceil(n_bins / kBlock)
     double *sums;         // [kEventSums]
     int64_t *k_limit;     // ISCO end: 1 + the largest K_s of the batch
-    unsigned *queue;      // [kQueues] work-queue counters of the tile kernel (zeroed by the event sums), or null
+    NodePlan *node_plan;  // the batch's node plan (split form on frequency nodes), or null
+    unsigned *queue;      // [2 kQueues] work-queue counters of the tile kernels (zeroed by the event sums), or null
 };
 
 // ---- launchers (gw_kernels.hip); all enqueue on `stream` and return the launch status ----
@@ -191,7 +194,7 @@ hipError_t launch_lnl_tiles(const gw_grid &grid, int n_det, int64_t n_samples, c
                             hipStream_t stream);
 
 hipError_t launch_lnl_finalize(const gw_grid &grid, int64_t n_samples, int n_det, const TilePlan &plan,
-                               const double2 *partials, const double *records, const EventBuffers &eb,
+                               bool mixed, const double2 *partials, const double *records, const EventBuffers &eb,
                                unsigned flags, double *lnl_out, hipStream_t stream);
 
 hipError_t launch_waveform(const gw_grid &grid, int n_out, int64_t n_samples, const Tab1 *tab1, const Tab2 *tab2,

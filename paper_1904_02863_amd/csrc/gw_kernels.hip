@@ -21,12 +21,15 @@
 // with R_last evaluated exactly once per tile.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "gw_build_id.h"
 #include "gw_device_math.h"
 #include "gw_internal.h"
+#include "gw_nodes.h"
 #include "gw_plan.h"
+#include "gw_reduce.h"
 #include "gw_template.h"
 
 // Tuning of the tile kernel's inner loop: bins per unrolled step (FP64 and
@@ -105,30 +108,6 @@ __device__ __forceinline__ void bin_data(const PrepView &v, int64_t k, bool dire
     }
 }
 
-// Fixed-order tree sum of x over the block; every thread gets the total.
-// `red` is kBlock doubles of LDS.  All threads must call it.
-__device__ __forceinline__ double block_sum(double x, double *red)
-{
-    red[threadIdx.x] = x;
-    __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    const double total = red[0];
-    __syncthreads();
-    return total;
-}
-
-// Sum over the 64 lanes of a wave by a fixed butterfly (lane 0's value is
-// the one used).
-__device__ __forceinline__ double wave_sum(double x)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-    return x;
-}
-
 // Block b of an event's preparation: bins [256 b, 256 b + 256); writes the
 // block's sums out[kPrepPerDet d + j] (wave sums, then the 4 waves in order).
 // `red` holds at least 4 kPrepPerDet kMaxDet doubles of LDS.
@@ -154,16 +133,6 @@ __device__ __forceinline__ void prep_block(const PrepView &v, int64_t b, bool di
         out[threadIdx.x] = ((red[threadIdx.x] + red[kQ + threadIdx.x]) + red[2 * kQ + threadIdx.x]) +
                            red[3 * kQ + threadIdx.x];
     __syncthreads();
-}
-
-// Column j of an event's per-block partials summed over its n_blocks blocks
-// (strided per thread, then a fixed tree): the event-wide sum of quantity j.
-__device__ __forceinline__ double column_total(int n_blocks, int per, int j, const double *__restrict__ partials,
-                                               double *red)
-{
-    double x = 0.0;
-    for (int b = threadIdx.x; b < n_blocks; b += kBlock) x += partials[(int64_t)b * per + j];
-    return block_sum(x, red);
 }
 
 // Inclusive Hillis-Steele scan of x over the block (fixed order); `red` is
@@ -330,10 +299,18 @@ __global__ __launch_bounds__(kBlock) void ragged_prefix_kernel(const RaggedEvent
 // channel 1 is h_cross.  The template's last bin K_s is n_bins - 1, or with
 // the ISCO end the last bin with f_k <= f_isco = 1 / (6^(3/2) pi M) (-1 when
 // there is none, and for samples that are not evaluated).
+// What a sample adds to the range of the batch's phase coefficients (kStatPairs
+// of gw_nodes.h): lo[j] = hi[j] but for the arrival times, whose pair spans
+// the detectors; ok: the sample is evaluated.
+struct SampleRange {
+    double lo[kStatPairs], tau_hi;
+    bool ok;
+};
+
 __device__ __forceinline__ void prep_sample(double f_low, double df, int64_t n_bins, int64_t s, int64_t n_samples,
                                             int n_param, int n_out, bool polarisations, bool isco,
                                             const DetGeom &geom, const double *__restrict__ theta,
-                                            double *__restrict__ rec)
+                                            double *__restrict__ rec, SampleRange *range = nullptr)
 {
     double t[kMaxParam];
 #pragma unroll
@@ -411,6 +388,21 @@ __device__ __forceinline__ void prep_sample(double f_low, double df, int64_t n_b
         }
     }
     const double tau0 = tc + dt[0];
+    if (range) {
+        double first = dt[0], last = dt[0];
+#pragma unroll
+        for (int d = 1; d < kMaxDet; ++d) {
+            if (d < n_out) {
+                first = fmin(first, dt[d]);
+                last = fmax(last, dt[d]);
+            }
+        }
+        const double v[kStatPairs] = {tc + first, cj[7], cj[6], cjl[6], cjl[5], cj[4], cj[3], cj[2], cj[0]};
+#pragma unroll
+        for (int j = 0; j < kStatPairs; ++j) range->lo[j] = v[j];
+        range->tau_hi = tc + last;
+        range->ok = status == 0;
+    }
 
     const double amp0 = sqrt(5.0 / 24.0) * pow(GW_PI, -2.0 / 3.0) * pow(mc * GW_MSUN_S, 5.0 / 6.0) / (dl * GW_MPC_S);
     const double rot_re = cos(phic + 0.25 * GW_PI), rot_im = sin(phic + 0.25 * GW_PI);
@@ -491,6 +483,65 @@ __global__ __launch_bounds__(kBlock) void event_data_kernel(PrepView v, int dire
     prep_block(v, b, direct != 0, norm != 0, red, partials + b * kPrepPerDet * v.n_det);
 }
 
+// The batch's range of each phase coefficient over the 64 samples of a wave:
+// entry[2 j], entry[2 j + 1] the smallest and largest (+inf, -inf when none of
+// the samples is evaluated).
+__device__ __forceinline__ void write_range(const SampleRange &r, bool live, double *__restrict__ entry)
+{
+    const bool ok = live && r.ok;
+#pragma unroll
+    for (int j = 0; j < kStatPairs; ++j) {
+        double lo = ok ? r.lo[j] : INFINITY, hi = ok ? (j == 0 ? r.tau_hi : r.lo[j]) : -INFINITY;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            lo = fmin(lo, __shfl_xor(lo, off, 64));
+            hi = fmax(hi, __shfl_xor(hi, off, 64));
+        }
+        if (threadIdx.x % 64 == 0) {
+            entry[2 * j] = lo;
+            entry[2 * j + 1] = hi;
+        }
+    }
+}
+
+// Sample records and their ranges, a wave of 64 samples per block: each
+// sample is one long chain of dependent FP64 work, so the chain's latency is
+// the kernel's time and the waves are spread over as many CUs as there are.
+__global__ __launch_bounds__(64) void node_samples_kernel(double f_low, double df, int64_t n_bins, int n_det,
+                                                           SamplePrep sp, double *__restrict__ stats)
+{
+    const int64_t s = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    const bool live = s < sp.n_samples;
+    SampleRange r;
+    prep_sample(f_low, df, n_bins, live ? s : sp.n_samples - 1, sp.n_samples, sp.n_param, n_det, false, false, sp.geom,
+                sp.theta, sp.records, &r);
+    write_range(r, live, stats + (int64_t)blockIdx.x * kStats);
+}
+
+// Block j: out[j] = the smallest (j even) or largest (j odd) of column j over
+// n entries.
+__global__ __launch_bounds__(kBlock) void node_range_kernel(int64_t n, const double *__restrict__ stats,
+                                                             double *__restrict__ out)
+{
+    __shared__ double red[kBlock];
+    const int j = blockIdx.x;
+    const bool low = j % 2 == 0;
+    double m = low ? INFINITY : -INFINITY;
+    for (int64_t e = threadIdx.x; e < n; e += kBlock) {
+        const double v = stats[e * kStats + j];
+        m = low ? fmin(m, v) : fmax(m, v);
+    }
+    red[threadIdx.x] = m;
+    __syncthreads();
+    for (int w = kBlock / 2; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w)
+            red[threadIdx.x] = low ? fmin(red[threadIdx.x], red[threadIdx.x + w])
+                                   : fmax(red[threadIdx.x], red[threadIdx.x + w]);
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) out[j] = red[0];
+}
+
 // *k_limit = 1 + the largest K_s of the batch (one block).
 __global__ __launch_bounds__(kBlock) void isco_limit_kernel(int64_t n_samples, const double *__restrict__ rec,
                                                              int64_t *__restrict__ k_limit)
@@ -541,6 +592,7 @@ struct EventView {
     const double *rec;
     const int64_t *k_limit;    // split form with the ISCO end: 1 + max K_s (device)
     double2 *partials;         // double [chunk][n_samples]: sum_det Re(P_det Z_det) (split), residual sum (direct)
+    const NodePlan *plan;      // node kernels: the batch's plan (device), else null
 };
 
 // LDS layout of a tile: tab1 [tile], then per detector D (split) or d/a
@@ -570,6 +622,98 @@ __device__ __forceinline__ double *stage_phasor_table(double4 *lds_raw)
     return reinterpret_cast<double *>(lds_raw);
 }
 
+// The bins (or nodes) 0 .. nk - 1 of one staged tile against this thread's
+// sample: the split forms' Z_0 and Horner sums S_d, or the direct form's residual
+// sum with its running T_d.  MIXED takes the phasor from the FP32 hardware
+// sine and cosine; otherwise it comes from the LDS table, cf scaled for it.
+// Bins past jcut carry no template (the forms that end templates).
+template <int NDET, bool MIXED, int FORM>
+__device__ __forceinline__ void tile_loop(const PhaseCoef &cf, const double2 *ptab, const Tab1 *lt, const double2 *ld,
+                                          const double *lv, int tile_bins, int nk, int jcut,
+                                          const double (&rho_re)[NDET], const double (&rho_im)[NDET],
+                                          double (&sr_)[NDET], double (&si_)[NDET], double &z0r, double &z0i,
+                                          double &acc)
+{
+    constexpr bool kDirect = FORM == kFormDirect;
+    constexpr bool kMasked = FORM != kFormSplit;
+#pragma unroll(MIXED ? kTileUnrollMixed : kTileUnroll)
+    for (int j = 0; j < nk; ++j) {
+        const Tab1 tb = lt[j];
+        double er, ei;
+        if constexpr (MIXED) {
+            // FP64 phase and exact reduction to a fractional turn, then the
+            // hardware sine and cosine (inputs in turns) in FP32
+            const double x = turns_phase(cf, tb);
+            const float r = (float)(x - __builtin_rint(x));
+            er = (double)__builtin_amdgcn_cosf(r);
+            ei = -(double)__builtin_amdgcn_sinf(r);
+        } else {
+#if GW_PHASOR_TABLE
+            gw_phasor_table(turns_phase(cf, tb), ptab, er, ei);
+#else
+            gw_phasor_turns(turns_phase(cf, tb), er, ei);
+#endif
+        }
+        if (kMasked && j > jcut) {
+            er = 0.0;
+            ei = 0.0;
+        }
+        if constexpr (kDirect) {
+#pragma unroll
+            for (int d = 0; d < NDET; ++d) {
+                const double2 e = ld[d * tile_bins + j];
+                const double v = lv[d * tile_bins + j];
+                // residual d/a - P_d e^{-i Phi_d}
+                double rr = __builtin_fma(-er, sr_[d], e.x);
+                rr = __builtin_fma(ei, si_[d], rr);
+                double ri = __builtin_fma(-er, si_[d], e.y);
+                ri = __builtin_fma(-ei, sr_[d], ri);
+                acc = __builtin_fma(v, __builtin_fma(rr, rr, ri * ri), acc);
+                if (d > 0) {
+                    const double tr = sr_[d] * rho_re[d] - si_[d] * rho_im[d];
+                    si_[d] = sr_[d] * rho_im[d] + si_[d] * rho_re[d];
+                    sr_[d] = tr;
+                }
+            }
+        } else {
+            const double2 d0 = ld[j];
+            z0r = __builtin_fma(d0.x, er, z0r);
+            z0r = __builtin_fma(-d0.y, ei, z0r);
+            z0i = __builtin_fma(d0.x, ei, z0i);
+            z0i = __builtin_fma(d0.y, er, z0i);
+#pragma unroll
+            for (int d = 1; d < NDET; ++d) {
+                const double2 dv = ld[d * tile_bins + j];
+                double tr = dv.x * er;
+                tr = __builtin_fma(-dv.y, ei, tr);
+                tr = __builtin_fma(sr_[d], rho_re[d], tr);
+                tr = __builtin_fma(si_[d], rho_im[d], tr);
+                double ti = dv.x * ei;
+                ti = __builtin_fma(dv.y, er, ti);
+                ti = __builtin_fma(si_[d], rho_re[d], ti);
+                ti = __builtin_fma(-sr_[d], rho_im[d], ti);
+                sr_[d] = tr;
+                si_[d] = ti;
+            }
+        }
+    }
+}
+
+// What a tile kernel sums: every bin; the plan's single bins and nodes; or one of
+// these (the mixed path runs them as two launches, since its FP32 phasors serve
+// the bins, where three blocks a CU without the table run best, and the
+// nodes, few and each standing for many bins, take FP64 phasors).
+enum NodeMode : int { kNoNodes = 0, kBinsAndNodes, kNodeBins, kNodesOnly };
+
+// A run of evenly spaced frequencies f(i) = f_low + (k0 + i step) df, i in
+// [begin, end): the bins themselves (k0 = 0, step = 1), or the nodes of a level.
+struct FreqRun {
+    const Tab1 *tab1;         // indexed by i
+    const double2 *src;       // detector d's values at src + d n_bins, indexed by i
+    int64_t k0, begin, end;
+    int step;
+};
+
 // The 256 samples of `group` (one per thread) against bins [k_begin, k_end)
 // of one event, staged through LDS tile by tile and shared by all the
 // block's samples; writes the chunk's partial sums of every sample.
@@ -580,11 +724,18 @@ __device__ __forceinline__ double *stage_phasor_table(double4 *lds_raw)
 // FORM (TileForm): the split forms accumulate Z_det (kFormSplitIsco only
 // over bins k <= K_s of each sample); the direct form accumulates
 // sum_det a^2/S |d/a - P_det e^{-i Phi_det}|^2 with the template zero above K_s.
+// NODES (split form, NodeMode): the bins and then nodes [n_begin, n_end) of the
+// batch's plan, run by run over its levels, or one of the two, all with the
+// coefficients less the plan's reference.  With kNodesOnly the chunk's totals
+// below n_add are already those of a kNodeBins pass, and this adds to them.
 // All threads of the block must call this with the same arguments.
-template <int NDET, bool MIXED, int FORM>
+template <int NDET, bool MIXED, int FORM, int NODES>
 __device__ __forceinline__ void tile_chunk(const EventView &ev, int group, int64_t chunk, int64_t k_begin,
-                                           int64_t k_end, int tile_bins, double *lds)
+                                           int64_t k_end, int64_t n_begin, int64_t n_end, int n_add, int tile_bins,
+                                           double *lds)
 {
+    static_assert(NODES == kNoNodes || FORM == kFormSplit, "nodes serve the split form only");
+    static_assert(!MIXED || NODES == kNoNodes || NODES == kNodeBins, "the nodes take FP64 phasors");
     // the phasor table sits just below the tiles (FP64 path; the mixed path has none)
     const double2 *ptab =
         (GW_PHASOR_TABLE && !MIXED) ? reinterpret_cast<const double2 *>(lds) - GW_PHTAB_N : nullptr;
@@ -592,8 +743,6 @@ __device__ __forceinline__ void tile_chunk(const EventView &ev, int group, int64
     constexpr bool kMasked = FORM != kFormSplit;
     const int64_t n_bins = ev.n_bins, n_samples = ev.n_samples;
     const double f_low = ev.f_low, df = ev.df;
-    const Tab1 *__restrict__ tab1 = ev.tab1;
-    const double2 *__restrict__ dsrc = kDirect ? ev.edir : ev.dcoef;
     const double *__restrict__ vdir = ev.vdir;
     const double *__restrict__ rec = ev.rec;
     const int64_t s = (int64_t)group * kBlock + threadIdx.x;
@@ -603,6 +752,7 @@ __device__ __forceinline__ void tile_chunk(const EventView &ev, int group, int64
     double *lv = reinterpret_cast<double *>(ld + NDET * tile_bins);
 
     PhaseCoef cf = load_coef(rec, n_samples, sr);
+    if constexpr (NODES != kNoNodes) cf = coef_less(cf, load_coef(ev.plan->mid, 1, 0));
 #if GW_PHASOR_TABLE
     // the table phasor takes the phase in units of 1/N turn (exact: N is a power of two)
     if constexpr (!MIXED) cf = scale_coef(cf, (double)GW_PHTAB_N);
@@ -617,117 +767,76 @@ __device__ __forceinline__ void tile_chunk(const EventView &ev, int group, int64
         }
         if (d == 0) continue;
         delta[d] = rec[(kRecDet + kRecFieldsPerDet * d + 2) * n_samples + sr];
-        gw_phasor_turns(df * delta[d], rho_re[d], rho_im[d]);
     }
     double zr[NDET], zi[NDET];
 #pragma unroll
     for (int d = 0; d < NDET; ++d) { zr[d] = 0.0; zi[d] = 0.0; }
     double acc = 0.0;
 
-    for (int64_t t0 = k_begin; t0 < k_end; t0 += tile_bins) {
-        const int nk = (int)min((int64_t)tile_bins, k_end - t0);
-        __syncthreads();
-        for (int i = threadIdx.x; i < nk; i += kBlock) {
-            lt[i] = tab1[t0 + i];
-#pragma unroll
-            for (int d = 0; d < NDET; ++d) {
-                ld[d * tile_bins + i] = dsrc[(int64_t)d * n_bins + t0 + i];
-                if (kDirect) lv[d * tile_bins + i] = vdir[(int64_t)d * n_bins + t0 + i];
+    const int n_runs = NODES == kBinsAndNodes || NODES == kNodesOnly ? 1 + ev.plan->n_levels : 1;
+    for (int run = NODES == kNodesOnly ? 1 : 0; run < n_runs; ++run) {
+        FreqRun fr{ev.tab1, kDirect ? ev.edir : ev.dcoef, 0, k_begin, k_end, 1};
+        if constexpr (NODES != kNoNodes) {
+            if (run > 0) {
+                const NodeLevel &v = ev.plan->level[run - 1];
+                const int64_t nodes = v.k0 + node_slots(v);      // where the level's nodes stand in D
+                fr.src = ev.dcoef + nodes;
+                fr.tab1 = reinterpret_cast<const Tab1 *>(ev.dcoef + nodes + node_count(v));
+                fr.k0 = v.k0 - (int64_t)kTapsBelow * v.q;
+                fr.step = v.q;
+                fr.begin = max(n_begin - v.node0, (int64_t)0);
+                fr.end = min(n_end - v.node0, (int64_t)node_count(v));
             }
         }
-        __syncthreads();
-        // last live bin of this lane within the tile (template end)
-        const int jcut = kMasked ? (int)max((int64_t)-1, min(kcut - t0, (int64_t)nk - 1)) : nk - 1;
-        // split: Horner sums S_d over the tile; direct: T_d = P_d e^{-2 pi i f delta_d} at the current bin
-        double sr_[NDET], si_[NDET];
+        if (fr.begin >= fr.end) continue;
 #pragma unroll
-        for (int d = 0; d < NDET; ++d) { sr_[d] = 0.0; si_[d] = 0.0; }
-        if (kDirect) {
-            const double f_first = __dadd_rn(f_low, __dmul_rn((double)t0, df));
-#pragma unroll
-            for (int d = 0; d < NDET; ++d) {
-                if (d == 0) {
-                    sr_[0] = p_re[0];
-                    si_[0] = p_im[0];
-                    continue;
-                }
-                double rr, ri;
-                gw_phasor_turns(f_first * delta[d], rr, ri);
-                sr_[d] = p_re[d] * rr - p_im[d] * ri;
-                si_[d] = p_re[d] * ri + p_im[d] * rr;
-            }
-        }
-#pragma unroll(MIXED ? kTileUnrollMixed : kTileUnroll)
-        for (int j = 0; j < nk; ++j) {
-            const Tab1 tb = lt[j];
-            double er, ei;
-            if constexpr (MIXED) {
-                // FP64 phase and exact reduction to a fractional turn, then the
-                // hardware sine and cosine (inputs in turns) in FP32
-                const double x = turns_phase(cf, tb);
-                const float r = (float)(x - __builtin_rint(x));
-                er = (double)__builtin_amdgcn_cosf(r);
-                ei = -(double)__builtin_amdgcn_sinf(r);
-            } else {
-#if GW_PHASOR_TABLE
-                gw_phasor_table(turns_phase(cf, tb), ptab, er, ei);
-#else
-                gw_phasor_turns(turns_phase(cf, tb), er, ei);
-#endif
-            }
-            if (kMasked && j > jcut) {
-                er = 0.0;
-                ei = 0.0;
-            }
-            if constexpr (kDirect) {
+        for (int d = 1; d < NDET; ++d) gw_phasor_turns((double)fr.step * df * delta[d], rho_re[d], rho_im[d]);
+        for (int64_t t0 = fr.begin; t0 < fr.end; t0 += tile_bins) {
+            const int nk = (int)min((int64_t)tile_bins, fr.end - t0);
+            __syncthreads();
+            for (int i = threadIdx.x; i < nk; i += kBlock) {
+                lt[i] = fr.tab1[t0 + i];
 #pragma unroll
                 for (int d = 0; d < NDET; ++d) {
-                    const double2 e = ld[d * tile_bins + j];
-                    const double v = lv[d * tile_bins + j];
-                    // residual d/a - P_d e^{-i Phi_d}
-                    double rr = __builtin_fma(-er, sr_[d], e.x);
-                    rr = __builtin_fma(ei, si_[d], rr);
-                    double ri = __builtin_fma(-er, si_[d], e.y);
-                    ri = __builtin_fma(-ei, sr_[d], ri);
-                    acc = __builtin_fma(v, __builtin_fma(rr, rr, ri * ri), acc);
-                    if (d > 0) {
-                        const double tr = sr_[d] * rho_re[d] - si_[d] * rho_im[d];
-                        si_[d] = sr_[d] * rho_im[d] + si_[d] * rho_re[d];
-                        sr_[d] = tr;
-                    }
-                }
-            } else {
-                const double2 d0 = ld[j];
-                zr[0] = __builtin_fma(d0.x, er, zr[0]);
-                zr[0] = __builtin_fma(-d0.y, ei, zr[0]);
-                zi[0] = __builtin_fma(d0.x, ei, zi[0]);
-                zi[0] = __builtin_fma(d0.y, er, zi[0]);
-#pragma unroll
-                for (int d = 1; d < NDET; ++d) {
-                    const double2 dv = ld[d * tile_bins + j];
-                    double tr = dv.x * er;
-                    tr = __builtin_fma(-dv.y, ei, tr);
-                    tr = __builtin_fma(sr_[d], rho_re[d], tr);
-                    tr = __builtin_fma(si_[d], rho_im[d], tr);
-                    double ti = dv.x * ei;
-                    ti = __builtin_fma(dv.y, er, ti);
-                    ti = __builtin_fma(si_[d], rho_re[d], ti);
-                    ti = __builtin_fma(-sr_[d], rho_im[d], ti);
-                    sr_[d] = tr;
-                    si_[d] = ti;
+                    ld[d * tile_bins + i] = fr.src[(int64_t)d * n_bins + t0 + i];
+                    if (kDirect) lv[d * tile_bins + i] = vdir[(int64_t)d * n_bins + t0 + i];
                 }
             }
-        }
-        if (!kDirect && NDET > 1) {
-            const double f_last = __dadd_rn(f_low, __dmul_rn((double)(t0 + nk - 1), df));
+            __syncthreads();
+            // last live bin of this lane within the tile (template end)
+            const int jcut = kMasked ? (int)max((int64_t)-1, min(kcut - t0, (int64_t)nk - 1)) : nk - 1;
+            // split: Horner sums S_d over the tile; direct: T_d = P_d e^{-2 pi i f delta_d} at the current bin
+            double sr_[NDET], si_[NDET];
 #pragma unroll
-            for (int d = 1; d < NDET; ++d) {
-                double rr, ri;
-                gw_phasor_turns(f_last * delta[d], rr, ri);
-                zr[d] = __builtin_fma(rr, sr_[d], zr[d]);
-                zr[d] = __builtin_fma(-ri, si_[d], zr[d]);
-                zi[d] = __builtin_fma(rr, si_[d], zi[d]);
-                zi[d] = __builtin_fma(ri, sr_[d], zi[d]);
+            for (int d = 0; d < NDET; ++d) { sr_[d] = 0.0; si_[d] = 0.0; }
+            if (kDirect) {
+                const double f_first = bin_frequency(f_low, df, t0);
+#pragma unroll
+                for (int d = 0; d < NDET; ++d) {
+                    if (d == 0) {
+                        sr_[0] = p_re[0];
+                        si_[0] = p_im[0];
+                        continue;
+                    }
+                    double rr, ri;
+                    gw_phasor_turns(f_first * delta[d], rr, ri);
+                    sr_[d] = p_re[d] * rr - p_im[d] * ri;
+                    si_[d] = p_re[d] * ri + p_im[d] * rr;
+                }
+            }
+            tile_loop<NDET, MIXED, FORM>(cf, ptab, lt, ld, lv, tile_bins, nk, jcut, rho_re, rho_im, sr_, si_, zr[0],
+                                         zi[0], acc);
+            if (!kDirect && NDET > 1) {
+                const double f_last = bin_frequency(f_low, df, fr.k0 + (t0 + nk - 1) * fr.step);
+#pragma unroll
+                for (int d = 1; d < NDET; ++d) {
+                    double rr, ri;
+                    gw_phasor_turns(f_last * delta[d], rr, ri);
+                    zr[d] = __builtin_fma(rr, sr_[d], zr[d]);
+                    zr[d] = __builtin_fma(-ri, si_[d], zr[d]);
+                    zi[d] = __builtin_fma(rr, si_[d], zi[d]);
+                    zi[d] = __builtin_fma(ri, sr_[d], zi[d]);
+                }
             }
         }
     }
@@ -743,7 +852,9 @@ __device__ __forceinline__ void tile_chunk(const EventView &ev, int group, int64
                 acc = __builtin_fma(-pi, zi[d], acc);
             }
         }
-        reinterpret_cast<double *>(ev.partials)[chunk * n_samples + s] = acc;
+        double *out = reinterpret_cast<double *>(ev.partials) + chunk * n_samples + s;
+        if (NODES == kNodesOnly && chunk < n_add) acc += *out;
+        *out = acc;
     }
 }
 
@@ -761,36 +872,50 @@ __device__ __forceinline__ void tile_chunk(const EventView &ev, int group, int64
 // others in turn.  With the ISCO end (split form) the chunks cover only the
 // bins below 1 + max K_s, read from the device, so that no block works on
 // bins every template has left.
-template <int NDET, bool MIXED, int FORM>
-__global__ __launch_bounds__(kBlock) GW_TILE_ATTR void lnl_tile_kernel(EventView ev, int n_groups, int n_chunks,
-                                                                       int rounds, int tile_bins,
-                                                                       unsigned *__restrict__ queue)
+// NODES: bins below the plan's k_bin, then the nodes; a chunk takes the same
+// share of both, and the plan made on the device sets how many of the host's
+// chunks and rounds the batch needs.
+// At least two waves per SIMD: a SIMD with one issues FP64 at half rate.
+template <int NDET, bool MIXED, int FORM, int NODES>
+__global__ __launch_bounds__(kBlock, 2) GW_TILE_ATTR void lnl_tile_kernel(EventView ev, int n_groups, int n_chunks,
+                                                                          int rounds, int tile_bins,
+                                                                          unsigned *__restrict__ queue)
 {
     extern __shared__ double4 lds_raw[];
     __shared__ int next_chunk, next_group;
-    const int64_t n_eff =
-        FORM == kFormSplitIsco ? min(ev.n_bins, max((int64_t)0, *ev.k_limit)) : ev.n_bins;
-    double *const tiles = stage_phasor_table<MIXED>(lds_raw);
-    if (queue == nullptr) {
-        const unsigned nb = gridDim.x, b = blockIdx.x;
-        const unsigned w = (nb % 8u == 0u) ? (b % 8u) * (nb / 8u) + b / 8u : b;
-        int64_t k_begin, k_end;
-        chunk_range(n_eff, (int64_t)(w / (unsigned)n_groups), n_chunks, rounds, k_begin, k_end);
-        tile_chunk<NDET, MIXED, FORM>(ev, (int)(w % (unsigned)n_groups), (int64_t)(w / (unsigned)n_groups), k_begin,
-                                      k_end, tile_bins, tiles);
-        return;
+    int64_t n_eff = FORM == kFormSplitIsco ? min(ev.n_bins, max((int64_t)0, *ev.k_limit)) : ev.n_bins;
+    int64_t n_nodes = 0;
+    int n_add = 0;
+    if constexpr (NODES != kNoNodes) {
+        n_eff = NODES == kNodesOnly ? 0 : ev.plan->k_bin;
+        n_nodes = NODES == kNodeBins ? 0 : ev.plan->n_nodes;
+        if (NODES != kBinsAndNodes && n_eff + n_nodes == 0) return;
+        if (NODES == kNodesOnly) n_add = node_chunks_of(ev.plan->k_bin, n_chunks, rounds);
+        node_split(n_eff + n_nodes, n_chunks, rounds, n_chunks, rounds);
     }
+    // without a queue the block has one item
+    const unsigned nb = gridDim.x, b = blockIdx.x;
+    const unsigned w = (nb % 8u == 0u) ? (b % 8u) * (nb / 8u) + b / 8u : b;
+    if (NODES && queue == nullptr && (int)(w / (unsigned)n_groups) >= n_chunks) return;
+    double *const tiles = stage_phasor_table<MIXED>(lds_raw);
     const unsigned home = blockIdx.x % kQueues;
-    unsigned visited = 0;                // queues found empty (thread 0)
+    unsigned visited = 0;                // queues found empty, or (no queue) the item taken (thread 0)
     for (;;) {
         __syncthreads();                 // every thread has read the item and left the LDS tiles
         if (threadIdx.x == 0) {
             int chunk = -1, group = 0;
-            while (visited < kQueues) {
-                const unsigned x = (home + visited) % kQueues;
-                const int k = (int)atomicAdd(queue + x, 1u);
-                if (queue_item((int)x, k, n_groups, n_chunks, chunk, group)) break;
-                ++visited;
+            if (queue == nullptr) {
+                if (visited++ == 0u) {
+                    chunk = (int)(w / (unsigned)n_groups);
+                    group = (int)(w % (unsigned)n_groups);
+                }
+            } else {
+                while (visited < kQueues) {
+                    const unsigned x = (home + visited) % kQueues;
+                    const int k = (int)atomicAdd(queue + x, 1u);
+                    if (queue_item((int)x, k, n_groups, n_chunks, chunk, group)) break;
+                    ++visited;
+                }
             }
             next_chunk = chunk;
             next_group = group;
@@ -798,9 +923,11 @@ __global__ __launch_bounds__(kBlock) GW_TILE_ATTR void lnl_tile_kernel(EventView
         __syncthreads();
         const int chunk = next_chunk;
         if (chunk < 0) break;
-        int64_t k_begin, k_end;
+        int64_t k_begin, k_end, n_begin = 0, n_end = 0;
         chunk_range(n_eff, chunk, n_chunks, rounds, k_begin, k_end);
-        tile_chunk<NDET, MIXED, FORM>(ev, next_group, chunk, k_begin, k_end, tile_bins, tiles);
+        if constexpr (NODES != kNoNodes) chunk_range(n_nodes, chunk, n_chunks, rounds, n_begin, n_end);
+        tile_chunk<NDET, MIXED, FORM, NODES>(ev, next_group, chunk, k_begin, k_end, n_begin, n_end, n_add, tile_bins,
+                                             tiles);
     }
 }
 
@@ -837,9 +964,10 @@ __global__ __launch_bounds__(kBlock) GW_TILE_ATTR void lnl_ragged_kernel(const R
         ev.rec = re.rec;
         ev.k_limit = nullptr;
         ev.partials = re.partials;
+        ev.plan = nullptr;
         const int64_t k_begin = (int64_t)wi.chunk * re.chunk_bins;
         const int64_t k_end = min(re.n_bins, k_begin + re.chunk_bins);
-        tile_chunk<NDET, MIXED, FORM>(ev, wi.group, wi.chunk, k_begin, k_end, tile_bins, tiles);
+        tile_chunk<NDET, MIXED, FORM, kNoNodes>(ev, wi.group, wi.chunk, k_begin, k_end, 0, 0, 0, tile_bins, tiles);
     }
 }
 
@@ -904,9 +1032,14 @@ __global__ __launch_bounds__(kBlock) void lnl_finalize_kernel(int64_t n_samples,
                                                                const double *__restrict__ rec,
                                                                const double *__restrict__ sums,
                                                                const double *__restrict__ qprefix,
-                                                               double *__restrict__ lnl)
+                                                               const NodePlan *__restrict__ plan, int rounds,
+                                                               int mixed, double *__restrict__ lnl)
 {
     __shared__ double red[kFinParts][kFinRows];
+    if (plan)
+        n_chunks = mixed ? max(node_chunks_of(plan->k_bin, n_chunks, rounds),
+                               node_chunks_of(plan->n_nodes, n_chunks, rounds))
+                         : node_chunks_of(plan->k_bin + plan->n_nodes, n_chunks, rounds);
     const int r = threadIdx.x % kFinRows, part = threadIdx.x / kFinRows;
     const int64_t s = (int64_t)blockIdx.x * kFinRows + r;
     if (s < n_samples) {
@@ -998,6 +1131,20 @@ hipError_t launch_isco_limit(int64_t n_samples, const double *records, int64_t *
     return hipGetLastError();
 }
 
+hipError_t launch_node_samples(const gw_grid &grid, int n_det, const SamplePrep &sp, double *stats,
+                               hipStream_t stream)
+{
+    const int64_t entries = node_stat_entries(sp.n_samples);
+    if (entries > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(node_samples_kernel, dim3((unsigned)entries), dim3(64), 0, stream, grid.f_low, grid.delta_f,
+                       grid.n_bins, n_det, sp, stats);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || entries <= kStatEntries) return e;
+    hipLaunchKernelGGL(node_range_kernel, dim3(kStats), dim3(kBlock), 0, stream, entries, stats,
+                       stats + entries * kStats);
+    return hipGetLastError();
+}
+
 size_t lnl_tile_lds_bytes(int n_det, int tile_bins, int form, bool mixed)
 {
     return tile_lds_bytes(n_det, tile_bins, form, mixed);
@@ -1007,9 +1154,9 @@ template <int NDET, bool MIXED>
 static const void *tile_kernel_form(int form)
 {
     switch (form) {
-    case kFormSplit: return reinterpret_cast<const void *>(&lnl_tile_kernel<NDET, MIXED, kFormSplit>);
-    case kFormSplitIsco: return reinterpret_cast<const void *>(&lnl_tile_kernel<NDET, MIXED, kFormSplitIsco>);
-    default: return reinterpret_cast<const void *>(&lnl_tile_kernel<NDET, MIXED, kFormDirect>);
+    case kFormSplit: return reinterpret_cast<const void *>(&lnl_tile_kernel<NDET, MIXED, kFormSplit, kNoNodes>);
+    case kFormSplitIsco: return reinterpret_cast<const void *>(&lnl_tile_kernel<NDET, MIXED, kFormSplitIsco, kNoNodes>);
+    default: return reinterpret_cast<const void *>(&lnl_tile_kernel<NDET, MIXED, kFormDirect, kNoNodes>);
     }
 }
 
@@ -1020,6 +1167,31 @@ static const void *ragged_kernel_form(int form)
     case kFormSplit: return reinterpret_cast<const void *>(&lnl_ragged_kernel<NDET, MIXED, kFormSplit>);
     case kFormSplitIsco: return reinterpret_cast<const void *>(&lnl_ragged_kernel<NDET, MIXED, kFormSplitIsco>);
     default: return reinterpret_cast<const void *>(&lnl_ragged_kernel<NDET, MIXED, kFormDirect>);
+    }
+}
+
+template <int NDET>
+static const void *node_kernel(NodeMode mode)
+{
+    switch (mode) {
+    case kNodeBins: return reinterpret_cast<const void *>(&lnl_tile_kernel<NDET, true, kFormSplit, kNodeBins>);
+    case kNodesOnly: return reinterpret_cast<const void *>(&lnl_tile_kernel<NDET, false, kFormSplit, kNodesOnly>);
+    default: return reinterpret_cast<const void *>(&lnl_tile_kernel<NDET, false, kFormSplit, kBinsAndNodes>);
+    }
+}
+
+static const void *node_kernel_for(int n_det, NodeMode mode)
+{
+    switch (n_det) {
+    case 1: return node_kernel<1>(mode);
+    case 2: return node_kernel<2>(mode);
+    case 3: return node_kernel<3>(mode);
+    case 4: return node_kernel<4>(mode);
+    case 5: return node_kernel<5>(mode);
+    case 6: return node_kernel<6>(mode);
+    case 7: return node_kernel<7>(mode);
+    case 8: return node_kernel<8>(mode);
+    default: return nullptr;
     }
 }
 
@@ -1077,14 +1249,23 @@ hipError_t launch_lnl_tiles(const gw_grid &grid, int n_det, int64_t n_samples, c
     ev.rec = records;
     ev.k_limit = eb.k_limit;
     ev.partials = partials;
-    const void *fn = kernel_for(false, n_det, mixed, form);
-    if (!fn) return hipErrorInvalidValue;
-    int n_groups = plan.n_groups, n_chunks = plan.n_chunks, rounds = plan.rounds, tile_bins = plan.tile_bins;
+    ev.plan = eb.node_plan;
+    int n_groups = plan.n_groups, n_chunks = plan.n_chunks, rounds = plan.rounds;
+    if (plan.rounds > 0 && !eb.queue) return hipErrorInvalidValue;
+    auto launch = [&](const void *fn, bool mixed_kernel, int tile_bins, unsigned *queue) {
+        if (!fn) return hipErrorInvalidValue;
+        void *args[] = {&ev, &n_groups, &n_chunks, &rounds, &tile_bins, &queue};
+        return hipLaunchKernel(fn, dim3((unsigned)plan.blocks), dim3(kBlock), args,
+                               tile_lds_bytes(n_det, tile_bins, form, mixed_kernel), stream);
+    };
     unsigned *queue = plan.rounds > 0 ? eb.queue : nullptr;
-    if (plan.rounds > 0 && !queue) return hipErrorInvalidValue;
-    void *args[] = {&ev, &n_groups, &n_chunks, &rounds, &tile_bins, &queue};
-    return hipLaunchKernel(fn, dim3((unsigned)plan.blocks), dim3(kBlock), args,
-                           tile_lds_bytes(n_det, plan.tile_bins, form, mixed), stream);
+    if (!eb.node_plan) return launch(kernel_for(false, n_det, mixed, form), mixed, plan.tile_bins, queue);
+    if (form != kFormSplit) return hipErrorInvalidValue;
+    if (!mixed) return launch(node_kernel_for(n_det, kBinsAndNodes), false, plan.tile_bins, queue);
+    hipError_t e = launch(node_kernel_for(n_det, kNodeBins), true, plan.tile_bins, queue);
+    if (e != hipSuccess) return e;
+    return launch(node_kernel_for(n_det, kNodesOnly), false, std::min(plan.tile_bins, tile_bins_for(n_det, form, false)),
+                  queue ? queue + kQueues : nullptr);
 }
 
 hipError_t launch_ragged(const RaggedLaunch &r, hipStream_t stream)
@@ -1128,13 +1309,13 @@ hipError_t launch_ragged(const RaggedLaunch &r, hipStream_t stream)
 }
 
 hipError_t launch_lnl_finalize(const gw_grid &grid, int64_t n_samples, int n_det, const TilePlan &plan,
-                               const double2 *partials, const double *records, const EventBuffers &eb,
+                               bool mixed, const double2 *partials, const double *records, const EventBuffers &eb,
                                unsigned flags, double *lnl_out, hipStream_t stream)
 {
     const int64_t blocks = (n_samples + kFinRows - 1) / kFinRows;
     hipLaunchKernelGGL(lnl_finalize_kernel, dim3((unsigned)blocks), dim3(kBlock), 0, stream, n_samples, n_det,
                        plan.n_chunks, grid.n_bins, grid.delta_f, flags, partials, records, eb.sums, eb.qprefix,
-                       lnl_out);
+                       eb.node_plan, plan.rounds, mixed ? 1 : 0, lnl_out);
     return hipGetLastError();
 }
 

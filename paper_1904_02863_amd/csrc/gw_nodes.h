@@ -1,0 +1,219 @@
+// Frequency nodes of the split-form likelihood: the geometry shared by the
+// kernels that form them (gw_nodes.hip), the pass that sums over them
+// (gw_kernels.hip) and the host code that lays out the workspace.
+//
+// The only sum over bins that depends on the sample is
+//     Z_d = sum_k D_d,k e^{-2 pi i x_d(f_k)},
+// x_d the template's phase at detector d in turns.  Neighbouring bins of one
+// template are far from independent: its phase turns by its local time,
+// |dx_d/df|, a fraction of a second over most of the band, against bins
+// delta_f = 1/T apart.  So the phasor of a bin is interpolated from nodes q
+// bins apart (32 weights of gw_resample_weights.h, exact to 4e-16 while the
+// phase turns by at most GW_RESAMPLE_BAND per node), the weights are applied
+// to the data once for all samples,
+//     nu_d,n = sum_k w_n(k) D_d,k,        Z_d = sum_n nu_d,n e^{-2 pi i x_d(f_n)},
+// and the per-sample sum runs over the nodes: 1,652 instead of 259,585
+// frequencies for 4096 heavy binaries in 128 s, 17,900 instead of 1,040,897
+// for neutron stars from 15 Hz in 512 s.  The sums agree with the direct ones to FP64
+// rounding.
+//
+// Before the weights, D is multiplied by the phasor of a reference template
+// (the middle of the batch's range in every phase coefficient), so what has to
+// be resolved is only how the batch's templates differ from it.  R(f), a
+// bound on that difference's |dx/df| over every sample and detector that
+// falls with f (see node_rate), fixes the spacing: q bins from the first bin
+// K(q) on at which every frequency that a bin's 32 nodes reach keeps
+// R q delta_f <= GW_RESAMPLE_BAND.  Bins below every K(q) are summed one by one.
+#pragma once
+
+#include <cstdint>
+
+#include <hip/hip_runtime.h>
+
+#include "gw_internal.h"
+#include "gw_resample_weights.h"
+
+namespace gw {
+
+constexpr int kTaps = GW_RESAMPLE_TAPS;              // nodes a bin is interpolated from
+constexpr int kTapsBelow = GW_RESAMPLE_HALF - 1;     // of them below the bin's own cell
+// Node spacings, in bins, about a factor 1.4 apart; below 8 bins the 31
+// nodes a level needs beyond its ends and the weighting cost what it saves.
+constexpr int kNodeSpacings = 15;
+__host__ __device__ constexpr int node_spacing(int i)
+{
+    constexpr int q[kNodeSpacings] = {8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512, 768, 1024};
+    return q[i];
+}
+// A level covers at least this many cells (a cell: the q bins between two
+// nodes), so that its 31 extra nodes stay below what it saves.
+constexpr int kNodeMinCells = 64;
+constexpr int kSpreadBins = 512;                     // bins a block weights at a time
+// Phase coefficients whose range over the batch is taken: tau (its lowest and
+// highest over the detectors), c7, c6, c6l, c5l, c4, c3, c2, c0; one
+// (minimum, maximum) pair each.
+constexpr int kStatPairs = 9;
+constexpr int kStats = 2 * kStatPairs;
+constexpr int kStatEntries = 256;                    // entries the plan is made from directly
+constexpr int kMids = 10;                            // reference coefficients, in RecordField order
+
+// One level: bins [k0, k1) with nodes q bins apart.  Node n of the level, n =
+// 0 .. cells + 30, stands at bin k0 + (n - 15) q; cell c is interpolated from
+// nodes c .. c + 31.  Chunks of the weighting: cpc cells each, every cell cut into
+// `subs` parts of sub_bins bins.
+struct NodeLevel {
+    int64_t k0, k1;
+    int q, cells, cpc, subs, sub_bins, n_chunks;
+    int chunk0;       // first chunk, counted over the bins' chunks and all levels
+    int node0;        // first node, counted over all levels
+};
+
+struct NodePlan {
+    int64_t k_bin;                // bins [0, k_bin) are summed one by one
+    int n_levels, n_nodes;        // nodes of all levels
+    int bin_chunks, n_chunks;     // chunks of the weighting: of the bins, of everything
+    double mid[kMids];            // reference coefficients
+    NodeLevel level[kNodeSpacings];
+};
+
+__host__ __device__ inline int node_count(const NodeLevel &v) { return v.cells + kTaps - 1; }
+
+// Cells that share the 16 columns of one matrix instruction (two columns per
+// detector: real and imaginary part).
+__host__ __device__ constexpr int node_pack(int n_det)
+{
+    return n_det <= 1 ? 8 : n_det == 2 ? 4 : n_det <= 4 ? 2 : 1;
+}
+
+__host__ __device__ inline void node_chunks(int n_det, NodeLevel &v)
+{
+    const int pack = node_pack(n_det);
+    if (v.q * pack <= kSpreadBins) {
+        v.cpc = kSpreadBins / v.q;
+        v.subs = 1;
+        v.sub_bins = v.q;
+    } else {
+        v.cpc = pack;
+        v.subs = (v.q * pack + kSpreadBins - 1) / kSpreadBins;
+        v.sub_bins = (v.q + v.subs - 1) / v.subs;
+    }
+    v.n_chunks = (v.cells + v.cpc - 1) / v.cpc * v.subs;
+}
+
+// A chunk of the weighting leaves cpc + 31 partial node values; they, the
+// level's nodes and the nodes' tables stand in the level's own part of the D
+// array, which holds nothing else: per detector, from bin k0 on, the chunks'
+// partials, then the nodes, then (detector 0) two entries per node for Tab1.
+// node_room_ok states that this fits: true for every level of at least
+// kNodeMinCells cells.
+__host__ __device__ inline int64_t node_slots(const NodeLevel &v)
+{
+    return (int64_t)v.n_chunks * (v.cpc + kTaps - 1);
+}
+__host__ __device__ inline bool node_room_ok(const NodeLevel &v)
+{
+    return node_slots(v) + 3 * (int64_t)node_count(v) <= v.k1 - v.k0;
+}
+
+// Levels for first bins k_first[i] of spacing node_spacing(i) (n_bins where a
+// spacing cannot be used), from the widest down; what no level takes is left
+// to single bins.
+__host__ __device__ inline void node_levels(const int64_t *k_first, int64_t n_bins, int n_det, NodePlan &p)
+{
+    int64_t end = n_bins;
+    int used[kNodeSpacings], n = 0;
+    for (int i = kNodeSpacings - 1; i >= 0; --i) {
+        const int64_t k = k_first[i] > 0 ? k_first[i] : 0;
+        if (k < end && end - k >= (int64_t)kNodeMinCells * node_spacing(i)) {
+            used[n++] = i;
+            end = k;
+        }
+    }
+    p.k_bin = end;
+    p.n_levels = n;
+    p.bin_chunks = (int)((end + kSpreadBins - 1) / kSpreadBins);
+    int chunk = p.bin_chunks, node = 0;
+    for (int l = 0; l < n; ++l) {
+        const int i = used[n - 1 - l];
+        NodeLevel &v = p.level[l];
+        v.k0 = k_first[i] > 0 ? k_first[i] : 0;
+        v.k1 = l + 1 < n ? (k_first[used[n - 2 - l]] > 0 ? k_first[used[n - 2 - l]] : 0) : n_bins;
+        v.q = node_spacing(i);
+        v.cells = (int)((v.k1 - v.k0 + v.q - 1) / v.q);
+        node_chunks(n_det, v);
+        v.chunk0 = chunk;
+        v.node0 = node;
+        chunk += v.n_chunks;
+        node += node_count(v);
+    }
+    p.n_chunks = chunk;
+    p.n_nodes = node;
+}
+
+// Chunks of the weighting that any plan of n_bins bins can have: a chunk of a
+// level holds at least 3/8 of kSpreadBins bins but for the level's last cells.
+__host__ __device__ inline int64_t node_max_chunks(int64_t n_bins)
+{
+    return (n_bins + kSpreadBins * 3 / 8 - 1) / (kSpreadBins * 3 / 8) + 4 * kNodeSpacings + 1;
+}
+
+// The work split of the sum over `units` bins and nodes: the host's plan
+// (n_chunks chunks in `rounds` rounds), or fewer rounds while they would be
+// left with less than kUnitsRound units a chunk, and of one round fewer chunks
+// below kUnitsChunk.
+constexpr int kUnitsRound = 48, kUnitsChunk = 16;
+__host__ __device__ inline void node_split(int64_t units, int n_chunks, int rounds, int &eff_chunks, int &eff_rounds)
+{
+    const int64_t per = rounds > 0 ? n_chunks / rounds : n_chunks;
+    const int64_t r = rounds > 0 ? units / (per * kUnitsRound) : 0;
+    eff_rounds = rounds > 0 ? (int)(r < 1 ? 1 : r > rounds ? rounds : r) : 0;
+    eff_chunks = (int)per * (eff_rounds > 1 ? eff_rounds : 1);
+    const int64_t most = (units + kUnitsChunk - 1) / kUnitsChunk;
+    if (eff_rounds <= 1 && eff_chunks > most) eff_chunks = (int)(most < 1 ? 1 : most);
+}
+
+__host__ __device__ inline int node_chunks_of(int64_t units, int n_chunks, int rounds)
+{
+    int c, r;
+    node_split(units, n_chunks, rounds, c, r);
+    return units > 0 ? c : 0;
+}
+
+// One event as the node kernels see it.
+struct NodeEvent {
+    int64_t n_bins;
+    int n_det;
+    double f_low, df;
+    const double2 *data;
+    const double *psd;
+    const Tab1 *tab1;
+    const Tab2 *tab2;
+    double2 *dcoef;       // [n_det][n_bins]: D of the single bins, and every level's partials and nodes
+    double *prep;         // [n_chunks][kPrepPerDet n_det] sums of each chunk of the weighting
+    double *sums;
+    double *stats;        // [n_stats][kStats]
+    int n_stats;
+    NodePlan *plan;
+};
+
+// A call takes the nodes (how many, the batch decides) when its direct sum has
+// at least this many (bin, group of 256 samples) pairs: the nodes' kernels take
+// about 15 us more than the event preparation they replace, a small direct sum
+// less than that.  Measured, 3 detectors: 8,192 bins x 8 groups 46.0 us direct, 49.3 us on
+// nodes; 16,384 x 8 71.7 us and 50.2 us.
+constexpr int64_t kNodeMinBins = 8192, kNodeMinWork = 98304;
+
+// Stats entries the sample kernel writes: one per wave of 64 samples.
+inline int64_t node_stat_entries(int64_t n_samples) { return (n_samples + 63) / 64; }
+
+// ---- launchers (gw_nodes.hip, gw_kernels.hip) ----
+// Sample records and the range of their phase coefficients, one entry of
+// `stats` per 64 samples (reduced to kStatEntries when there are more).
+hipError_t launch_node_samples(const gw_grid &grid, int n_det, const SamplePrep &sp, double *stats,
+                               hipStream_t stream);
+// Plan, D, event sums' partials, and every level's weighted partial nodes.
+hipError_t launch_node_spread(const NodeEvent &ev, bool norm, int n_cu, hipStream_t stream);
+// Nodes from their partials, the nodes' tables, the event sums; zeroes the queue.
+hipError_t launch_node_combine(const NodeEvent &ev, unsigned *queue, hipStream_t stream);
+
+}  // namespace gw

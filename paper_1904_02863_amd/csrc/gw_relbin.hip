@@ -303,18 +303,7 @@ __global__ __launch_bounds__(kBlock) void lnl_kernel(int64_t n_samples, int64_t 
         __syncthreads();
     }
 
-    PhaseCoef c = load_coef(rec, n_samples, sr);
-    const PhaseCoef c0 = load_coef(fid, 1, 0);
-    c.c8 -= c0.c8;
-    c.c7 -= c0.c7;
-    c.c6 -= c0.c6;
-    c.c6l -= c0.c6l;
-    c.c5 -= c0.c5;
-    c.c5l -= c0.c5l;
-    c.c4 -= c0.c4;
-    c.c3 -= c0.c3;
-    c.c2 -= c0.c2;
-    c.c0 -= c0.c0;
+    PhaseCoef c = coef_less(load_coef(rec, n_samples, sr), load_coef(fid, 1, 0));
     // FP64: phase in units of 1/N turn for the table phasor (exact: N is a power of two)
     const double scale = MIXED ? 1.0 : (double)GW_PHTAB_N;
     if constexpr (!MIXED) c = scale_coef(c, scale);

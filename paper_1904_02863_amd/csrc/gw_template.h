@@ -69,6 +69,22 @@ __device__ __forceinline__ PhaseCoef load_coef(const double *__restrict__ rec, i
     return c;
 }
 
+// Coefficients a - b: the phase of one template less that of another.
+__device__ __forceinline__ PhaseCoef coef_less(PhaseCoef a, const PhaseCoef &b)
+{
+    a.c8 -= b.c8;
+    a.c7 -= b.c7;
+    a.c6 -= b.c6;
+    a.c6l -= b.c6l;
+    a.c5 -= b.c5;
+    a.c5l -= b.c5l;
+    a.c4 -= b.c4;
+    a.c3 -= b.c3;
+    a.c2 -= b.c2;
+    a.c0 -= b.c0;
+    return a;
+}
+
 // Every coefficient times k; with k a power of two the phase comes out scaled
 // by k exactly.
 __device__ __forceinline__ PhaseCoef scale_coef(PhaseCoef c, double k)
