@@ -11,7 +11,10 @@ b_i = sinc(2 NU (i - x)).  G is ill-conditioned (that is what makes the error
 small), so they are solved with 70 digits and a ridge of 1e-33, which keeps
 the weights' sum of magnitudes near 2.  Each weight is a smooth function of x
 and is written as a polynomial in s = 2 x - 1, interpolated at Chebyshev
-points, so that the kernels can form the weights of any bin spacing.
+points, so that the kernels can form the weights of any bin spacing.  The
+weights are mirror images, w_t(s) = w_{TAPS - 1 - t}(-s), so the header holds
+those of the lower half, and one evaluation of their even and odd parts gives
+a pair: w_t = E + s O, w_{TAPS - 1 - t} = E - s O with polynomials E, O in s^2.
 
     python gen_resample.py            # writes the header
     python gen_resample.py --check    # prints the error of the double evaluation
@@ -64,13 +67,17 @@ def polynomials():
 
 
 def evaluate(coef, x):
-    """Weights [len(x)][TAPS] in double by Horner's rule, as the kernels do."""
-    c = np.asarray(coef)
+    """Weights [len(x)][TAPS] in double from the lower half's coefficients, as
+    the kernels form them."""
+    c = np.asarray(coef)[:P]
     s = 2.0 * np.asarray(x, dtype=np.float64)[:, None] - 1.0
-    acc = np.broadcast_to(c[:, -1], (s.shape[0], TAPS)).copy()
-    for j in range(DEGREE - 1, -1, -1):
-        acc = acc * s + c[:, j]
-    return acc
+    z = s * s
+    even = np.broadcast_to(c[:, DEGREE - 1], (s.shape[0], P)).copy()
+    odd = np.broadcast_to(c[:, DEGREE], (s.shape[0], P)).copy()
+    for j in range(DEGREE - 3, -1, -2):
+        even = even * z + c[:, j]
+        odd = odd * z + c[:, j + 1]
+    return np.hstack([even + s * odd, (even - s * odd)[:, ::-1]])
 
 
 def band_error(coef, nu_max=float(NU), n_x=97, n_nu=120):
@@ -94,8 +101,8 @@ def header(coef) -> str:
     e, _ = band_error(coef)
     rows = []
     for j in range(DEGREE + 1):
-        vals = [repr(coef[t][j]) for t in range(TAPS)]
-        lines = [", ".join(vals[i:i + 4]) for i in range(0, TAPS, 4)]
+        vals = [repr(coef[t][j]) for t in range(P)]
+        lines = [", ".join(vals[i:i + 4]) for i in range(0, P, 4)]
         rows.append("    {" + ", \\\n     ".join(lines) + "}")
     return ("// Written by gen_resample.py.  Weights of the frequency resampling: weight t (node\n"
             f"// offset t - {P - 1}) of a point a fraction x of a node spacing past node 0 is the\n"

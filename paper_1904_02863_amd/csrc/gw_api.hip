@@ -268,7 +268,7 @@ struct LnlLayout {
 };
 
 LnlLayout lnl_layout_as(int64_t n_bins, int n_det, int64_t n_samples, const gw::TilePlan &plan, unsigned flags,
-                        bool nodes)
+                        int n_cu, bool nodes)
 {
     LnlLayout l;
     Carver c;
@@ -283,8 +283,7 @@ LnlLayout lnl_layout_as(int64_t n_bins, int n_det, int64_t n_samples, const gw::
     l.qprefix = isco ? c.take(sizeof(double) * n_bins * n_det) : 0;
     l.qoffsets = isco ? c.take(sizeof(double) * (size_t)l.prep_blocks * n_det) : 0;
     l.prep_partials = c.take(sizeof(double) * gw::kPrepPerDet * n_det *
-                             (nodes ? std::max<int64_t>(gw::node_max_chunks(n_bins), l.prep_blocks)
-                                    : (int64_t)l.prep_blocks));
+                             (nodes ? std::max(gw::node_spread_blocks(n_bins, n_cu), l.prep_blocks) : l.prep_blocks));
     l.event_sums = c.take(sizeof(double) * gw::kEventSums);
     l.k_limit = c.take(sizeof(int64_t));
     l.records = c.take(sizeof(double) * gw::record_fields(n_det) * std::max<int64_t>(n_samples, 1));
@@ -302,13 +301,13 @@ LnlLayout lnl_layout_as(int64_t n_bins, int n_det, int64_t n_samples, const gw::
 // push a call out of the static array that fits it without them, and
 // gw_lnl_batch and gw_lnl_batch_static run the same kernels on the same call,
 // so the rule is the same for both.
-LnlLayout lnl_layout(int64_t n_bins, int n_det, int64_t n_samples, const gw::TilePlan &plan, unsigned flags)
+LnlLayout lnl_layout(int64_t n_bins, int n_det, int64_t n_samples, const gw::TilePlan &plan, unsigned flags, int n_cu)
 {
-    const LnlLayout plain = lnl_layout_as(n_bins, n_det, n_samples, plan, flags, false);
+    const LnlLayout plain = lnl_layout_as(n_bins, n_det, n_samples, plan, flags, n_cu, false);
     if (gw::tile_form(flags) != gw::kFormSplit || n_bins < gw::kNodeMinBins || n_bins > 0x7fffffffLL ||
         (double)n_bins * (double)plan.n_groups < (double)gw::kNodeMinWork)
         return plain;
-    const LnlLayout nodes = lnl_layout_as(n_bins, n_det, n_samples, plan, flags, true);
+    const LnlLayout nodes = lnl_layout_as(n_bins, n_det, n_samples, plan, flags, n_cu, true);
     const bool leaves_array = plain.total <= kStaticScratchBytes && nodes.total > kStaticScratchBytes;
     return leaves_array ? plain : nodes;
 }
@@ -411,13 +410,14 @@ int lnl_enqueue(gw_workspace *ws, char *base, const LnlLayout &l, const gw::Tile
         ne.tab2 = eb.tab2;
         ne.dcoef = eb.dcoef;
         ne.prep = eb.prep;
+        ne.spread_blocks = gw::node_spread_blocks(grid.n_bins, n_cu);
         ne.sums = eb.sums;
         ne.stats = entries > gw::kStatEntries ? stats + entries * gw::kStats : stats;
         ne.n_stats = entries > gw::kStatEntries ? 1 : (int)entries;
         ne.plan = eb.node_plan;
         if ((e = gw::launch_node_samples(grid, n_det, sp, stats, stream)) != hipSuccess)
             return hip_fail(e, "sample prep");
-        if ((e = gw::launch_node_spread(ne, (flags & GW_FLAG_ADD_NORM) != 0, n_cu, stream)) != hipSuccess)
+        if ((e = gw::launch_node_spread(ne, (flags & GW_FLAG_ADD_NORM) != 0, stream)) != hipSuccess)
             return hip_fail(e, "weighting the data onto the nodes");
         if ((e = gw::launch_node_combine(ne, eb.queue, stream)) != hipSuccess) return hip_fail(e, "nodes");
     } else if ((e = gw::launch_event_data(grid, n_det, data, psd, eb, flags, &sp, stream)) != hipSuccess) {
@@ -489,7 +489,7 @@ int tune_single_event(gw_workspace *ws, const gw_grid &grid, int n_det, const gw
     const int form = gw::tile_form(flags);
     const std::vector<gw::TilePlan> plans = tuning_candidates(ws, grid.n_bins, n_det, n_samples, mixed, form);
     size_t need = 0;
-    for (const gw::TilePlan &p : plans) need = std::max(need, lnl_layout(grid.n_bins, n_det, n_samples, p, flags).total);
+    for (const gw::TilePlan &p : plans) need = std::max(need, lnl_layout(grid.n_bins, n_det, n_samples, p, flags, ws->n_cu).total);
     if (int rc = ensure_capacity(ws, need, stream)) return rc;
     const bool timing = ws->timing;
     ws->timing = false;                  // the trial calls are not measurements of the caller's
@@ -505,7 +505,7 @@ int tune_single_event(gw_workspace *ws, const gw_grid &grid, int n_det, const gw
     for (int pass = -1; pass < 2 && rc == GW_OK; ++pass) {
         for (size_t i = 0; i < plans.size() && rc == GW_OK; ++i) {
             if (pass < 0 && i > 0) break;    // one warm-up call lets the clock settle
-            const LnlLayout l = lnl_layout(grid.n_bins, n_det, n_samples, plans[i], flags);
+            const LnlLayout l = lnl_layout(grid.n_bins, n_det, n_samples, plans[i], flags, ws->n_cu);
             if ((e = hipEventRecord(ev[0], stream)) != hipSuccess) { rc = hip_fail(e, "hipEventRecord"); break; }
             if ((rc = lnl_enqueue(ws, static_cast<char *>(ws->base), l, plans[i], grid, n_det, geom, data, psd, theta,
                                   n_param, n_samples, lnl_out, mixed, flags, ws->n_cu, stream)) != GW_OK)
@@ -549,7 +549,7 @@ int lnl_one_event(gw_workspace *ws, const gw_grid &grid, int n_det, const gw::De
             return rc;
     }
     const gw::TilePlan plan = plan_tiles(ws, grid.n_bins, n_det, n_samples, mixed, form);
-    const LnlLayout l = lnl_layout(grid.n_bins, n_det, n_samples, plan, flags);
+    const LnlLayout l = lnl_layout(grid.n_bins, n_det, n_samples, plan, flags, ws->n_cu);
     if (int rc = ensure_capacity(ws, l.total, stream)) return rc;
     return lnl_enqueue(ws, static_cast<char *>(ws->base), l, plan, grid, n_det, geom, data, psd, theta, n_param,
                        n_samples, lnl_out, mixed, flags, ws->n_cu, stream);
@@ -1061,8 +1061,8 @@ int gw_workspace_reserve(gw_workspace *ws, int64_t n_bins, int n_det, int64_t n_
             std::vector<gw::TilePlan> plans = tuning_candidates(ws, n_bins, n_det, n_samples, mixed != 0, form);
             plans.push_back(plan_tiles(ws, n_bins, n_det, n_samples, mixed != 0, form));
             for (const gw::TilePlan &p : plans) {
-                need = std::max(need, lnl_layout_as(n_bins, n_det, n_samples, p, all_flags, false).total);
-                need = std::max(need, lnl_layout_as(n_bins, n_det, n_samples, p, 0u, true).total);
+                need = std::max(need, lnl_layout_as(n_bins, n_det, n_samples, p, all_flags, ws->n_cu, false).total);
+                need = std::max(need, lnl_layout_as(n_bins, n_det, n_samples, p, 0u, ws->n_cu, true).total);
             }
         }
     size_t wave = align_up(sizeof(gw::Tab1) * n_bins) + align_up(sizeof(gw::Tab2) * n_bins) +
@@ -1114,7 +1114,7 @@ int64_t gw_lnl_batch_static_bytes(const gw_grid *grid, int n_det, int64_t n_samp
     if (int rc = static_device(device, &d)) return rc;
     const gw::TilePlan plan = plan_tiles_on(d->n_cu, d->occupancy, grid->n_bins, n_det, n_samples,
                                             precision == GW_PREC_MIXED, gw::tile_form(flags));
-    return (int64_t)lnl_layout(grid->n_bins, n_det, n_samples, plan, flags).total;
+    return (int64_t)lnl_layout(grid->n_bins, n_det, n_samples, plan, flags, d->n_cu).total;
 }
 
 int gw_lnl_batch_static(const gw_grid *grid, int n_det, const gw_detector *dets, const gw_c128 *data,
@@ -1142,7 +1142,7 @@ int gw_lnl_batch_static(const gw_grid *grid, int n_det, const gw_detector *dets,
     if (int rc = static_device(device, &d)) return rc;
     const gw::TilePlan plan = plan_tiles_on(d->n_cu, d->occupancy, grid->n_bins, n_det, n_samples, mixed,
                                             gw::tile_form(flags));
-    const LnlLayout l = lnl_layout(grid->n_bins, n_det, n_samples, plan, flags);
+    const LnlLayout l = lnl_layout(grid->n_bins, n_det, n_samples, plan, flags, d->n_cu);
     if (l.total > kStaticScratchBytes)
         return fail(GW_EINVAL, "gw_lnl_batch_static: this call needs " + std::to_string(l.total) +
                                    " bytes of scratch, more than the library's static " +

@@ -45,9 +45,10 @@ __host__ __device__ constexpr int node_spacing(int i)
     constexpr int q[kNodeSpacings] = {8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512, 768, 1024};
     return q[i];
 }
-// A level covers at least this many cells (a cell: the q bins between two
-// nodes), so that its 31 extra nodes stay below what it saves.
-constexpr int kNodeMinCells = 64;
+// A level covers at least kNodeMinCells cells (a cell: the q bins between two
+// nodes), so that its 31 extra nodes stay below what it saves over the next
+// smaller spacing; the lowest level, which saves single bins, kNodeLowCells.
+constexpr int kNodeMinCells = 64, kNodeLowCells = 40;
 constexpr int kSpreadBins = 512;                     // bins a block weights at a time
 // Phase coefficients whose range over the batch is taken: tau (its lowest and
 // highest over the detectors), c7, c6, c6l, c5l, c4, c3, c2, c0; one
@@ -105,7 +106,7 @@ __host__ __device__ inline void node_chunks(int n_det, NodeLevel &v)
 // array, which holds nothing else: per detector, from bin k0 on, the chunks'
 // partials, then the nodes, then (detector 0) two entries per node for Tab1.
 // node_room_ok states that this fits: true for every level of at least
-// kNodeMinCells cells.
+// kNodeLowCells cells.
 __host__ __device__ inline int64_t node_slots(const NodeLevel &v)
 {
     return (int64_t)v.n_chunks * (v.cpc + kTaps - 1);
@@ -117,34 +118,54 @@ __host__ __device__ inline bool node_room_ok(const NodeLevel &v)
 
 // Levels for first bins k_first[i] of spacing node_spacing(i) (n_bins where a
 // spacing cannot be used), from the widest down; what no level takes is left
-// to single bins.
-__host__ __device__ inline void node_levels(const int64_t *k_first, int64_t n_bins, int n_det, NodePlan &p)
+// to single bins.  node_pick returns how many levels there are and where the
+// single bins end, and fills v with level number `want` counted from the widest
+// (so that the kernels can have one thread per level).
+__host__ __device__ inline int node_pick(const int *k_first, int n_bins, int n_det, int want, NodeLevel &v, int &k_bin)
 {
-    int64_t end = n_bins;
-    int used[kNodeSpacings], n = 0;
-    for (int i = kNodeSpacings - 1; i >= 0; --i) {
-        const int64_t k = k_first[i] > 0 ? k_first[i] : 0;
-        if (k < end && end - k >= (int64_t)kNodeMinCells * node_spacing(i)) {
-            used[n++] = i;
-            end = k;
+    int end = n_bins, n = 0, last = kNodeSpacings;
+    v.q = 0;
+#pragma unroll
+    for (int pass = 0; pass < 2; ++pass) {
+        if (end == 0) break;
+#pragma unroll
+        for (int i = kNodeSpacings - 1; i >= 0; --i) {
+            const int k = k_first[i], q = node_spacing(i);
+            if (i < last && k < end && end - k >= (pass == 0 ? kNodeMinCells : kNodeLowCells) * q) {
+                if (n == want) {
+                    v.k0 = k;
+                    v.k1 = end;
+                    v.q = q;
+                }
+                ++n;
+                end = k;
+                last = i;
+            }
         }
     }
-    p.k_bin = end;
-    p.n_levels = n;
-    p.bin_chunks = (int)((end + kSpreadBins - 1) / kSpreadBins);
-    int chunk = p.bin_chunks, node = 0;
-    for (int l = 0; l < n; ++l) {
-        const int i = used[n - 1 - l];
-        NodeLevel &v = p.level[l];
-        v.k0 = k_first[i] > 0 ? k_first[i] : 0;
-        v.k1 = l + 1 < n ? (k_first[used[n - 2 - l]] > 0 ? k_first[used[n - 2 - l]] : 0) : n_bins;
-        v.q = node_spacing(i);
-        v.cells = (int)((v.k1 - v.k0 + v.q - 1) / v.q);
+    k_bin = end;
+    if (v.q > 0) {
+        v.cells = (int)(((unsigned)(v.k1 - v.k0) + (unsigned)v.q - 1u) / (unsigned)v.q);
         node_chunks(n_det, v);
-        v.chunk0 = chunk;
-        v.node0 = node;
-        chunk += v.n_chunks;
-        node += node_count(v);
+    }
+    return n;
+}
+
+inline void node_levels(const int *k_first, int n_bins, int n_det, NodePlan &p)
+{
+    NodeLevel v;
+    int k_bin = 0;
+    p.n_levels = node_pick(k_first, n_bins, n_det, 0, v, k_bin);
+    p.k_bin = k_bin;
+    p.bin_chunks = (k_bin + kSpreadBins - 1) / kSpreadBins;
+    int chunk = p.bin_chunks, node = 0;
+    for (int l = 0; l < p.n_levels; ++l) {
+        NodeLevel &w = p.level[l];
+        node_pick(k_first, n_bins, n_det, p.n_levels - 1 - l, w, k_bin);
+        w.chunk0 = chunk;
+        w.node0 = node;
+        chunk += w.n_chunks;
+        node += node_count(w);
     }
     p.n_chunks = chunk;
     p.n_nodes = node;
@@ -155,6 +176,14 @@ __host__ __device__ inline void node_levels(const int64_t *k_first, int64_t n_bi
 __host__ __device__ inline int64_t node_max_chunks(int64_t n_bins)
 {
     return (n_bins + kSpreadBins * 3 / 8 - 1) / (kSpreadBins * 3 / 8) + 4 * kNodeSpacings + 1;
+}
+
+// Blocks of the weighting: one per chunk, up to three per CU (what fits at
+// once); more chunks take turns.
+inline int node_spread_blocks(int64_t n_bins, int n_cu)
+{
+    const int64_t c = node_max_chunks(n_bins), most = 3 * (int64_t)n_cu;
+    return (int)(c < most ? c : most);
 }
 
 // The work split of the sum over `units` bins and nodes: the host's plan
@@ -189,7 +218,8 @@ struct NodeEvent {
     const Tab1 *tab1;
     const Tab2 *tab2;
     double2 *dcoef;       // [n_det][n_bins]: D of the single bins, and every level's partials and nodes
-    double *prep;         // [n_chunks][kPrepPerDet n_det] sums of each chunk of the weighting
+    double *prep;         // [spread_blocks][kPrepPerDet n_det] sums over each block's chunks
+    int spread_blocks;    // blocks of the weighting
     double *sums;
     double *stats;        // [n_stats][kStats]
     int n_stats;
@@ -203,7 +233,7 @@ struct NodeEvent {
 // nodes; 16,384 x 8 71.7 us and 50.2 us.
 constexpr int64_t kNodeMinBins = 8192, kNodeMinWork = 98304;
 
-// Stats entries the sample kernel writes: one per wave of 64 samples.
+// Stats entries the sample kernel writes: one per block of 64 samples.
 inline int64_t node_stat_entries(int64_t n_samples) { return (n_samples + 63) / 64; }
 
 // ---- launchers (gw_nodes.hip, gw_kernels.hip) ----
@@ -212,7 +242,7 @@ inline int64_t node_stat_entries(int64_t n_samples) { return (n_samples + 63) / 
 hipError_t launch_node_samples(const gw_grid &grid, int n_det, const SamplePrep &sp, double *stats,
                                hipStream_t stream);
 // Plan, D, event sums' partials, and every level's weighted partial nodes.
-hipError_t launch_node_spread(const NodeEvent &ev, bool norm, int n_cu, hipStream_t stream);
+hipError_t launch_node_spread(const NodeEvent &ev, bool norm, hipStream_t stream);
 // Nodes from their partials, the nodes' tables, the event sums; zeroes the queue.
 hipError_t launch_node_combine(const NodeEvent &ev, unsigned *queue, hipStream_t stream);
 

@@ -2,8 +2,8 @@
 // batch, the weighting of the data onto the nodes, and the nodes' tables.
 //
 // Measured on MI355X, a whole gw_lnl_batch call (every bin summed per sample ->
-// nodes): 4096 heavy binaries, 3 detectors, 259,585 bins: 1.60 ms -> 76 us;
-// 4096 neutron-star rows, 1,040,897 bins from 15 Hz: 6.27 ms -> 0.25 ms.
+// nodes): 4096 heavy binaries, 3 detectors, 259,585 bins: 1.60 ms -> 60 us;
+// 4096 neutron-star rows, 1,040,897 bins from 15 Hz: 6.30 ms -> 0.20 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -20,8 +20,10 @@ namespace gw {
 
 typedef double double4_t __attribute__((ext_vector_type(4)));
 
-// Weight t of a point at s = 2 x - 1 in its cell: sum_j coef[j][t] s^j.
-static __constant__ double resample_coef[GW_RESAMPLE_DEGREE + 1][kTaps] = {GW_RESAMPLE_COEF_VALUES};
+// Weight t < 16 of a point at s = 2 x - 1 in its cell: sum_j coef[j][t] s^j;
+// weight 31 - t is weight t at -s.
+static __constant__ double resample_coef[GW_RESAMPLE_DEGREE + 1][kTaps / 2] = {GW_RESAMPLE_COEF_VALUES};
+static_assert(GW_RESAMPLE_DEGREE % 2 == 1, "even and odd parts of equal length");
 
 // ---------------------------------------------------------------- the plan
 // Half the batch's range of every phase coefficient about the reference, as
@@ -55,15 +57,22 @@ __device__ __forceinline__ double node_rate(const RateBound &r, double u)
 // reference is more than 1.5 times the coefficient itself, and one far-off row of
 // a batch cannot cost the others their digits.
 constexpr int kPlanSlices = kBlock / kStats;                       // 14 slices of the entries
-constexpr int kPlanScratch = kPlanSlices * kStats + 2 * kStatPairs + kNodeSpacings;
+constexpr int kPlanScratch = kPlanSlices * kStats + 2 * kStatPairs + 3 * kNodeSpacings;   // 5 kNodeSpacings ints at the end
 
 __device__ __forceinline__ void make_node_plan(double f_low, double df, int64_t n_bins, int n_det,
                                                const double *__restrict__ stats, int n_stats, NodePlan &p,
                                                double *red)
 {
     double *const half = red + kPlanSlices * kStats, *const mid = half + kStatPairs;
-    double *const first = mid + kStatPairs;
+    int *const first = reinterpret_cast<int *>(mid + kStatPairs);
     const int t = threadIdx.x;
+    // frequencies first: they do not wait for the ranges.  Nodes stand up to 16
+    // cells past the band's ends
+    const double f_high = f_low + (double)(n_bins - 1) * df;
+    const double f_past = f_high + 2.0 * kTaps * node_spacing(kNodeSpacings - 1) * df;
+    const double u_low = cbrt(0.5 * f_low), u_high = cbrt(f_high);
+    const double du = (u_high - u_low) * (1.0 / (kBlock - 1));
+    const double l_most = fmax(fabs(log(0.5 * f_low)), fabs(log(f_past))) * (1.0 / 3.0) + 1.0;
     if (t < kPlanSlices * kStats) {
         const int j = t % kStats;
         double m = j % 2 == 0 ? INFINITY : -INFINITY;
@@ -99,50 +108,69 @@ __device__ __forceinline__ void make_node_plan(double f_low, double df, int64_t 
     r.c3 = half[6];
     r.c2 = half[7];
     r.c0 = half[8];
-    // |d/du of (c6 + c6l L) u| = |c6 + c6l (L + 1)|; nodes stand up to 16 cells past the band's ends
-    const double f_high = f_low + (double)(n_bins - 1) * df;
-    const double u_high = cbrt(f_high);
-    const double f_past = f_high + 2.0 * kTaps * node_spacing(kNodeSpacings - 1) * df;
-    r.c6 = half[2] + half[3] * (fmax(fabs(log(0.5 * f_low)), fabs(log(f_past))) * (1.0 / 3.0) + 1.0);
-    // first bin of every spacing: 16 threads each search the lowest frequency
-    // from which on the rate bound holds, 17-ary on u (the bound falls with u)
-    const int g = t / 16, lane = t % 16;
-    if (g < kNodeSpacings) {
-        const int q = node_spacing(g);
-        const double step = (double)q * df;
-        const double f_min = fmax(f_low - 16.0 * step, 0.5 * f_low);
-        double lo = cbrt(f_min), hi = u_high;
-        const bool never = !(node_rate(r, hi) * step <= GW_RESAMPLE_BAND);
-        if (node_rate(r, lo) * step <= GW_RESAMPLE_BAND) hi = lo;
-        for (int it = 0; it < 7; ++it) {
-            const double w = (hi - lo) * (1.0 / 17.0);
-            const bool ok = node_rate(r, lo + w * (double)(lane + 1)) * step <= GW_RESAMPLE_BAND;
-            const unsigned bits = (unsigned)(__ballot(!ok) >> (16 * (g % 4))) & 0xffffu;
-            const int n_bad = __popc(bits);          // the bound falls with u: the low points fail first
-            const double base = lo;
-            lo = base + w * (double)n_bad;
-            hi = n_bad == 16 ? hi : base + w * (double)(n_bad + 1);
-        }
-        if (lane == 0) {
-            const double k = ceil((hi * hi * hi + 16.0 * step - f_low) / df);
-            first[g] = never || !(k < (double)n_bins) ? (double)n_bins : fmax(k, 0.0);
-        }
+    r.c6 = half[2] + half[3] * l_most;               // |d/du of (c6 + c6l L) u| = |c6 + c6l (L + 1)|
+    // first bin of every spacing: the bound at kBlock frequencies from half of
+    // f_low up, even in u (about 1% apart in f); thread t finds the widest
+    // spacing its frequency allows, and since the bound falls with f, the first
+    // frequency that allows spacing g is the number of threads that do not
+    const double rate = node_rate(r, t == kBlock - 1 ? u_high : u_low + du * (double)t);
+    int widest = 0;                  // spacings allowed
+#pragma unroll
+    for (int g = 0; g < kNodeSpacings; ++g) widest += rate * ((double)node_spacing(g) * df) <= GW_RESAMPLE_BAND;
+    int *const failing = first + kNodeSpacings;
+#pragma unroll
+    for (int g = 0; g < kNodeSpacings; ++g) {
+        const int n = __popcll(__ballot(widest <= g));
+        if (t % 64 == g) failing[(t / 64) * kNodeSpacings + g] = n;
     }
     __syncthreads();
-    if (t == 0) {
-        int64_t k_first[kNodeSpacings];
-        for (int i = 0; i < kNodeSpacings; ++i) k_first[i] = (int64_t)first[i];
-        node_levels(k_first, n_bins, n_det, p);
-        p.mid[kRecC8] = mid[0];
-        p.mid[kRecC7] = mid[1];
-        p.mid[kRecC6] = mid[2];
-        p.mid[kRecC6L] = mid[3];
-        p.mid[kRecC5] = 0.0;
-        p.mid[kRecC5L] = mid[4];
-        p.mid[kRecC4] = mid[5];
-        p.mid[kRecC3] = mid[6];
-        p.mid[kRecC2] = mid[7];
-        p.mid[kRecC0] = mid[8];
+    if (t < kNodeSpacings) {
+        const int n = failing[t] + failing[kNodeSpacings + t] + failing[2 * kNodeSpacings + t] +
+                      failing[3 * kNodeSpacings + t];
+        const double reach = (double)((kTapsBelow + 1) * node_spacing(t)) * df;   // a bin's nodes reach this far down
+        const double u = n == kBlock - 1 ? u_high : u_low + du * (double)n;
+        const double k = ceil((fmax(u * u * u, f_low - reach) + reach - f_low) / df);
+        first[t] = n == kBlock || !(k < (double)n_bins) ? (int)n_bins : (int)fmax(k, 0.0);
+    }
+    __syncthreads();
+    if (t < 64) {
+        int k_first[kNodeSpacings];
+#pragma unroll
+        for (int i = 0; i < kNodeSpacings; ++i) k_first[i] = first[i];
+        NodeLevel v{};
+        int k_bin = 0;
+        // lane t holds level t from the widest spacing, i.e. from the top of the band
+        const int n = node_pick(k_first, (int)n_bins, n_det, t, v, k_bin);
+        int chunks = t < n ? v.n_chunks : 0, nodes = t < n ? node_count(v) : 0;
+        const int own_chunks = chunks, own_nodes = nodes;
+#pragma unroll
+        for (int off = 1; off < 16; off <<= 1) {             // inclusive sums over the levels below
+            const int c = __shfl_down(chunks, off, 64), m = __shfl_down(nodes, off, 64);
+            chunks += c;
+            nodes += m;
+        }
+        const int bin_chunks = (k_bin + kSpreadBins - 1) / kSpreadBins;
+        if (t < n) {
+            v.chunk0 = bin_chunks + chunks - own_chunks;
+            v.node0 = nodes - own_nodes;
+            p.level[n - 1 - t] = v;
+        }
+        if (t == 0) {
+            p.k_bin = k_bin;
+            p.n_levels = n;
+            p.n_nodes = nodes;
+            p.bin_chunks = bin_chunks;
+            p.n_chunks = bin_chunks + chunks;
+        }
+        if (t < kMids) {
+            // kRecC8 .. kRecC0 from the pairs' order; the constant kRecC5 needs no reference
+            constexpr int pair[kMids] = {0, 1, 2, 3, -1, 4, 5, 6, 7, 8};
+            int at = -1;
+#pragma unroll
+            for (int i = 0; i < kMids; ++i)
+                if (i == t) at = pair[i];
+            p.mid[t] = at >= 0 ? mid[at] : 0.0;
+        }
     }
     __syncthreads();
 }
@@ -162,14 +190,18 @@ __device__ __forceinline__ PhaseCoef reference_coef(const NodePlan &p) { return 
 // v_mfma_f64_16x16x4 does the product: a wave holds 16 columns (node_pack
 // cells) of both halves of the taps; with few cells the waves share out the q
 // bins instead, and the parts are added with the cells' Y.
-// What bounds it: one division, one reference phasor and 64 n_det
-// multiply-adds per bin, against 72 + 48 bytes read.
+// What bounds it: per bin one division per detector, one reference phasor and 64
+// n_det multiply-adds (a third more in the matrix instructions' unused columns),
+// against 48 + 24 n_det bytes read.  3 detectors, 259,585 bins: 26 us, of which a block
+// spends 5 on the plan, 5 waiting for its bins and 5 in the product; 40 us with the
+// levels worked out by one thread, two blocks a CU (two turns of chunks) and the sums
+// of every chunk reduced through LDS permutes.
 template <int NDET>
 struct SpreadShape {
     static constexpr int kComp = 2 * NDET;
     static constexpr int kPack = node_pack(NDET);
     static constexpr int kStride = kSpreadBins + 4;          // LDS row of one component, in doubles
-    static constexpr int kPacks = 8;                         // packs of cells per batch
+    static constexpr int kPacks = 4;                         // packs of cells per batch
     static constexpr int kMaxNodes = kSpreadBins / 8 + kTaps - 1;
     static constexpr int kAcc = (kMaxNodes * kComp + kBlock - 1) / kBlock;
     static constexpr size_t kLds = sizeof(double) * ((size_t)kComp * kStride + (size_t)kPacks * kTaps * 16);
@@ -177,7 +209,7 @@ struct SpreadShape {
 
 template <int NDET>
 __device__ __forceinline__ void spread_chunk(const NodeEvent &ev, const NodePlan &plan, int chunk, bool norm,
-                                             double *lds_d, double *lds_y, double *red)
+                                             double *lds_d, double *lds_y, double (&acc)[kPrepPerDet * NDET])
 {
     using S = SpreadShape<NDET>;
     constexpr int kComp = S::kComp, kPack = S::kPack, kStride = S::kStride;
@@ -199,35 +231,38 @@ __device__ __forceinline__ void spread_chunk(const NodeEvent &ev, const NodePlan
     const int64_t k_end = single ? plan.k_bin : v.k1;
     const PhaseCoef ref = reference_coef(plan);
 
-    double acc[kPrepPerDet * NDET];
-#pragma unroll
-    for (int i = 0; i < kPrepPerDet * NDET; ++i) acc[i] = 0.0;
+    // every load of a bin is issued before the first use (one bin at a time:
+    // both of a thread's bins would spill at three blocks a CU)
+#pragma unroll 1
     for (int b = t; b < kSpreadBins; b += kBlock) {
-        const int cell = b / sub_bins, j = b - cell * sub_bins;
-        const int64_t k = single ? k_base + b : k_base + (int64_t)cell * v.q + j;
+        const int cell = single ? 0 : (int)((unsigned)b / (unsigned)sub_bins), j = b - cell * sub_bins;
+        const int64_t k = k_base + (single ? 0 : (int64_t)cell * v.q) + j;
         const bool live = b < n_here && k < k_end && (single || j0 + j < v.q);
-        double er = 0.0, ei = 0.0, amp = 0.0;
-        if (live) {
-            gw_phasor_turns(turns_phase(ref, ev.tab1[k]), er, ei);
-            amp = ev.tab2[k].amp;
-        }
+        const int64_t at = live ? k : 0;
+        const Tab1 t1 = ev.tab1[at];
+        const double amp = ev.tab2[at].amp;
+        double psd[NDET];
+        double2 x[NDET];
 #pragma unroll
         for (int d = 0; d < NDET; ++d) {
-            double dr = 0.0, di = 0.0;
+            psd[d] = ev.psd[(int64_t)d * n_bins + at];
+            x[d] = ev.data[(int64_t)d * n_bins + at];
+        }
+        double er, ei;
+        gw_phasor_turns(turns_phase(ref, t1), er, ei);
+#pragma unroll
+        for (int d = 0; d < NDET; ++d) {
+            const double w = (psd[d] > 0.0 && psd[d] < INFINITY) ? 1.0 / psd[d] : NAN;
+            const double scale = 4.0 * ev.df * amp * w;
+            const double xr = scale * x[d].x, xi = -scale * x[d].y;
+            const double dr = live ? xr * er - xi * ei : 0.0, di = live ? xr * ei + xi * er : 0.0;
             if (live) {
-                const double s = ev.psd[(int64_t)d * n_bins + k];
-                const double w = (s > 0.0 && s < INFINITY) ? 1.0 / s : NAN;
-                const double2 x = ev.data[(int64_t)d * n_bins + k];
-                const double scale = 4.0 * ev.df * amp * w;
-                const double xr = scale * x.x, xi = -scale * x.y;
-                dr = xr * er - xi * ei;
-                di = xr * ei + xi * er;
-                acc[kPrepPerDet * d] += (x.x * x.x + x.y * x.y) * w;
+                acc[kPrepPerDet * d] += (x[d].x * x[d].x + x[d].y * x[d].y) * w;
                 acc[kPrepPerDet * d + 1] += amp * amp * w;
-                if (norm) acc[kPrepPerDet * d + 2] += log(2.0 * GW_PI * s);
+                if (norm) acc[kPrepPerDet * d + 2] += log(2.0 * GW_PI * psd[d]);
             }
             if (single) {
-                if (live) ev.dcoef[(int64_t)d * n_bins + k] = make_double2(dr, di);
+                if (live) ev.dcoef[(int64_t)d * n_bins + at] = make_double2(dr, di);
             } else {
                 lds_d[(2 * d) * kStride + b] = dr;
                 lds_d[(2 * d + 1) * kStride + b] = di;
@@ -235,30 +270,15 @@ __device__ __forceinline__ void spread_chunk(const NodeEvent &ev, const NodePlan
         }
     }
     if (!single && t < 4 * kComp) lds_d[(t / 4) * kStride + kSpreadBins + t % 4] = 0.0;
-    // the chunk's share of the event sums: wave sums, then the waves in order
+    if (single) return;
+    // the tap this lane weights (and its mirror image)
+    double coef[GW_RESAMPLE_DEGREE + 1];
 #pragma unroll
-    for (int i = 0; i < kPrepPerDet * NDET; ++i) {
-        const double s = wave_sum(acc[i]);
-        if (lane == 0) red[wave * kPrepPerDet * NDET + i] = s;
-    }
+    for (int j = 0; j <= GW_RESAMPLE_DEGREE; ++j) coef[j] = resample_coef[j][t % 16];
     __syncthreads();
-    if (t < kPrepPerDet * NDET) {
-        constexpr int n = kPrepPerDet * NDET;
-        ev.prep[(int64_t)chunk * n + t] = ((red[t] + red[n + t]) + red[2 * n + t]) + red[3 * n + t];
-    }
-    if (single) {
-        __syncthreads();
-        return;
-    }
 
-    // weights: this lane's taps (both halves) and its place among 4 bins
+    // this lane's column, and its place among 4 bins
     const int col = lane % 16, kk = lane / 16;
-    double c0[GW_RESAMPLE_DEGREE + 1], c1[GW_RESAMPLE_DEGREE + 1];
-#pragma unroll
-    for (int j = 0; j <= GW_RESAMPLE_DEGREE; ++j) {
-        c0[j] = resample_coef[j][col];
-        c1[j] = resample_coef[j][16 + col];
-    }
     const double inv_q2 = 2.0 / (double)v.q;
     const int cell_of_col = col / kComp, comp = col % kComp;
     const bool col_live = cell_of_col < kPack;
@@ -270,49 +290,41 @@ __device__ __forceinline__ void spread_chunk(const NodeEvent &ev, const NodePlan
         const int cells = min(kPack * S::kPacks, v.cpc - cb);
         const int packs = (cells + kPack - 1) / kPack;
         // waves share the packs, and the bins of a cell when there are fewer packs than waves
-        const int kparts = packs == 1 ? 4 : packs < 4 ? 2 : 1;
+        const int kparts = packs == 1 ? 4 : packs == 2 ? 2 : 1;
         const int groups = 4 / kparts;               // waves per part
         const int part = wave / groups, pack0 = wave % groups;
         const int steps = (sub_bins + 3) / 4;
         const int s0 = steps * part / kparts, s1 = steps * (part + 1) / kparts;
-        for (int pk = pack0; pk < packs; pk += 2 * groups) {
-            // two packs at a time share the weights
-            double4_t y00 = {0.0, 0.0, 0.0, 0.0}, y01 = y00, y10 = y00, y11 = y00;
-            const int cell_a = cb + pk * kPack + cell_of_col, cell_b = cell_a + groups * kPack;
-            const bool two = pk + groups < packs;
-            const bool live_a = col_live && cell_a < v.cpc, live_b = col_live && two && cell_b < v.cpc;
-            const double *da = lds_d + comp * kStride + (live_a ? cell_a * sub_bins : 0);
-            const double *db = lds_d + comp * kStride + (live_b ? cell_b * sub_bins : 0);
+        if (pack0 < packs) {
+            const int pk = pack0;                    // kPacks packs at most: one a wave
+            double4_t y0 = {0.0, 0.0, 0.0, 0.0}, y1 = y0;
+            const int cell = cb + pk * kPack + cell_of_col;
+            const bool on = col_live && cell < v.cpc;
+            const double *dc = lds_d + comp * kStride + (on ? cell * sub_bins : 0);
+#pragma unroll 2
             for (int s = s0; s < s1; ++s) {
                 const int j = 4 * s + kk;
                 const double x = (double)(j0 + j) * inv_q2 - 1.0;
-                double w0 = c0[GW_RESAMPLE_DEGREE], w1 = c1[GW_RESAMPLE_DEGREE];
+                const double z = x * x;
+                double even = coef[GW_RESAMPLE_DEGREE - 1], odd = coef[GW_RESAMPLE_DEGREE];
 #pragma unroll
-                for (int i = GW_RESAMPLE_DEGREE - 1; i >= 0; --i) {
-                    w0 = __builtin_fma(w0, x, c0[i]);
-                    w1 = __builtin_fma(w1, x, c1[i]);
+                for (int i = GW_RESAMPLE_DEGREE - 3; i >= 0; i -= 2) {
+                    even = __builtin_fma(even, z, coef[i]);
+                    odd = __builtin_fma(odd, z, coef[i + 1]);
                 }
-                if (j >= sub_bins) w0 = w1 = 0.0;
-                const double a = live_a && j < sub_bins ? da[j] : 0.0;
-                y00 = __builtin_amdgcn_mfma_f64_16x16x4f64(w0, a, y00, 0, 0, 0);
-                y01 = __builtin_amdgcn_mfma_f64_16x16x4f64(w1, a, y01, 0, 0, 0);
-                if (two) {
-                    const double b = live_b && j < sub_bins ? db[j] : 0.0;
-                    y10 = __builtin_amdgcn_mfma_f64_16x16x4f64(w0, b, y10, 0, 0, 0);
-                    y11 = __builtin_amdgcn_mfma_f64_16x16x4f64(w1, b, y11, 0, 0, 0);
-                }
+                // taps col and 31 - col
+                const double w0 = __builtin_fma(x, odd, even), w1 = __builtin_fma(-x, odd, even);
+                const double d = on && j < sub_bins ? dc[j] : 0.0;
+                y0 = __builtin_amdgcn_mfma_f64_16x16x4f64(w0, d, y0, 0, 0, 0);
+                y1 = __builtin_amdgcn_mfma_f64_16x16x4f64(w1, d, y1, 0, 0, 0);
             }
-            // row kk + 4 r of a 16 x 16 result is in register r
-            double *ya = lds_y + (part * packs + pk) * kTaps * 16 + col;
-            double *yb = ya + groups * kTaps * 16;
+            // row kk + 4 r of a 16 x 16 result is in register r; the second product's rows are
+            // the upper taps from the top down
+            double *y = lds_y + (part * packs + pk) * kTaps * 16 + col;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                ya[(kk + 4 * r) * 16] = y00[r];
-                ya[(16 + kk + 4 * r) * 16] = y01[r];
-                if (two) {
-                    yb[(kk + 4 * r) * 16] = y10[r];
-                    yb[(16 + kk + 4 * r) * 16] = y11[r];
-                }
+                y[(kk + 4 * r) * 16] = y0[r];
+                y[(kTaps - 1 - kk - 4 * r) * 16] = y1[r];
             }
         }
         __syncthreads();
@@ -345,12 +357,16 @@ __device__ __forceinline__ void spread_chunk(const NodeEvent &ev, const NodePlan
 // One event: every block makes the plan for itself (it costs less than a launch
 // of its own) and takes chunks blockIdx.x, + gridDim.x, ...; block 0 leaves
 // the plan for the kernels that follow.
+// Three blocks a CU where the registers allow it (up to 3 detectors): a
+// chunk is a chain of short phases, and one more block hides their latency.
 template <int NDET>
-__global__ __launch_bounds__(kBlock) void node_spread_kernel(NodeEvent ev, int norm)
+__global__ __launch_bounds__(kBlock, NDET <= 3 ? 3 : 2) void node_spread_kernel(NodeEvent ev, int norm)
 {
     extern __shared__ double lds[];
     __shared__ NodePlan plan;
     __shared__ double red[kPlanScratch];
+    constexpr int n = kPrepPerDet * NDET;
+    static_assert(kPlanScratch >= 4 * n, "the waves' sums share the plan's scratch");
     make_node_plan(ev.f_low, ev.df, ev.n_bins, NDET, ev.stats, ev.n_stats, plan, red);
     if (blockIdx.x == 0) {
         const int *src = reinterpret_cast<const int *>(&plan);
@@ -358,8 +374,21 @@ __global__ __launch_bounds__(kBlock) void node_spread_kernel(NodeEvent ev, int n
         for (int i = threadIdx.x; i < (int)(sizeof(NodePlan) / sizeof(int)); i += kBlock) dst[i] = src[i];
     }
     double *const lds_y = lds + SpreadShape<NDET>::kComp * SpreadShape<NDET>::kStride;
+    double acc[n];
+#pragma unroll
+    for (int i = 0; i < n; ++i) acc[i] = 0.0;
     for (int c = blockIdx.x; c < plan.n_chunks; c += gridDim.x)
-        spread_chunk<NDET>(ev, plan, c, norm != 0, lds, lds_y, red);
+        spread_chunk<NDET>(ev, plan, c, norm != 0, lds, lds_y, acc);
+    // the block's share of the event sums: wave sums, then the waves in order
+    const int wave = threadIdx.x / 64;
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+        const double s = wave_sum(acc[i]);
+        if (threadIdx.x % 64 == 0) red[wave * n + i] = s;
+    }
+    __syncthreads();
+    const int t = threadIdx.x;
+    if (t < n) ev.prep[(int64_t)blockIdx.x * n + t] = ((red[t] + red[n + t]) + red[2 * n + t]) + red[3 * n + t];
 }
 
 // ---------------------------------------------------------------- nodes and sums
@@ -431,7 +460,7 @@ __global__ __launch_bounds__(kBlock) void node_combine_kernel(NodeEvent ev, unsi
     __syncthreads();
     const int n_sums = kPrepPerDet * ev.n_det;
     if ((int)blockIdx.x < n_sums) {
-        const double s = column_total(plan.n_chunks, n_sums, blockIdx.x, ev.prep, red);
+        const double s = column_total(ev.spread_blocks, n_sums, blockIdx.x, ev.prep, red);
         if (threadIdx.x == 0) ev.sums[blockIdx.x] = s;
         if (queue && blockIdx.x == 0 && threadIdx.x < 2 * kQueues) queue[threadIdx.x] = 0u;
         return;
@@ -442,25 +471,24 @@ __global__ __launch_bounds__(kBlock) void node_combine_kernel(NodeEvent ev, unsi
 
 // ---------------------------------------------------------------- launchers
 template <int NDET>
-static hipError_t spread(const NodeEvent &ev, bool norm, int n_cu, hipStream_t stream)
+static hipError_t spread(const NodeEvent &ev, bool norm, hipStream_t stream)
 {
-    const int64_t blocks = std::min<int64_t>(node_max_chunks(ev.n_bins), (int64_t)n_cu * 2);
-    hipLaunchKernelGGL(node_spread_kernel<NDET>, dim3((unsigned)blocks), dim3(kBlock), SpreadShape<NDET>::kLds, stream,
-                       ev, norm ? 1 : 0);
+    hipLaunchKernelGGL(node_spread_kernel<NDET>, dim3((unsigned)ev.spread_blocks), dim3(kBlock), SpreadShape<NDET>::kLds,
+                       stream, ev, norm ? 1 : 0);
     return hipGetLastError();
 }
 
-hipError_t launch_node_spread(const NodeEvent &ev, bool norm, int n_cu, hipStream_t stream)
+hipError_t launch_node_spread(const NodeEvent &ev, bool norm, hipStream_t stream)
 {
     switch (ev.n_det) {
-    case 1: return spread<1>(ev, norm, n_cu, stream);
-    case 2: return spread<2>(ev, norm, n_cu, stream);
-    case 3: return spread<3>(ev, norm, n_cu, stream);
-    case 4: return spread<4>(ev, norm, n_cu, stream);
-    case 5: return spread<5>(ev, norm, n_cu, stream);
-    case 6: return spread<6>(ev, norm, n_cu, stream);
-    case 7: return spread<7>(ev, norm, n_cu, stream);
-    case 8: return spread<8>(ev, norm, n_cu, stream);
+    case 1: return spread<1>(ev, norm, stream);
+    case 2: return spread<2>(ev, norm, stream);
+    case 3: return spread<3>(ev, norm, stream);
+    case 4: return spread<4>(ev, norm, stream);
+    case 5: return spread<5>(ev, norm, stream);
+    case 6: return spread<6>(ev, norm, stream);
+    case 7: return spread<7>(ev, norm, stream);
+    case 8: return spread<8>(ev, norm, stream);
     default: return hipErrorInvalidValue;
     }
 }

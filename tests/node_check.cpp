@@ -28,14 +28,14 @@ int main()
         const double lg = std::uniform_real_distribution<double>(9.0, it % 50 == 0 ? 21.0 : 18.0)(rng);
         const int64_t n_bins = 1 + (int64_t)std::exp2(lg);
         const int n_det = 1 + (int)(rng() % 8);
-        int64_t first[gw::kNodeSpacings];
+        int first[gw::kNodeSpacings];
         int64_t k = it % 3 == 0 ? 0 : (int64_t)(rng() % (uint64_t)(n_bins / 4 + 1));
         for (int i = 0; i < gw::kNodeSpacings; ++i) {
-            first[i] = k < n_bins ? k : n_bins;
+            first[i] = (int)(k < n_bins ? k : n_bins);
             if (rng() % 4) k += (int64_t)(rng() % (uint64_t)(1 + n_bins / 6)) * (int64_t)(rng() % 3) / 2;
         }
         gw::NodePlan p{};
-        gw::node_levels(first, n_bins, n_det, p);
+        gw::node_levels(first, (int)n_bins, n_det, p);
         int q = 0;
         int64_t at = p.k_bin;
         int chunk = p.bin_chunks, node = 0;
@@ -47,7 +47,7 @@ int main()
             REQUIRE(v.k0 == at && v.k1 > v.k0 && v.chunk0 == chunk && v.node0 == node);
             REQUIRE(l == 0 || v.q > p.level[l - 1].q);
             REQUIRE((int64_t)v.cells * v.q >= v.k1 - v.k0 && (int64_t)(v.cells - 1) * v.q < v.k1 - v.k0);
-            REQUIRE(v.k1 - v.k0 >= (int64_t)gw::kNodeMinCells * v.q && gw::node_room_ok(v));
+            REQUIRE(v.k1 - v.k0 >= (int64_t)(l > 0 ? gw::kNodeMinCells : gw::kNodeLowCells) * v.q && gw::node_room_ok(v));
             REQUIRE(v.subs * v.sub_bins >= v.q && v.cpc * v.sub_bins <= gw::kSpreadBins);
             REQUIRE(v.cpc <= gw::kSpreadBins / gw::node_spacing(0));
             REQUIRE(v.subs == 1 ? v.sub_bins == v.q : v.cpc == gw::node_pack(n_det));
