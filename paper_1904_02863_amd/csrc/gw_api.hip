@@ -605,9 +605,27 @@ struct RaggedPlan {
     std::vector<gw::WorkItem> items;     // all classes, class by class
     std::vector<int> class_begin;        // first item of each class
     gw::RaggedLaunch launch{};
+    // on frequency nodes, class by class: the events, and the weighting's blocks; and the blocks of the node sums
+    std::vector<int> members;
+    std::vector<int2> spread_map, combine_map;
     size_t off_events = 0, off_block_map = 0, off_groups = 0, off_geoms = 0, off_items = 0, off_counters = 0;
+    size_t off_members = 0, off_first = 0, off_spread = 0, off_combine = 0;
     size_t total = 0;
 };
+
+// Whether a ragged pass sums over frequency nodes: the rule of one event's call (lnl_layout).
+bool ragged_nodes(int n_events, const gw_event *events, unsigned flags)
+{
+    if (gw::tile_form(flags) != gw::kFormSplit) return false;
+    double work = 0.0;
+    int64_t longest = 0;
+    for (int i = 0; i < n_events; ++i) {
+        const int64_t m = events[i].grid.n_bins;
+        longest = std::max(longest, m);
+        work += (double)m * (double)((events[i].n_samples + gw::kBlock - 1) / gw::kBlock);
+    }
+    return longest >= gw::kNodeMinBins && longest <= 0x7fffffffLL && work >= (double)gw::kNodeMinWork;
+}
 
 int64_t ragged_pairs(int n_events, const gw_event *events)
 {
@@ -624,9 +642,12 @@ RaggedPlan ragged_plan(gw_workspace *ws, int n_events, const gw_event *events, c
 {
     const bool direct = (flags & GW_FLAG_DIRECT) != 0, isco = (flags & GW_FLAG_TERM_ISCO) != 0;
     const int form = gw::tile_form(flags);
+    const bool nodes = ragged_nodes(n_events, events, flags);
     RaggedPlan p;
     Carver c;
     p.events.resize(n_events);
+    int64_t all_groups = 0;
+    for (int e = 0; e < n_events; ++e) all_groups += (events[e].n_samples + gw::kBlock - 1) / gw::kBlock;
     std::vector<std::vector<gw::WorkItem>> by_det(gw::kMaxDet + 1);
     std::vector<int64_t> cost_of;
     for (int e = 0; e < n_events; ++e) {
@@ -642,6 +663,15 @@ RaggedPlan ragged_plan(gw_workspace *ws, int n_events, const gw_event *events, c
         re.chunk_bins = std::min<int64_t>(chunk_bins, m);
         re.n_chunks = (int)((m + re.chunk_bins - 1) / re.chunk_bins);
         re.prep_blocks = (int)((m + gw::kBlock - 1) / gw::kBlock);
+        if (nodes) {
+            re.n_chunks = gw::ragged_max_chunks(m, all_groups, mixed);
+            re.n_stats = (int)gw::node_stat_entries(s);
+            re.spread_blocks = gw::ragged_spread_blocks(m);
+            re.combine_blocks = gw::ragged_combine_blocks(m);
+            re.plan = reinterpret_cast<gw::NodePlan *>(base + c.take(sizeof(gw::NodePlan)));
+            re.stats = reinterpret_cast<double *>(base + c.take(sizeof(double) * gw::kStats * re.n_stats));
+            re.split = reinterpret_cast<int *>(base + c.take(2 * sizeof(int)));
+        }
         re.data = reinterpret_cast<const double2 *>(data + ev.data_offset);
         re.psd = psd + ev.data_offset;
         re.theta = theta ? theta + ev.theta_offset * n_param : nullptr;
@@ -664,6 +694,7 @@ RaggedPlan ragged_plan(gw_workspace *ws, int n_events, const gw_event *events, c
         const int n_groups = (int)((s + gw::kBlock - 1) / gw::kBlock);
         for (int gi = 0; gi < n_groups; ++gi) {
             p.groups.push_back(make_int2(e, gi));
+            if (nodes) continue;             // the device cuts the event up, once it knows its nodes
             const int64_t rows = std::min<int64_t>(gw::kBlock, s - (int64_t)gi * gw::kBlock);
             for (int ch = 0; ch < re.n_chunks; ++ch) {
                 const int64_t bins = std::min(re.chunk_bins, m - (int64_t)ch * re.chunk_bins);
@@ -682,6 +713,30 @@ RaggedPlan ragged_plan(gw_workspace *ws, int n_events, const gw_event *events, c
     L.mixed = mixed;
     L.flags = flags;
     L.n_classes = 0;
+    L.nodes = nodes;
+    std::vector<size_t> member_begin, spread_begin, first_begin;
+    size_t n_first = 0;
+    for (int d = 1; nodes && d <= gw::kMaxDet; ++d) {
+        const size_t m0 = p.members.size(), b0 = p.spread_map.size();
+        for (int e = 0; e < n_events; ++e) {
+            if (events[e].n_det != d) continue;
+            p.members.push_back(e);
+            for (int b = 0; b < p.events[e].spread_blocks; ++b) p.spread_map.push_back(make_int2(e, b));
+        }
+        if (p.members.size() == m0) continue;
+        gw::RaggedClass &rc = L.classes[L.n_classes++];
+        rc.n_det = d;
+        rc.n_events = (int)(p.members.size() - m0);
+        rc.n_spread = (int)(p.spread_map.size() - b0);
+        rc.grid = ws->n_cu * gw::ragged_node_blocks_per_cu(d, tile_bins);
+        member_begin.push_back(m0);
+        spread_begin.push_back(b0);
+        first_begin.push_back(n_first);
+        n_first += 2 * ((size_t)rc.n_events + 1);
+    }
+    for (int e = 0; nodes && e < n_events; ++e)
+        for (int b = 0; b < p.events[e].combine_blocks; ++b) p.combine_map.push_back(make_int2(e, b));
+    L.n_combine = (int)p.combine_map.size();
     for (int d = 1; d <= gw::kMaxDet; ++d) {
         auto &v = by_det[d];
         if (v.empty()) continue;
@@ -702,22 +757,35 @@ RaggedPlan ragged_plan(gw_workspace *ws, int n_events, const gw_event *events, c
     p.off_groups = c.take(sizeof(int2) * std::max<size_t>(p.groups.size(), 1));
     p.off_geoms = c.take(sizeof(gw::DetGeom) * std::max(n_events, 1));
     p.off_items = c.take(sizeof(gw::WorkItem) * std::max<size_t>(p.items.size(), 1));
-    p.off_counters = c.take(sizeof(unsigned) * gw::kMaxDet);
+    p.off_counters = c.take(sizeof(unsigned) * 2 * gw::kMaxDet);
+    p.off_members = c.take(sizeof(int) * std::max<size_t>(p.members.size(), 1));
+    p.off_first = c.take(sizeof(unsigned) * std::max<size_t>(n_first, 1));
+    p.off_spread = c.take(sizeof(int2) * std::max<size_t>(p.spread_map.size(), 1));
+    p.off_combine = c.take(sizeof(int2) * std::max<size_t>(p.combine_map.size(), 1));
     p.total = c.offset;
     L.events = reinterpret_cast<const gw::RaggedEvent *>(base + p.off_events);
     L.block_map = reinterpret_cast<const int2 *>(base + p.off_block_map);
     L.groups = reinterpret_cast<const int2 *>(base + p.off_groups);
     L.geoms = reinterpret_cast<const gw::DetGeom *>(base + p.off_geoms);
     L.counters = reinterpret_cast<unsigned *>(base + p.off_counters);
+    L.combine_map = reinterpret_cast<const int2 *>(base + p.off_combine);
     for (int i = 0; i < L.n_classes; ++i) {
-        L.classes[i].items = reinterpret_cast<const gw::WorkItem *>(base + p.off_items) + p.class_begin[i];
-        L.classes[i].counter = L.counters + i;
+        gw::RaggedClass &rc = L.classes[i];
+        rc.counter = L.counters + 2 * i;
+        if (nodes) {
+            rc.events = reinterpret_cast<const int *>(base + p.off_members) + member_begin[i];
+            rc.spread_map = reinterpret_cast<const int2 *>(base + p.off_spread) + spread_begin[i];
+            rc.first = reinterpret_cast<unsigned *>(base + p.off_first) + first_begin[i];
+        } else {
+            rc.items = reinterpret_cast<const gw::WorkItem *>(base + p.off_items) + p.class_begin[i];
+        }
     }
     return p;
 }
 
-// Plans with the arena's real base, growing it first if needed, and copies
-// the host arrays to the device.  Waits for `stream` (the arena may still be
+// Plans with the arena's real base, growing it first if needed, copies the
+// host arrays to the device and writes the bin tables there (on the
+// workspace's own stream: the caller waits for it).  Waits for `stream` (the arena may still be
 // in use by earlier work there).
 int ragged_materialise(gw_workspace *ws, int n_events, const gw_event *events, const std::vector<gw::DetGeom> &geoms,
                        const gw_c128 *data, const double *psd, const double *theta, int n_param, double *lnl,
@@ -740,12 +808,17 @@ int ragged_materialise(gw_workspace *ws, int n_events, const gw_event *events, c
         {out->off_groups, out->groups.data(), sizeof(int2) * out->groups.size()},
         {out->off_geoms, geoms.data(), sizeof(gw::DetGeom) * geoms.size()},
         {out->off_items, out->items.data(), sizeof(gw::WorkItem) * out->items.size()},
+        {out->off_members, out->members.data(), sizeof(int) * out->members.size()},
+        {out->off_spread, out->spread_map.data(), sizeof(int2) * out->spread_map.size()},
+        {out->off_combine, out->combine_map.data(), sizeof(int2) * out->combine_map.size()},
     };
     for (const Copy &cp : copies) {
         if (cp.bytes == 0) continue;
         e = hipMemcpy(base + cp.off, cp.src, cp.bytes, hipMemcpyHostToDevice);
         if (e != hipSuccess) return hip_fail(e, "hipMemcpy of the ragged plan");
     }
+    e = gw::launch_ragged_tables(out->launch, ws->capture_stream);
+    if (e != hipSuccess) return hip_fail(e, "ragged bin tables");
     return GW_OK;
 }
 
@@ -831,16 +904,18 @@ int ragged_run(gw_workspace *ws, int n_events, const gw_event *events, const std
     // tile shape: autotuned once per (detectors, precision and form, size bucket)
     const int64_t pairs = ragged_pairs(na, ev);
     const int bucket = pairs > 0 ? (int)std::floor(std::log2((double)pairs)) : 0;
-    const auto tkey = std::make_tuple(max_det, (mixed ? 1 : 0) + 2 * form, bucket);
+    const auto tkey = std::make_tuple(max_det, (mixed ? 1 : 0) + 2 * form + (ragged_nodes(na, ev, flags) ? 2 * gw::kForms : 0), bucket);
     auto it = ws->ragged_tuning.find(tkey);
     int tile_bins = 0;
     int64_t chunk_bins = 0;
     RaggedPlan plan;
+    const bool on_nodes = ragged_nodes(na, ev, flags);
     if (it == ws->ragged_tuning.end()) {
         float best = 0.0f;
         for (int tb : kTuneTiles) {
             if (gw::lnl_tile_lds_bytes(max_det, tb, form, mixed) > 80 * 1024) continue;
             for (int64_t cb : kTuneChunks) {
+                if (on_nodes && cb != kTuneChunks[0]) break;     // the device sizes the items
                 if (int rc = ragged_materialise(ws, na, ev, active_geoms, data, psd, theta, n_param, lnl, mixed, flags,
                                                 tb, cb, ws->capture_stream, &plan))
                     return rc;

@@ -68,6 +68,8 @@ struct Tab2 { double f, amp; };
 
 // One event of a ragged batch as the device sees it (pointers into the
 // caller's packed arrays and into the workspace).
+struct NodePlan;          // gw_nodes.h
+
 struct RaggedEvent {
     int64_t n_bins, n_samples;
     double f_low, df;
@@ -88,6 +90,12 @@ struct RaggedEvent {
     double2 *partials;    // double [chunk][n_samples]: the chunk totals the finalize adds
     double *prep;
     double *sums;
+    // calls on frequency nodes (else null or 0): n_chunks then is the most the
+    // event may be cut into
+    NodePlan *plan;
+    double *stats;        // ranges of the phase coefficients, an entry per 64 samples
+    int *split;           // chunks of the bins (and nodes), chunks of the nodes alone (mixed precision)
+    int n_stats, spread_blocks, combine_blocks, pad2_;
 };
 
 // One unit of the persistent ragged kernel: one sample group of one event
@@ -102,7 +110,14 @@ struct RaggedClass {
     int n_items;
     int grid;                 // persistent blocks
     const WorkItem *items;    // device, sorted by decreasing cost
-    unsigned *counter;        // device
+    unsigned *counter;        // device; on frequency nodes two, one per pass
+    // on frequency nodes: the class's events, the first item of each event in
+    // either pass ([2][n_events + 1]), and the weighting's blocks (event, block)
+    const int *events;
+    int n_events;
+    unsigned *first;
+    const int2 *spread_map;
+    int n_spread;
 };
 
 // Everything one ragged pass launches (device pointers into the workspace).
@@ -115,7 +130,10 @@ struct RaggedLaunch {
     int n_groups;
     const DetGeom *geoms;     // per event
     int n_param;
-    unsigned *counters;       // kMaxDet counters
+    unsigned *counters;       // 2 kMaxDet counters
+    bool nodes;               // the call sums over frequency nodes
+    const int2 *combine_map;  // on frequency nodes, per block of the node sums: (event, block within event)
+    int n_combine;
     RaggedClass classes[kMaxDet];
     int n_classes;
     int tile_bins;
@@ -140,8 +158,6 @@ struct EventSizes {
     int64_t n_samples;
     int prep_blocks;
 };
-
-struct NodePlan;          // gw_nodes.h
 
 // Device buffers of one event's preparation (workspace sections).
 struct EventBuffers {
@@ -201,8 +217,12 @@ hipError_t launch_waveform(const gw_grid &grid, int n_out, int64_t n_samples, co
                            const double *records, gw_c128 *h_out, hipStream_t stream);
 hipError_t launch_fill_c128(int64_t n, double re, double im, gw_c128 *out, int n_cu, hipStream_t stream);
 
+// The bin tables of every event: functions of the grids alone, written once
+// per plan.
+hipError_t launch_ragged_tables(const RaggedLaunch &r, hipStream_t stream);
 hipError_t launch_ragged(const RaggedLaunch &r, hipStream_t stream);
 int lnl_ragged_blocks_per_cu(int n_det, int tile_bins, bool mixed, int form);
+int ragged_node_blocks_per_cu(int n_det, int tile_bins);
 
 // Population likelihood (gw_pop.hip): workspace bytes, weight-kernel blocks
 // and the launch of the hyper-parameter, weights and finalize kernels.

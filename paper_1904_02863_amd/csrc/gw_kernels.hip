@@ -244,6 +244,16 @@ __device__ __forceinline__ PrepView prep_view(const RaggedEvent &re)
     return v;
 }
 
+// Bin tables of all events of a ragged batch, blocks as in ragged_event_prep_kernel.
+__global__ __launch_bounds__(kBlock) void ragged_tables_kernel(const RaggedEvent *__restrict__ events,
+                                                               const int2 *__restrict__ block_map)
+{
+    const int2 em = block_map[blockIdx.x];
+    const RaggedEvent &re = events[em.x];
+    const int64_t k = (int64_t)em.y * kBlock + threadIdx.x;
+    if (k < re.n_bins) bin_tables(re.f_low, re.df, k, re.tab1, re.tab2);
+}
+
 // Ragged batch, all events at once: block b handles bins
 // [256 local, 256 local + 256) of event e, (e, local) = block_map[b].
 __global__ __launch_bounds__(kBlock) void ragged_event_prep_kernel(const RaggedEvent *__restrict__ events,
@@ -253,9 +263,6 @@ __global__ __launch_bounds__(kBlock) void ragged_event_prep_kernel(const RaggedE
     __shared__ double red[kBlock];
     const int2 em = block_map[blockIdx.x];
     const RaggedEvent &re = events[em.x];
-    const int64_t k = (int64_t)em.y * kBlock + threadIdx.x;
-    if (k < re.n_bins) bin_tables(re.f_low, re.df, k, re.tab1, re.tab2);
-    __syncthreads();
     prep_block(prep_view(re), em.y, direct != 0, norm != 0, red,
                re.prep + (int64_t)em.y * kPrepPerDet * re.n_det);
 }
@@ -610,7 +617,7 @@ __global__ __launch_bounds__(kBlock) void ragged_sample_prep_kernel(const Ragged
     const int64_t s0 = (int64_t)eg.y * kBlock + (int64_t)(blockIdx.x % kParts) * kSampleRows;
     if (s0 >= re.n_samples) return;
     prep_samples(re.f_low, re.df, re.n_bins, s0, re.n_samples, n_param, re.n_det, false, isco != 0, geoms[eg.x],
-                 re.theta, re.rec, sh, nullptr);
+                 re.theta, re.rec, sh, re.stats ? re.stats + s0 / kSampleRows * kStats : nullptr);
 }
 
 // Sets n counters to zero (a kernel rather than a memset, so that it can be
@@ -1035,6 +1042,124 @@ __global__ __launch_bounds__(kBlock) GW_TILE_ATTR void lnl_ragged_kernel(const R
     }
 }
 
+// Sample groups of an event.
+__device__ __forceinline__ int64_t groups_of(const RaggedEvent &re) { return (re.n_samples + kBlock - 1) / kBlock; }
+
+// Bins and nodes that a pass of a ragged call sums for every sample: FP64 one
+// pass over both; mixed precision the bins (0), then the nodes (1).
+__device__ __forceinline__ int64_t pass_units(const RaggedEvent &re, bool mixed, int pass)
+{
+    const NodePlan &p = *re.plan;
+    return mixed ? (pass == 0 ? p.k_bin : (int64_t)p.n_nodes) : p.k_bin + p.n_nodes;
+}
+
+// One block: the items of one detector count's events.  An event's units are known only now, and
+// differ by far more than its bins do (a short event keeps its bins, a long one
+// is nearly all nodes), so the items' size is set here: about kRaggedItems
+// items per resident block, each kRaggedUnits units or more.  Writes every event's
+// chunks (split), the first item of each (first, [2][n + 1]) and zero counters.
+__global__ __launch_bounds__(kBlock) void ragged_split_kernel(const RaggedEvent *__restrict__ events,
+                                                              const int *__restrict__ members, int n, int mixed,
+                                                              int grid, unsigned *__restrict__ first,
+                                                              unsigned *__restrict__ counter)
+{
+    __shared__ double red[kBlock];
+    const int per = (n + kBlock - 1) / kBlock;
+    const int i0 = min(n, (int)threadIdx.x * per), i1 = min(n, i0 + per);
+    if (threadIdx.x < 2) counter[threadIdx.x] = 0u;
+    for (int pass = 0; pass < (mixed ? 2 : 1); ++pass) {
+        double work = 0.0;
+        for (int i = i0; i < i1; ++i) {
+            const RaggedEvent &re = events[members[i]];
+            work += (double)(pass_units(re, mixed != 0, pass) * groups_of(re));
+        }
+        work = block_sum(work, red);
+        const int64_t size = max((int64_t)kRaggedUnits, (int64_t)ceil(work / ((double)kRaggedItems * (double)grid)));
+        double items = 0.0;
+        for (int i = i0; i < i1; ++i) {
+            const RaggedEvent &re = events[members[i]];
+            const int64_t most = mixed ? re.n_chunks / 2 : re.n_chunks;
+            const int64_t c = min(most, (pass_units(re, mixed != 0, pass) + size - 1) / size);
+            re.split[pass] = (int)c;
+            if (!mixed) re.split[1] = 0;
+            items += (double)(c * groups_of(re));
+        }
+        const double upto = block_scan(items, red);
+        double at = upto - items;
+        unsigned *const f = first + (int64_t)pass * (n + 1);
+        for (int i = i0; i < i1; ++i) {
+            const RaggedEvent &re = events[members[i]];
+            f[i] = (unsigned)at;
+            at += (double)((int64_t)re.split[pass] * groups_of(re));
+        }
+        if (threadIdx.x == kBlock - 1) f[n] = (unsigned)upto;
+    }
+}
+
+// The persistent kernel of a ragged call on frequency nodes: item k of pass `pass`
+// belongs to the event i with first[i] <= k < first[i + 1], chunk by chunk, the
+// chunk's sample groups together; a chunk takes the same share of the event's
+// bins and nodes.
+template <int NDET, bool MIXED, int NODES>
+__global__ __launch_bounds__(kBlock, 2) GW_TILE_ATTR
+void ragged_node_kernel(const RaggedEvent *__restrict__ events, const int *__restrict__ members, int n,
+                        const unsigned *__restrict__ first, unsigned *__restrict__ counter, int tile_bins)
+{
+    constexpr int kPass = NODES == kNodesOnly ? 1 : 0;
+    extern __shared__ double4 lds_raw[];
+    __shared__ int next_event, next_item;
+    double *const tiles = stage_phasor_table<MIXED>(lds_raw);
+    first += (int64_t)kPass * (n + 1);
+    const unsigned n_items = first[n];
+    for (;;) {
+        __syncthreads();                 // every thread has read the item and left the LDS tiles
+        if (threadIdx.x < 64) {
+            unsigned k = 0;
+            if (threadIdx.x == 0) k = atomicAdd(counter + kPass, 1u);
+            k = (unsigned)__shfl((int)k, 0, 64);
+            int lo = -1;
+            if (k < n_items) {
+                // the last event whose first item is not past k, 64 candidates at a time
+                lo = 0;
+                for (int span = n; span > 1;) {
+                    const int step = (span + 63) / 64, off = (int)threadIdx.x * step;
+                    const int m = __popcll(__ballot(off < span && first[lo + min(off, span - 1)] <= k)) - 1;
+                    lo += m * step;
+                    span = min(step, span - m * step);
+                }
+            }
+            if (threadIdx.x == 0) {
+                next_event = lo < 0 ? -1 : members[lo];
+                next_item = lo < 0 ? 0 : (int)(k - first[lo]);
+            }
+        }
+        __syncthreads();
+        if (next_event < 0) break;
+        const RaggedEvent &re = events[next_event];
+        const int groups = (int)groups_of(re);
+        const int chunk = next_item / groups, group = next_item % groups;
+        EventView ev;
+        ev.n_bins = re.n_bins;
+        ev.n_samples = re.n_samples;
+        ev.f_low = re.f_low;
+        ev.df = re.df;
+        ev.tab1 = re.tab1;
+        ev.dcoef = re.dcoef;
+        ev.edir = nullptr;
+        ev.vdir = nullptr;
+        ev.rec = re.rec;
+        ev.k_limit = nullptr;
+        ev.partials = re.partials;
+        ev.plan = re.plan;
+        const int n_chunks = re.split[kPass];
+        int64_t k_begin = 0, k_end = 0, n_begin = 0, n_end = 0;
+        if constexpr (NODES != kNodesOnly) chunk_range(re.plan->k_bin, chunk, n_chunks, 0, k_begin, k_end);
+        if constexpr (NODES != kNodeBins) chunk_range(re.plan->n_nodes, chunk, n_chunks, 0, n_begin, n_end);
+        tile_chunk<NDET, MIXED, kFormSplit, NODES>(ev, group, (kPass ? re.split[0] : 0) + chunk, k_begin, k_end, n_begin,
+                                                   n_end, 0, tile_bins, tiles);
+    }
+}
+
 // lnL of row s from its chunk totals: split forms -1/2 <d,d> + sum_det
 // [Re(P Z_det) - 1/2 |P|^2 Q_det], Q_det from the event sums or, with the
 // ISCO end, 4 df times the prefix sum of a^2/S up to K_s; direct form -2 df
@@ -1090,6 +1215,25 @@ __device__ __forceinline__ double finalize_row(int64_t s, int64_t n_samples, int
 // 0..15.
 constexpr int kFinRows = 16, kFinParts = kBlock / kFinRows;
 
+// Row s's chunk totals added up; true in the thread that has the sum.
+__device__ __forceinline__ bool row_total(int64_t s, int64_t n_samples, int n_chunks,
+                                          const double2 *__restrict__ partials, double &total)
+{
+    __shared__ double red[kFinParts][kFinRows];
+    const int r = threadIdx.x % kFinRows, part = threadIdx.x / kFinRows;
+    if (s < n_samples) {
+        const double *pd = reinterpret_cast<const double *>(partials);
+        double acc = 0.0;
+        for (int c = part; c < n_chunks; c += kFinParts) acc += pd[(int64_t)c * n_samples + s];
+        red[part][r] = acc;
+    }
+    __syncthreads();
+    if (part != 0 || s >= n_samples) return false;
+    total = 0.0;
+    for (int p = 0; p < kFinParts; ++p) total += red[p][r];
+    return true;
+}
+
 __global__ __launch_bounds__(kBlock) void lnl_finalize_kernel(int64_t n_samples, int n_det, int n_chunks,
                                                                int64_t n_bins, double df, unsigned flags,
                                                                const double2 *__restrict__ partials,
@@ -1099,24 +1243,27 @@ __global__ __launch_bounds__(kBlock) void lnl_finalize_kernel(int64_t n_samples,
                                                                const NodePlan *__restrict__ plan, int rounds,
                                                                int mixed, double *__restrict__ lnl)
 {
-    __shared__ double red[kFinParts][kFinRows];
     if (plan)
         n_chunks = mixed ? max(node_chunks_of(plan->k_bin, n_chunks, rounds),
                                node_chunks_of(plan->n_nodes, n_chunks, rounds))
                          : node_chunks_of(plan->k_bin + plan->n_nodes, n_chunks, rounds);
-    const int r = threadIdx.x % kFinRows, part = threadIdx.x / kFinRows;
-    const int64_t s = (int64_t)blockIdx.x * kFinRows + r;
-    if (s < n_samples) {
-        const double *pd = reinterpret_cast<const double *>(partials);
-        double acc = 0.0;
-        for (int c = part; c < n_chunks; c += kFinParts) acc += pd[(int64_t)c * n_samples + s];
-        red[part][r] = acc;
-    }
-    __syncthreads();
-    if (part != 0 || s >= n_samples) return;
-    double total = 0.0;
-    for (int p = 0; p < kFinParts; ++p) total += red[p][r];
-    lnl[s] = assemble_row(s, n_samples, n_det, n_bins, df, flags, total, rec, sums, qprefix);
+    const int64_t s = (int64_t)blockIdx.x * kFinRows + threadIdx.x % kFinRows;
+    double total;
+    if (row_total(s, n_samples, n_chunks, partials, total))
+        lnl[s] = assemble_row(s, n_samples, n_det, n_bins, df, flags, total, rec, sums, qprefix);
+}
+
+// Ragged batch on frequency nodes: blocks 16 i .. 16 i + 15 finalize the rows of group i.
+__global__ __launch_bounds__(kBlock) void ragged_node_finalize_kernel(const RaggedEvent *__restrict__ events,
+                                                                      const int2 *__restrict__ groups, unsigned flags)
+{
+    constexpr int kParts = kBlock / kFinRows;
+    const int2 eg = groups[blockIdx.x / kParts];
+    const RaggedEvent &re = events[eg.x];
+    const int64_t s = (int64_t)eg.y * kBlock + (int64_t)(blockIdx.x % kParts) * kFinRows + threadIdx.x % kFinRows;
+    double total;
+    if (row_total(s, re.n_samples, re.split[0] + re.split[1], re.partials, total))
+        re.lnl[s] = assemble_row(s, re.n_samples, re.n_det, re.n_bins, re.df, flags, total, re.rec, re.sums, nullptr);
 }
 
 // Ragged batch: block (event, group) finalizes the group's rows.
@@ -1260,6 +1407,31 @@ static const void *node_kernel_for(int n_det, NodeMode mode)
     }
 }
 
+template <int NDET>
+static const void *ragged_node_kernel_mode(NodeMode mode)
+{
+    switch (mode) {
+    case kNodeBins: return reinterpret_cast<const void *>(&ragged_node_kernel<NDET, true, kNodeBins>);
+    case kNodesOnly: return reinterpret_cast<const void *>(&ragged_node_kernel<NDET, false, kNodesOnly>);
+    default: return reinterpret_cast<const void *>(&ragged_node_kernel<NDET, false, kBinsAndNodes>);
+    }
+}
+
+static const void *ragged_node_kernel_for(int n_det, NodeMode mode)
+{
+    switch (n_det) {
+    case 1: return ragged_node_kernel_mode<1>(mode);
+    case 2: return ragged_node_kernel_mode<2>(mode);
+    case 3: return ragged_node_kernel_mode<3>(mode);
+    case 4: return ragged_node_kernel_mode<4>(mode);
+    case 5: return ragged_node_kernel_mode<5>(mode);
+    case 6: return ragged_node_kernel_mode<6>(mode);
+    case 7: return ragged_node_kernel_mode<7>(mode);
+    case 8: return ragged_node_kernel_mode<8>(mode);
+    default: return nullptr;
+    }
+}
+
 // The kernel (tile or ragged) for a detector count, precision and form.
 static const void *kernel_for(bool ragged, int n_det, bool mixed, int form)
 {
@@ -1298,6 +1470,11 @@ int lnl_ragged_blocks_per_cu(int n_det, int tile_bins, bool mixed, int form)
     return occupancy(kernel_for(true, n_det, mixed, form), tile_lds_bytes(n_det, tile_bins, form, mixed));
 }
 
+int ragged_node_blocks_per_cu(int n_det, int tile_bins)
+{
+    return occupancy(ragged_node_kernel_for(n_det, kBinsAndNodes), tile_lds_bytes(n_det, tile_bins, kFormSplit, false));
+}
+
 hipError_t launch_lnl_tiles(const gw_grid &grid, int n_det, int64_t n_samples, const TilePlan &plan, bool mixed,
                             int form, const EventBuffers &eb, const double *records, double2 *partials,
                             hipStream_t stream)
@@ -1333,8 +1510,53 @@ hipError_t launch_lnl_tiles(const gw_grid &grid, int n_det, int64_t n_samples, c
                   queue ? queue + kQueues : nullptr);
 }
 
+hipError_t launch_ragged_tables(const RaggedLaunch &r, hipStream_t stream)
+{
+    hipLaunchKernelGGL(ragged_tables_kernel, dim3(r.n_prep_blocks), dim3(kBlock), 0, stream, r.events, r.block_map);
+    return hipGetLastError();
+}
+
+// A ragged pass on frequency nodes: the samples first (the range of their phases
+// decides where an event's nodes stand), then as one event's call does it.
+static hipError_t launch_ragged_nodes(const RaggedLaunch &r, hipStream_t stream)
+{
+    hipLaunchKernelGGL(ragged_sample_prep_kernel, dim3(r.n_groups * (kBlock / kSampleRows)), dim3(kBlock), 0, stream,
+                       r.events, r.groups, r.geoms, r.n_param, 0);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || (e = launch_ragged_plans(r, stream)) != hipSuccess) return e;
+    for (int i = 0; i < r.n_classes; ++i) {
+        const RaggedClass &c = r.classes[i];
+        hipLaunchKernelGGL(ragged_split_kernel, dim3(1), dim3(kBlock), 0, stream, r.events, c.events, c.n_events,
+                           r.mixed ? 1 : 0, c.grid, c.first, c.counter);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    if ((e = launch_ragged_spread(r, stream)) != hipSuccess) return e;
+    if ((e = launch_ragged_combine(r, stream)) != hipSuccess) return e;
+    for (int i = 0; i < r.n_classes; ++i) {
+        const RaggedClass &c = r.classes[i];
+        const RaggedEvent *events = r.events;
+        const int *members = c.events;
+        const unsigned *first = c.first;
+        unsigned *counter = c.counter;
+        int n = c.n_events, tile_bins = r.tile_bins;
+        void *args[] = {&events, &members, &n, &first, &counter, &tile_bins};
+        for (const NodeMode mode : {kNodeBins, kNodesOnly, kBinsAndNodes}) {
+            if ((mode != kBinsAndNodes) != r.mixed) continue;
+            const void *fn = ragged_node_kernel_for(c.n_det, mode);
+            if (!fn) return hipErrorInvalidValue;
+            e = hipLaunchKernel(fn, dim3(c.grid), dim3(kBlock), args,
+                                tile_lds_bytes(c.n_det, tile_bins, kFormSplit, mode == kNodeBins), stream);
+            if (e != hipSuccess) return e;
+        }
+    }
+    hipLaunchKernelGGL(ragged_node_finalize_kernel, dim3((unsigned)r.n_groups * (kBlock / kFinRows)), dim3(kBlock), 0,
+                       stream, r.events, r.groups, r.flags);
+    return hipGetLastError();
+}
+
 hipError_t launch_ragged(const RaggedLaunch &r, hipStream_t stream)
 {
+    if (r.nodes) return launch_ragged_nodes(r, stream);
     const int direct = (r.flags & GW_FLAG_DIRECT) ? 1 : 0, norm = (r.flags & GW_FLAG_ADD_NORM) ? 1 : 0;
     const int form = tile_form(r.flags);
     hipLaunchKernelGGL(ragged_event_prep_kernel, dim3(r.n_prep_blocks), dim3(kBlock), 0, stream, r.events,
@@ -1353,7 +1575,7 @@ hipError_t launch_ragged(const RaggedLaunch &r, hipStream_t stream)
     hipLaunchKernelGGL(ragged_sample_prep_kernel, dim3(r.n_groups * (kBlock / kSampleRows)), dim3(kBlock), 0, stream, r.events, r.groups,
                        r.geoms, r.n_param, (r.flags & GW_FLAG_TERM_ISCO) ? 1 : 0);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(64), 0, stream, r.counters, kMaxDet);
+    hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(64), 0, stream, r.counters, 2 * kMaxDet);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     for (int i = 0; i < r.n_classes; ++i) {
         const RaggedClass &c = r.classes[i];

@@ -236,7 +236,34 @@ constexpr int64_t kNodeMinBins = 8192, kNodeMinWork = 98304;
 // Stats entries the sample kernel writes: one per block of 64 samples.
 inline int64_t node_stat_entries(int64_t n_samples) { return (n_samples + 63) / 64; }
 
+// A ragged call takes the nodes when its events together have that much work and
+// one of them is that long.  64 neutron-star events of 8 to 256 s, 512 rows each: 8.50 ms summing
+// every bin, 0.95 ms on nodes (0.37 of it the weighting, 0.48 the sums).
+// Its events are cut into items of at least kRaggedUnits bins and nodes each,
+// kRaggedItems items per resident block where there is that much work.
+constexpr int kRaggedUnits = 64, kRaggedItems = 8;
+// Blocks of the weighting of one event of a ragged call (about four chunks each),
+// and of the node sums (the first takes the event sums).
+inline int ragged_spread_blocks(int64_t n_bins) { return (int)((n_bins + 4 * kSpreadBins - 1) / (4 * kSpreadBins)); }
+inline int ragged_combine_blocks(int64_t n_bins)
+{
+    const int64_t b = (n_bins + 8191) / 8192;
+    return 1 + (int)(b < 64 ? b : 64);
+}
+// The most chunks an event of a ragged call of n_groups sample groups is cut
+// into (the chunks' partial sums take 64 MB or less over the call).
+inline int ragged_max_chunks(int64_t n_bins, int64_t n_groups, bool mixed)
+{
+    const int64_t share = 32768 / n_groups + 1, most = (n_bins + kRaggedUnits - 1) / kRaggedUnits;
+    const int64_t c = share < most ? share : most;
+    return (int)(mixed && c < 2 ? 2 : c);
+}
+
 // ---- launchers (gw_nodes.hip, gw_kernels.hip) ----
+// Ragged calls: plans, weighting (per detector count) and node sums.
+hipError_t launch_ragged_plans(const RaggedLaunch &r, hipStream_t stream);
+hipError_t launch_ragged_spread(const RaggedLaunch &r, hipStream_t stream);
+hipError_t launch_ragged_combine(const RaggedLaunch &r, hipStream_t stream);
 // Sample records and the range of their phase coefficients, one entry of
 // `stats` per 64 samples (reduced to kStatEntries when there are more).
 hipError_t launch_node_samples(const gw_grid &grid, int n_det, const SamplePrep &sp, double *stats,

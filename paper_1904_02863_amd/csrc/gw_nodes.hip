@@ -360,25 +360,16 @@ __device__ __forceinline__ void spread_chunk(const NodeEvent &ev, const NodePlan
 // Three blocks a CU where the registers allow it (up to 3 detectors): a
 // chunk is a chain of short phases, and one more block hides their latency.
 template <int NDET>
-__global__ __launch_bounds__(kBlock, NDET <= 3 ? 3 : 2) void node_spread_kernel(NodeEvent ev, int norm)
+__device__ __forceinline__ void spread_block(const NodeEvent &ev, const NodePlan &plan, int block, bool norm,
+                                             double *lds, double *red)
 {
-    extern __shared__ double lds[];
-    __shared__ NodePlan plan;
-    __shared__ double red[kPlanScratch];
     constexpr int n = kPrepPerDet * NDET;
-    static_assert(kPlanScratch >= 4 * n, "the waves' sums share the plan's scratch");
-    make_node_plan(ev.f_low, ev.df, ev.n_bins, NDET, ev.stats, ev.n_stats, plan, red);
-    if (blockIdx.x == 0) {
-        const int *src = reinterpret_cast<const int *>(&plan);
-        int *dst = reinterpret_cast<int *>(ev.plan);
-        for (int i = threadIdx.x; i < (int)(sizeof(NodePlan) / sizeof(int)); i += kBlock) dst[i] = src[i];
-    }
     double *const lds_y = lds + SpreadShape<NDET>::kComp * SpreadShape<NDET>::kStride;
     double acc[n];
 #pragma unroll
     for (int i = 0; i < n; ++i) acc[i] = 0.0;
-    for (int c = blockIdx.x; c < plan.n_chunks; c += gridDim.x)
-        spread_chunk<NDET>(ev, plan, c, norm != 0, lds, lds_y, acc);
+    for (int c = block; c < plan.n_chunks; c += ev.spread_blocks)
+        spread_chunk<NDET>(ev, plan, c, norm, lds, lds_y, acc);
     // the block's share of the event sums: wave sums, then the waves in order
     const int wave = threadIdx.x / 64;
 #pragma unroll
@@ -388,7 +379,75 @@ __global__ __launch_bounds__(kBlock, NDET <= 3 ? 3 : 2) void node_spread_kernel(
     }
     __syncthreads();
     const int t = threadIdx.x;
-    if (t < n) ev.prep[(int64_t)blockIdx.x * n + t] = ((red[t] + red[n + t]) + red[2 * n + t]) + red[3 * n + t];
+    if (t < n) ev.prep[(int64_t)block * n + t] = ((red[t] + red[n + t]) + red[2 * n + t]) + red[3 * n + t];
+}
+
+// A plan moved by all threads of a block.
+__device__ __forceinline__ void copy_plan(NodePlan *to, const NodePlan *from)
+{
+    const int *src = reinterpret_cast<const int *>(from);
+    int *dst = reinterpret_cast<int *>(to);
+    for (int i = threadIdx.x; i < (int)(sizeof(NodePlan) / sizeof(int)); i += kBlock) dst[i] = src[i];
+}
+
+template <int NDET>
+__global__ __launch_bounds__(kBlock, NDET <= 3 ? 3 : 2) void node_spread_kernel(NodeEvent ev, int norm)
+{
+    extern __shared__ double lds[];
+    __shared__ NodePlan plan;
+    __shared__ double red[kPlanScratch];
+    static_assert(kPlanScratch >= 4 * kPrepPerDet * NDET, "the waves' sums share the plan's scratch");
+    make_node_plan(ev.f_low, ev.df, ev.n_bins, NDET, ev.stats, ev.n_stats, plan, red);
+    if (blockIdx.x == 0) copy_plan(ev.plan, &plan);
+    spread_block<NDET>(ev, plan, blockIdx.x, norm != 0, lds, red);
+}
+
+// ---------------------------------------------------------------- ragged calls
+__device__ __forceinline__ NodeEvent node_event(const RaggedEvent &re)
+{
+    NodeEvent ev;
+    ev.n_bins = re.n_bins;
+    ev.n_det = re.n_det;
+    ev.f_low = re.f_low;
+    ev.df = re.df;
+    ev.data = re.data;
+    ev.psd = re.psd;
+    ev.tab1 = re.tab1;
+    ev.tab2 = re.tab2;
+    ev.dcoef = re.dcoef;
+    ev.prep = re.prep;
+    ev.spread_blocks = re.spread_blocks;
+    ev.sums = re.sums;
+    ev.stats = re.stats;
+    ev.n_stats = re.n_stats;
+    ev.plan = re.plan;
+    return ev;
+}
+
+// Block e: event e's plan.
+__global__ __launch_bounds__(kBlock) void ragged_plan_kernel(const RaggedEvent *__restrict__ events)
+{
+    __shared__ NodePlan plan;
+    __shared__ double red[kPlanScratch];
+    const RaggedEvent &re = events[blockIdx.x];
+    make_node_plan(re.f_low, re.df, re.n_bins, re.n_det, re.stats, re.n_stats, plan, red);
+    copy_plan(re.plan, &plan);
+}
+
+// Block (e, i) = map[b]: chunks i, + spread_blocks, ... of event e.
+template <int NDET>
+__global__ __launch_bounds__(kBlock, NDET <= 3 ? 3 : 2) void ragged_spread_kernel(
+    const RaggedEvent *__restrict__ events, const int2 *__restrict__ map, int norm)
+{
+    extern __shared__ double lds[];
+    __shared__ NodePlan plan;
+    __shared__ double red[4 * kPrepPerDet * NDET];
+    const int2 em = map[blockIdx.x];
+    const RaggedEvent &re = events[em.x];
+    copy_plan(&plan, re.plan);
+    const NodeEvent ev = node_event(re);
+    __syncthreads();
+    spread_block<NDET>(ev, plan, em.y, norm != 0, lds, red);
 }
 
 // ---------------------------------------------------------------- nodes and sums
@@ -452,11 +511,7 @@ __global__ __launch_bounds__(kBlock) void node_combine_kernel(NodeEvent ev, unsi
 {
     __shared__ NodePlan plan;
     __shared__ double red[kBlock];
-    {
-        const int *src = reinterpret_cast<const int *>(ev.plan);
-        int *dst = reinterpret_cast<int *>(&plan);
-        for (int i = threadIdx.x; i < (int)(sizeof(NodePlan) / sizeof(int)); i += kBlock) dst[i] = src[i];
-    }
+    copy_plan(&plan, ev.plan);
     __syncthreads();
     const int n_sums = kPrepPerDet * ev.n_det;
     if ((int)blockIdx.x < n_sums) {
@@ -469,7 +524,72 @@ __global__ __launch_bounds__(kBlock) void node_combine_kernel(NodeEvent ev, unsi
                   (int64_t)(gridDim.x - n_sums) * kBlock);
 }
 
+// Block (e, i) = map[b] of a ragged call: event e's sums (i = 0), or a share of its nodes.
+__global__ __launch_bounds__(kBlock) void ragged_combine_kernel(const RaggedEvent *__restrict__ events,
+                                                                const int2 *__restrict__ map)
+{
+    __shared__ NodePlan plan;
+    __shared__ double red[kBlock];
+    const int2 em = map[blockIdx.x];
+    const RaggedEvent &re = events[em.x];
+    if (em.y == 0) {
+        const int n_sums = kPrepPerDet * re.n_det;
+        for (int j = 0; j < n_sums; ++j) {
+            const double s = column_total(re.spread_blocks, n_sums, j, re.prep, red);
+            if (threadIdx.x == 0) re.sums[j] = s;
+        }
+        return;
+    }
+    copy_plan(&plan, re.plan);
+    const NodeEvent ev = node_event(re);
+    __syncthreads();
+    combine_items(ev, plan, (int64_t)(em.y - 1) * kBlock + threadIdx.x, (int64_t)(re.combine_blocks - 1) * kBlock);
+}
+
 // ---------------------------------------------------------------- launchers
+template <int NDET>
+static hipError_t ragged_spread(const RaggedLaunch &r, const RaggedClass &c, int norm, hipStream_t stream)
+{
+    hipLaunchKernelGGL(ragged_spread_kernel<NDET>, dim3((unsigned)c.n_spread), dim3(kBlock), SpreadShape<NDET>::kLds,
+                       stream, r.events, c.spread_map, norm);
+    return hipGetLastError();
+}
+
+hipError_t launch_ragged_spread(const RaggedLaunch &r, hipStream_t stream)
+{
+    const int norm = (r.flags & GW_FLAG_ADD_NORM) ? 1 : 0;
+    for (int i = 0; i < r.n_classes; ++i) {
+        const RaggedClass &c = r.classes[i];
+        hipError_t e = hipErrorInvalidValue;
+        switch (c.n_det) {
+        case 1: e = ragged_spread<1>(r, c, norm, stream); break;
+        case 2: e = ragged_spread<2>(r, c, norm, stream); break;
+        case 3: e = ragged_spread<3>(r, c, norm, stream); break;
+        case 4: e = ragged_spread<4>(r, c, norm, stream); break;
+        case 5: e = ragged_spread<5>(r, c, norm, stream); break;
+        case 6: e = ragged_spread<6>(r, c, norm, stream); break;
+        case 7: e = ragged_spread<7>(r, c, norm, stream); break;
+        case 8: e = ragged_spread<8>(r, c, norm, stream); break;
+        default: break;
+        }
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+hipError_t launch_ragged_plans(const RaggedLaunch &r, hipStream_t stream)
+{
+    hipLaunchKernelGGL(ragged_plan_kernel, dim3((unsigned)r.n_events), dim3(kBlock), 0, stream, r.events);
+    return hipGetLastError();
+}
+
+hipError_t launch_ragged_combine(const RaggedLaunch &r, hipStream_t stream)
+{
+    hipLaunchKernelGGL(ragged_combine_kernel, dim3((unsigned)r.n_combine), dim3(kBlock), 0, stream, r.events,
+                       r.combine_map);
+    return hipGetLastError();
+}
+
 template <int NDET>
 static hipError_t spread(const NodeEvent &ev, bool norm, hipStream_t stream)
 {
