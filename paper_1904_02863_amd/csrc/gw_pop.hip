@@ -22,11 +22,13 @@
 // a last kernel adds the events of each Lambda by a fixed tree.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <string>
 
 #include "gw_build_id.h"
 #include "gw_internal.h"
+#include "gw_reduce.h"
 
 namespace gw {
 namespace pop {
@@ -38,19 +40,31 @@ constexpr int kThreads = 256;
 constexpr int kPerThread = GW_POP_PER_THREAD;     // samples per thread, held in registers
 constexpr int kPerBlock = kThreads * kPerThread;   // samples of one event per block
 constexpr int kWaves = kThreads / 64;
+constexpr int64_t kFillBlocks = 1024;              // blocks that fill the device, four a compute unit
+static_assert(kPerThread % 2 == 0, "samples share divisions in pairs");
 static_assert(kThreads == 256, "the weights kernel fills its 256-entry exp table one entry per thread");
 
-// Constants of one hyper-parameter point.
+// Constants of one hyper-parameter point.  (Their rounding is common to all events, so lnL
+// feels it once per event: coefficients scaled to the exponentials' table and
+// constants folded together, which save 6 operations, made the error against 64 bits 3 to
+// 5% larger.)
 struct HyperC {
-    double neg_alpha, ln_zpl;             // power law: m^-alpha / Z_pl
-    double mu, inv_sigma, ln_zg;          // peak: exp(-((m - mu)/sigma)^2 / 2) / (sigma sqrt(2 pi) Z_g)
+    double mmin, mmax, ln_mmin, mu;
+    double beta, ach_m1, bch_m1, c_e;     // q^beta and the spin magnitudes
+    double neg_alpha, c_pl;               // power law: m^-alpha / Z_pl
+    double inv_sigma, c_g;                // peak: exp(-((m - mu) / sigma)^2 / 2 + c_g)
     double one_m_lam, lam;
-    double mmin, mmax, ln_mmin, beta, one_p_beta;
-    double ach_m1, bch_m1, ln_beta_fn;    // spin magnitudes
-    double iso, xi, k1, k2, ln_zt;        // tilts
+    double k1, k2, c_t, iso, xi;          // tilts: iso + xi exp(k1 c1^2 + k2 c2^2 + c_t)
+    double one_p_beta, num;               // mass ratio: num / expm1(one_p_beta ln q_min)
     int status;                           // 1 evaluate, 0 out of domain, -1 non-finite
     int beta_is_m1;                       // beta == -1: log normalisation of q
+    int pairs, pad;                       // two samples may share a division (kPairsMin)
 };
+
+// Two samples' weights n0 / d0 + n1 / d1 are one quotient over d0 d1.  The
+// product must not leave the range: |d| <= 1 for beta > -1 (and a logarithm
+// for beta = -1), and this far above -1 it stays above 1e-38.
+constexpr double kPairsMin = 1e-3;
 
 __device__ __forceinline__ double gauss_mass(double mu, double sigma, double lo, double hi)
 {
@@ -79,37 +93,50 @@ __global__ __launch_bounds__(kThreads) void hyper_kernel(int64_t n_hyper, const 
         const double L = log(mmax / mmin);
         const double e = 1.0 - alpha;
         const double zpl = alpha == 1.0 ? L : exp(e * log(mmin)) * expm1(e * L) / e;
+        const double ln_beta_fn = lgamma(ach) + lgamma(bch) - lgamma(ach + bch);
         c.neg_alpha = -alpha;
-        c.ln_zpl = log(zpl);
+        c.c_pl = -log(zpl);
+        c.c_e = -2.0 * ln_beta_fn;
         c.mu = mpp;
         c.inv_sigma = 1.0 / sigpp;
-        c.ln_zg = log(sigpp * 2.5066282746310002 * gauss_mass(mpp, sigpp, mmin, mmax));
+        c.c_g = -log(sigpp * 2.5066282746310002 * gauss_mass(mpp, sigpp, mmin, mmax));
         c.one_m_lam = 1.0 - lam;
         c.lam = lam;
         c.mmin = mmin;
         c.mmax = mmax;
         c.ln_mmin = log(mmin);
         c.beta = beta;
-        c.one_p_beta = 1.0 + beta;
+        c.one_p_beta = (1.0 + beta);
         c.beta_is_m1 = beta == -1.0 ? 1 : 0;
-        c.ach_m1 = ach - 1.0;
-        c.bch_m1 = bch - 1.0;
-        c.ln_beta_fn = lgamma(ach) + lgamma(bch) - lgamma(ach + bch);
+        c.num = c.beta_is_m1 ? -1.0 : -(1.0 + beta);
+        c.pairs = c.beta_is_m1 || 1.0 + beta >= kPairsMin ? 1 : 0;
+        c.ach_m1 = (ach - 1.0);
+        c.bch_m1 = (bch - 1.0);
         c.iso = (1.0 - xi) / 4.0;
         c.xi = xi;
-        c.k1 = 0.5 / (s1 * s1);
-        c.k2 = 0.5 / (s2 * s2);
-        c.ln_zt = log(s1 * 2.5066282746310002 * gauss_mass(1.0, s1, -1.0, 1.0)) +
-                  log(s2 * 2.5066282746310002 * gauss_mass(1.0, s2, -1.0, 1.0));
+        c.k1 = -0.5 / (s1 * s1);
+        c.k2 = -0.5 / (s2 * s2);
+        c.c_t = -(log(s1 * 2.5066282746310002 * gauss_mass(1.0, s1, -1.0, 1.0)) +
+                  log(s2 * 2.5066282746310002 * gauss_mass(1.0, s2, -1.0, 1.0)));
     }
     out[k] = c;
 }
 
 // One sample's logarithms and flags, kept across the hyper-parameter loop.
 struct Sample {
-    double m1, ln_m1, ln_q, q, ln_a_sum, ln_1ma_sum, c1m, c2m, ln_prior;
+    double m1, ln_m1, ln_q, ln_a_sum, ln_1ma_sum, c1m, c2m, ln_prior;
     bool ok;   // inside every support that does not depend on Lambda
+    double c1s, c2s, prior;               // what the loop takes of the last three (loop_terms)
 };
+
+// m1 = -1 for a sample outside the supports: no mass support holds it.
+__device__ __forceinline__ void loop_terms(Sample &x)
+{
+    x.m1 = x.ok ? x.m1 : -1.0;
+    x.c1s = x.c1m * x.c1m;
+    x.c2s = x.c2m * x.c2m;
+    x.prior = -x.ln_prior;
+}
 
 __device__ __forceinline__ Sample load_sample(const double *__restrict__ s, int64_t plane, int64_t idx, bool live)
 {
@@ -124,7 +151,6 @@ __device__ __forceinline__ Sample load_sample(const double *__restrict__ s, int6
     if (!x.ok) return x;
     x.m1 = m1;
     x.ln_m1 = log(m1);
-    x.q = q;
     x.ln_q = log(q);
     x.ln_a_sum = log(a1) + log(a2);
     x.ln_1ma_sum = log1p(-a1) + log1p(-a2);
@@ -172,72 +198,132 @@ __global__ __launch_bounds__(kThreads) void prepare_kernel(int64_t plane, const 
     p[7 * plane + i] = x.ok ? x.ln_prior : 0.0;
 }
 
-// e^x for finite x from the table t[j] = 2^(j/256) (LDS, 256 entries): with
-// k = rint(256 x / ln 2) (the round-to-integer of adding 1.5 * 2^52, whose low
-// bits are k in two's complement) and r = x - k ln 2 / 256 (two-constant
-// Cody-Waite reduction, |r| <= ln 2 / 512), e^x = 2^(k >> 8) t[k & 255] e^r,
-// e^r by its Taylor polynomial of degree 4 (next term below 4e-17).  x is
-// clamped to [-746, 710] first (below, e^x underflows to 0; above, the
-// result overflows to inf), which keeps |k| < 2^19.  14 operations and one
-// LDS read against ~30 for the library's exp.
-__device__ __forceinline__ double table_exp(double x, const double *__restrict__ t)
+// Table entries of the exponential, 2^(j/256) and what rounding left of it.
+struct ExpTable {
+    double hi[256], lo[256];
+};
+
+// Entry j as the product of its bits' factors in two doubles each.
+__device__ __forceinline__ void fill_exp_table(ExpTable &t, int j)
+{
+    constexpr double fh[8] = {1.0027112750502025, 1.0054299011128027, 1.0108892860517005, 1.0218971486541166,
+                              1.0442737824274138, 1.0905077326652577, 1.189207115002721, 1.4142135623730951};
+    constexpr double fl[8] = {-3.636615928692264e-17, 9.499186535455032e-17, -1.5234778603368577e-17,
+                              5.109225028973444e-17, 8.551889705537965e-17, -3.046782079812471e-17,
+                              3.982015231465646e-17, -9.667293313452913e-17};
+    double h = 1.0, l = 0.0;
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+        const double gh = (j >> b) & 1 ? fh[b] : 1.0, gl = (j >> b) & 1 ? fl[b] : 0.0;
+        const double p = h * gh;
+        const double e = __builtin_fma(h, gh, -p) + __builtin_fma(h, gl, l * gh);
+        h = p + e;
+        l = e - (h - p);
+    }
+    t.hi[j] = h;
+    t.lo[j] = l;
+}
+
+// An exponent x in table steps of ln 2 / 256: x = k ln 2 / 256 + r, k the nearest integer
+// (the round-to-integer of adding 1.5 * 2^52, whose low bits are k in two's
+// complement), r by a two-constant Cody-Waite reduction, |r| <= ln 2 / 512, so e^x =
+// 2^(k >> 8) 2^((k & 255) / 256) e^r.  x is clamped first: below -746 e^x underflows
+// to 0, above 710 it overflows to inf, and |k| stays below 2^19.
+struct Steps {
+    int k;
+    double r;
+};
+
+__device__ __forceinline__ Steps split_steps(double x, double most)
 {
     constexpr double kRound = 6755399441055744.0;          // 1.5 * 2^52
     constexpr double kInvStep = 369.3299304675746;          // 256 / ln 2
     constexpr double kStepHi = 0.002707604318857193;        // ln 2 / 256, 21 leading bits
     constexpr double kStepLo = 1.855205093371747e-09;       // the rest of ln 2 / 256
-    x = fmin(fmax(x, -746.0), 710.0);
+    x = fmin(fmax(x, -746.0), most);
     const double tt = __builtin_fma(x, kInvStep, kRound);
     const double kf = tt - kRound;
-    double r = __builtin_fma(-kf, kStepHi, x);
-    r = __builtin_fma(-kf, kStepLo, r);
-    const int k = __double2loint(tt);
+    Steps s;
+    s.r = __builtin_fma(-kf, kStepLo, __builtin_fma(-kf, kStepHi, x));
+    s.k = __double2loint(tt);
+    return s;
+}
+
+// (e^r - 1) / r, its Taylor polynomial of degree 3 (next term of the exponential below 4e-17).
+__device__ __forceinline__ double step_poly(double r)
+{
     double p = __builtin_fma(r, 1.0 / 24.0, 1.0 / 6.0);
     p = __builtin_fma(p, r, 0.5);
-    p = __builtin_fma(p, r, 1.0);
-    p = __builtin_fma(p, r, 1.0);
-    return __builtin_ldexp(t[k & 255] * p, k >> 8);
+    return __builtin_fma(p, r, 1.0);
 }
 
-// p(theta | Lambda) / p(theta | 0) of one sample; t: the table of table_exp.
-__device__ __forceinline__ double weight(const Sample &x, const HyperC &c, const double *__restrict__ t)
+// e^x: 14 operations and one LDS read.
+__device__ __forceinline__ double table_exp(double x, const ExpTable &t)
 {
-    if (!x.ok || x.m1 < c.mmin || x.m1 > c.mmax) return 0.0;
-    const double ln_qmin = c.ln_mmin - x.ln_m1;          // q_min = m_min / m1
-    if (x.m1 <= c.mmin || x.ln_q < ln_qmin) return 0.0;
-    // q^beta, the two spin magnitudes and the prior: the log of every factor
-    // but the primary mass, tilts and q normalisation
-    double e = __builtin_fma(c.beta, x.ln_q, -x.ln_prior);
-    e = __builtin_fma(c.ach_m1, x.ln_a_sum, e);
-    e = __builtin_fma(c.bch_m1, x.ln_1ma_sum, e);
-    e -= 2.0 * c.ln_beta_fn;
-    // primary mass times exp(e): both mixture components carry it
-    const double a_pl = __builtin_fma(c.neg_alpha, x.ln_m1, e - c.ln_zpl);
-    const double z = (x.m1 - c.mu) * c.inv_sigma;
-    const double a_g = __builtin_fma(-0.5 * z, z, e - c.ln_zg);
-    const double p_me = __builtin_fma(c.one_m_lam, table_exp(a_pl, t), c.lam * table_exp(a_g, t));
-    // 1 / the mass ratio normalisation int_{q_min}^1 x^beta dx (one division
-    // whichever form the point takes)
-    const double num = c.beta_is_m1 ? -1.0 : -c.one_p_beta;
-    const double den = c.beta_is_m1 ? ln_qmin : expm1(c.one_p_beta * ln_qmin);
-    const double inv_zq = num / den;
-    // tilts
-    const double g = table_exp(-(c.k1 * x.c1m * x.c1m + c.k2 * x.c2m * x.c2m) - c.ln_zt, t);
-    const double p_t = __builtin_fma(c.xi, g, c.iso);
-    return p_me * p_t * inv_zq;
+    const Steps s = split_steps(x, 710.0);
+    const double h = t.hi[s.k & 255];
+    return __builtin_ldexp(__builtin_fma(h * s.r, step_poly(s.r), h), s.k >> 8);
 }
 
-// Block b = event * chunks + chunk: kPerBlock samples of the event; for every
-// Lambda each wave writes the sum of its samples' weights to
+// e^x - 1 with no digits lost near 0: 2^k - 1 is exact up to the entry's own
+// rounding, which is in the table too.  The clamp keeps 2^k finite.
+__device__ __forceinline__ double table_expm1(double x, const ExpTable &t)
+{
+    const Steps s = split_steps(x, 709.7);
+    const int j = s.k & 255, e = s.k >> 8;
+    const double h = __builtin_ldexp(t.hi[j], e), l = __builtin_ldexp(t.lo[j], e);
+    return (h - 1.0) + __builtin_fma(h * s.r, step_poly(s.r), l);
+}
+
+// p(theta | Lambda) / p(theta | 0) of one sample is c.num n / d: d the integral of
+// the mass ratio's power law, n the rest.  Samples outside the support: 0 / 1.
+__device__ __forceinline__ void weight(const Sample &x, const HyperC &c, const ExpTable &t, double &n, double &d)
+{
+    const double ln_qmin = c.ln_mmin - x.ln_m1;          // q_min = m_min / m1
+    // (a sample outside every support carries m1 <= 0)
+    const bool in = (x.m1 > c.mmin) & (x.m1 <= c.mmax) & (x.ln_q >= ln_qmin);
+    // the log of every factor but the primary mass, tilts and q normalisation
+    double e = __builtin_fma(c.beta, x.ln_q, x.prior);
+    e = __builtin_fma(c.ach_m1, x.ln_a_sum, e);
+    e = __builtin_fma(c.bch_m1, x.ln_1ma_sum, e) + c.c_e;
+    // primary mass times exp(e): both mixture components carry it
+    const double a_pl = __builtin_fma(c.neg_alpha, x.ln_m1, e + c.c_pl);
+    const double z = (x.m1 - c.mu) * c.inv_sigma;
+    const double a_g = __builtin_fma(-0.5 * z, z, e + c.c_g);
+    const double p_me = __builtin_fma(c.one_m_lam, table_exp(a_pl, t), c.lam * table_exp(a_g, t));
+    const double g = table_exp(__builtin_fma(c.k1, x.c1s, __builtin_fma(c.k2, x.c2s, c.c_t)), t);
+    const double w = p_me * __builtin_fma(c.xi, g, c.iso);
+    // (evaluated for beta = -1 too: a branch here would keep the samples' chains apart)
+    const double q = table_expm1(c.one_p_beta * ln_qmin, t);
+    n = in ? w : 0.0;
+    d = in ? (c.beta_is_m1 ? ln_qmin : q) : 1.0;
+}
+
+// 1 / x for x of ordinary size: the hardware's approximation and two Newton steps.
+__device__ __forceinline__ double reciprocal(double x)
+{
+    double y = __builtin_amdgcn_rcp(x);
+    y = __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+    return __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+}
+
+// Block (b = event * chunks + chunk, y): kPerBlock samples of the event; for every
+// Lambda of slice y each wave writes the sum of its samples' weights to
 // partials[(k * n_events + event) * n_slots + chunk * kWaves + wave].
+//
+// Bound by instruction issue: 109 vector instructions per sample and Lambda, three
+// exponentials, one expm1 and half a division among them, at about 0.9 of the issue
+// slots.  200 events x 20,000 samples x 64 points, the whole call: 1131 us with the
+// library's expm1 and a division per sample (150 instructions), 779 us now.  4 samples per thread: 6 and 8
+// measured 2 to 3% less (2: 15% more), but events of a few hundred samples fill fewer lanes.
 template <bool PREPARED>
-__global__ __launch_bounds__(kThreads) void weights_kernel(int64_t n_events, int64_t n_per, int64_t chunks,
+__global__ __launch_bounds__(kThreads, 2) void weights_kernel(int64_t n_events, int64_t n_per, int64_t chunks,
                                                            const double *__restrict__ s, int64_t n_hyper,
                                                            const HyperC *__restrict__ hc, int64_t n_slots,
                                                            double *__restrict__ partials)
 {
-    __shared__ double t_exp[256];
-    t_exp[threadIdx.x] = exp2((double)threadIdx.x / 256.0);     // kThreads == 256
+    __shared__ ExpTable t_exp;
+    fill_exp_table(t_exp, threadIdx.x);                         // kThreads == 256
     __syncthreads();
     const int64_t event = (int64_t)blockIdx.x / chunks, chunk = (int64_t)blockIdx.x % chunks;
     const int64_t plane = n_events * n_per;
@@ -249,16 +335,27 @@ __global__ __launch_bounds__(kThreads) void weights_kernel(int64_t n_events, int
         const int64_t j = chunk * kPerBlock + (int64_t)i * kThreads + threadIdx.x;
         x[i] = PREPARED ? load_prepared(s, plane, event * n_per + j, j < n_per)
                         : load_sample(s, plane, event * n_per + j, j < n_per);
+        loop_terms(x[i]);
     }
-    for (int64_t k = 0; k < n_hyper; ++k) {
+    const int64_t k_end = n_hyper * (blockIdx.y + 1) / gridDim.y;
+    for (int64_t k = n_hyper * blockIdx.y / gridDim.y; k < k_end; ++k) {
         const HyperC c = hc[k];
         double w = 0.0;
         if (c.status == 1) {
+            double n[kPerThread], d[kPerThread];
 #pragma unroll
-            for (int i = 0; i < kPerThread; ++i) w += weight(x[i], c, t_exp);
+            for (int i = 0; i < kPerThread; ++i) weight(x[i], c, t_exp, n[i], d[i]);
+            if (c.pairs) {
+#pragma unroll
+                for (int i = 0; i < kPerThread; i += 2)
+                    w = __builtin_fma(__builtin_fma(n[i], d[i + 1], n[i + 1] * d[i]), reciprocal(d[i] * d[i + 1]), w);
+            } else {
+#pragma unroll
+                for (int i = 0; i < kPerThread; ++i) w += n[i] / d[i];
+            }
+            w *= c.num;
         }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) w += __shfl_xor(w, off, 64);
+        w = wave_sum(w);
         if (lane == 0) partials[(k * n_events + event) * n_slots + chunk * kWaves + wave] = w;
     }
 }
@@ -337,11 +434,15 @@ hipError_t launch(int64_t n_events, int64_t n_per, const double *samples, bool p
     const int64_t chunks = (n_per + kPerBlock - 1) / kPerBlock;
     const int64_t n_slots = slots_per_event(n_per);
     if (t_start && (e = hipEventRecord(t_start, stream)) != hipSuccess) return e;
+    // With few blocks the points are shared out as well: 10 events x 500 samples x 64 points
+    // 114 us with every point in the 10 blocks, 20 us; 100 x 1000 x 64 151 and 42 us.
+    const int64_t blocks = chunks * n_events;
+    const unsigned slices = (unsigned)std::max<int64_t>(1, std::min(n_hyper, kFillBlocks / blocks));
     if (prepared)
-        hipLaunchKernelGGL(weights_kernel<true>, dim3((unsigned)(chunks * n_events)), dim3(kThreads), 0, stream,
+        hipLaunchKernelGGL(weights_kernel<true>, dim3((unsigned)blocks, slices), dim3(kThreads), 0, stream,
                            n_events, n_per, chunks, samples, n_hyper, hc, n_slots, partials);
     else
-        hipLaunchKernelGGL(weights_kernel<false>, dim3((unsigned)(chunks * n_events)), dim3(kThreads), 0, stream,
+        hipLaunchKernelGGL(weights_kernel<false>, dim3((unsigned)blocks, slices), dim3(kThreads), 0, stream,
                            n_events, n_per, chunks, samples, n_hyper, hc, n_slots, partials);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (t_stop && (e = hipEventRecord(t_stop, stream)) != hipSuccess) return e;
