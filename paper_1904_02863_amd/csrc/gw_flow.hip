@@ -293,11 +293,14 @@ __device__ __forceinline__ void gemm_group_tile(GemmArgs g, const GemmGroup &gg,
     gemm_tile<true, true>(g, gg.va[p], gg.vb[p], bx, by, bz);
 }
 
-// Blocks layer by layer, each layer's as start[] lays out its three products.
+// Block b works on layer b mod L, so that with 8 layers each XCD (the dispatcher deals
+// blocks to them in turn) reads one layer's operands into its own L2; a layer's blocks
+// as start[] lays out its three products.  4096 rows, 8 layers of 256: 36 us layer by layer, 30.
 __global__ __launch_bounds__(256) void gemm_group_kernel(GemmGroup gg)
 {
-    const int layer = (int)blockIdx.x / gg.start[3];
-    const int b = (int)blockIdx.x - layer * gg.start[3];
+    const int layers = (int)gridDim.x / gg.start[3];
+    const int layer = (int)blockIdx.x % layers;
+    const int b = (int)blockIdx.x / layers;
     const int p = (b >= gg.start[1]) + (b >= gg.start[2]);
     const int local = b - gg.start[p];
     const int bx = local % gg.gx[p], rest = local / gg.gx[p];
@@ -478,112 +481,24 @@ __global__ __launch_bounds__(256) void coupling_kernel(int n, int dim, unsigned 
 // A coupling of the flow on kLayerRows rows per block, for hidden widths
 // H = 128 and 256: the MLP's three products on the matrix cores with both
 // hidden activations held in LDS, then the coupling of each row.  Each of the
-// 4 waves owns H/4 hidden columns; lane l works on rows l%16 and k group l/16
+// waves owns a share of the hidden columns; lane l works on rows l%16 and k group l/16
 // as in the GEMM, with the same v_mfma_f32_16x16x32_bf16 sequence over k, so
 // the activations and outputs equal the GEMM path's bit for bit.  The
 // weights come straight from global memory (L2-resident) in 16-byte
 // fragments: W1 with padded rows (K = kInPad, zero padding), W2 [H][H] and
 // W3 [2 dim][H] as stored (out, in).
 constexpr int kLayerRows = 16;
-
-struct LayerArgs {
-    int n, dim, dir;
-    unsigned cond;
-    const uint16_t *xm;                   // [n][kInPad] masked MLP input
-    const uint16_t *w1p, *w2, *w3;
-    const float *b1, *b2, *b3;
-    uint16_t *h1, *h2;                    // [n][H] activations, kept for the backward pass
-    uint16_t *h1T, *h2T;                  // transposed copies (training) or null
-    int64_t ldT;
-    const double *a;
-    double *y, *sum_s, *s_out;
-    NextMask nm;
-};
-
-__device__ __forceinline__ bf16x8_t ld_bf16x8(const uint16_t *p) { return *reinterpret_cast<const bf16x8_t *>(p); }
-
-template <int H>
-__device__ __forceinline__ void store_hidden(const LayerArgs &p, uint16_t (*hs)[H + 8], uint16_t *hg, uint16_t *hT,
-                                             const float4_t (&acc)[H / 64], const float (&bias)[H / 64], int r0,
-                                             int c0, int g, int lr)
-{
-#pragma unroll
-    for (int t = 0; t < H / 64; ++t) {
-        const int j = c0 + 16 * t + lr;
-        const float bj = bias[t];
-        uint16_t q[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            float v = acc[t][r] + bj;
-            v = v > 0.f ? v : 0.f;
-            q[r] = f32_to_bf16(v);
-            hs[4 * g + r][j] = q[r];
-            const int i = r0 + 4 * g + r;
-            if (i < p.n) hg[(int64_t)i * H + j] = q[r];
-        }
-        if (hT) {
-            uint16_t *t4 = hT + (int64_t)j * p.ldT + r0 + 4 * g;
-            if (r0 + 4 * g + 3 < p.n) {
-                *reinterpret_cast<uint2 *>(t4) = make_uint2((uint32_t)q[0] | ((uint32_t)q[1] << 16),
-                                                            (uint32_t)q[2] | ((uint32_t)q[3] << 16));
-            } else {
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (r0 + 4 * g + r < p.n) t4[r] = q[r];
-            }
-        }
-    }
-}
-
-// The fragments of the H x H matrix w read as B(k, j) = w[j H + k] that this
-// wave's columns c0 + 16 t + lr take in the k step kk = 32 k: f[t][k], 16
-// bytes each from global memory.  The coupling kernels load them all at
-// their start (128 VGPRs at H = 256; a block of 4 waves runs one wave per
-// SIMD), so that the loads overlap the first product instead of making each
-// k step of the middle one wait on L2.
-template <int H>
-__device__ __forceinline__ void load_square_frags(bf16x8_t (&f)[H / 64][H / 32], const uint16_t *__restrict__ w,
-                                                  int c0, int g, int lr)
-{
-#pragma unroll
-    for (int k = 0; k < H / 32; ++k)
-#pragma unroll
-        for (int t = 0; t < H / 64; ++t) f[t][k] = ld_bf16x8(w + (int64_t)(c0 + 16 * t + lr) * H + 32 * k + 8 * g);
-}
-
-// acc[t] += rows of xs (LDS, [16][H + 8]) times w, from its fragments f
-// (load_square_frags), k step by k step.
-template <int H>
-__device__ __forceinline__ void products_from_lds(float4_t (&acc)[H / 64], const uint16_t (*xs)[H + 8],
-                                                  const bf16x8_t (&f)[H / 64][H / 32], int g, int lr)
-{
-#pragma unroll
-    for (int k = 0; k < H / 32; ++k) {
-        const bf16x8_t av = *reinterpret_cast<const bf16x8_t *>(&xs[lr][32 * k + 8 * g]);
-#pragma unroll
-        for (int t = 0; t < H / 64; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, f[t][k], acc[t], 0, 0, 0);
-    }
-}
-
-// A chain of couplings applied to the same rows in the order of c.layer[]:
-// coupling li + 1 takes coupling li's output rows.  A row's chain does not
-// involve the other rows, so one block carries its 16 rows through every
-// coupling of the chain: the output element of thread (row, dimension) stays
-// in its register as that thread's input of the next coupling, the next
-// coupling's masked BF16 input in LDS, and each row's sum of log-scales in a
-// register of one thread.  Every coupling still writes its outputs to global
-// memory (the backward pass and the weight gradients read them).  The
-// couplings share n, dim and sum_s; the first coupling's masked BF16 input is
-// formed from its input rows (layer[0].xm is not read).
-constexpr int kMaxChain = 16;
+#ifndef GW_FLOW_WAVES
+#define GW_FLOW_WAVES 8
+#endif
+constexpr int kChainWaves = GW_FLOW_WAVES;    // waves of a block
 
 // What a chain launch does around its couplings (the flow's ends, so that a
 // pass needs no other launch).
 struct ChainEnds {
     int init_sum;             // the rows' sums of log-scales start from zero (else from sum_s)
-    int affine_in;            // the first coupling's input is (a - mu) / sigma of the rows a = layer[0].a,
+    int affine_in;            // the first coupling's input is (a - mu) / sigma of its rows a,
                               // and the sums start from sum log sigma
-    NextMask in_mask;         // with affine_in: where the first coupling's masked input is kept (xm may be null)
     double *affine_out;       // x = mu + sigma y of the last coupling's output rows goes here (null: none),
                               // and the sums gain sum log sigma
     const double *mu, *log_sigma;
@@ -592,35 +507,174 @@ struct ChainEnds {
     double *logq, *loss, *g;  // -|z|^2/2 - dim/2 log 2 pi - sum_s, |z|^2/2 + sum_s, z / n (each may be null)
 };
 
+__device__ __forceinline__ bf16x8_t ld_bf16x8(const uint16_t *p) { return *reinterpret_cast<const bf16x8_t *>(p); }
+
+// The couplings of a chain, in the order applied: coupling l = first + step k
+// for k = 0 .. count - 1.  Every array is given by its base and its stride from
+// layer to layer, so that the arguments are a few cache lines: a launch's
+// arguments lie in host memory, and reading a coupling's own pointers from
+// there (150 bytes each) before each coupling put that latency into the chain.
+constexpr int kMaxChain = 16;
+
 struct LayerChain {
-    LayerArgs layer[kMaxChain];
-    int count;
+    int n, dim, dir, first, step, count;
+    unsigned cond[kMaxChain + 1];         // conditioning masks in that order, and the one after the last (0: none)
+    const uint16_t *w1p, *w2, *w3;        // BF16 weights of layer 0
+    int64_t wT_stride, w_stride;          // layer strides of w1p, and of w2 and w3
+    const float *b1, *b2, *b3;
+    int64_t b_stride;
+    // training: transposed activations [layer][H][ldT] and inputs [layer][kInPad][ldT], boundaries
+    // [layer + 1][..] and log-scales [layer][..]
+    uint16_t *h1T, *h2T, *xmT;
+    int64_t ldT;
+    double *bound, *s_out;
+    int64_t row_stride;                   // layer stride of bound and s_out
+    const double *a;                      // input rows
+    double *sum_s;
+    double *y_out;                        // the last coupling's output rows (null: not wanted)
     ChainEnds e;
 };
 static_assert(sizeof(LayerChain) <= 4096, "a chain is passed by value as the kernel's arguments (4 KiB at most)");
 
-template <int H>
-__global__ __launch_bounds__(256) void layer_kernel(LayerChain c)
+// Hidden activations of the block's 16 rows: relu(acc + bias) as BF16 to LDS, and with
+// KEEP to the transposed copy (rows past n are the padding of its rows).
+template <int H, int NW, bool KEEP>
+__device__ __forceinline__ void store_hidden(uint16_t (*hs)[H + 8], uint16_t *hT, int64_t ldT,
+                                             const float4_t (&acc)[H / 16 / NW], const float (&bias)[H / 16 / NW],
+                                             int r0, int c0, int g, int lr)
+{
+#pragma unroll
+    for (int t = 0; t < H / 16 / NW; ++t) {
+        const int j = c0 + 16 * t + lr;
+        uint16_t q[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            float v = acc[t][r] + bias[t];
+            v = v > 0.f ? v : 0.f;
+            q[r] = f32_to_bf16(v);
+            hs[4 * g + r][j] = q[r];
+        }
+        if constexpr (KEEP)
+            *reinterpret_cast<uint2 *>(hT + (int64_t)j * ldT + r0 + 4 * g) =
+                make_uint2((uint32_t)q[0] | ((uint32_t)q[1] << 16), (uint32_t)q[2] | ((uint32_t)q[3] << 16));
+    }
+}
+
+// The fragments of the H x H matrix w (frag_index, row j the product's column) that
+// this wave's columns c0 + 16 t + lr take in the k step kk = 32 k: f[t][k].
+template <int H, int NW>
+__device__ __forceinline__ void load_square_frags(bf16x8_t (&f)[H / 16 / NW][H / 32], const uint16_t *__restrict__ w,
+                                                  int c0, int lane)
+{
+#pragma unroll
+    for (int k = 0; k < H / 32; ++k)
+#pragma unroll
+        for (int t = 0; t < H / 16 / NW; ++t)
+            f[t][k] = ld_bf16x8(w + (((c0 / 16 + t) * (H / 32) + k) * 64 + lane) * 8);
+}
+
+// acc[t] += rows of xs (LDS, [16][H + 8]) times w, from its fragments f
+// (load_square_frags), k step by k step.
+template <int H, int NW>
+__device__ __forceinline__ void products_from_lds(float4_t (&acc)[H / 16 / NW], const uint16_t (*xs)[H + 8],
+                                                  const bf16x8_t (&f)[H / 16 / NW][H / 32], int g, int lr)
+{
+#pragma unroll
+    for (int k = 0; k < H / 32; ++k) {
+        const bf16x8_t av = *reinterpret_cast<const bf16x8_t *>(&xs[lr][32 * k + 8 * g]);
+#pragma unroll
+        for (int t = 0; t < H / 16 / NW; ++t)
+            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, f[t][k], acc[t], 0, 0, 0);
+    }
+}
+
+// 4 rows (4 q .. 4 q + 3) of a column of LDS as 8 bytes of a transposed copy.
+template <typename T, int LD>
+__device__ __forceinline__ uint2 column4(const T (*xs)[LD], int col, int q)
+{
+    uint32_t v[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        if constexpr (sizeof(T) == 2)
+            v[r] = xs[4 * q + r][col];
+        else
+            v[r] = f32_to_bf16(xs[4 * q + r][col]);
+    }
+    return make_uint2(v[0] | (v[1] << 16), v[2] | (v[3] << 16));
+}
+
+// A chain of couplings applied to the same rows: one block carries its 16
+// rows through every coupling, since a row's chain does not involve the other
+// rows; the output element of thread (row, dimension) stays in its register as that
+// thread's input of the next coupling, the next coupling's masked BF16 input in
+// LDS, and each row's sum of log-scales in a register of one thread.  KEEP
+// (training): the couplings leave what the backward pass and the weight gradients
+// read; otherwise only the chain's ends reach memory.
+//
+// What bounds it: a serial chain of short phases per coupling (three products
+// of 16 rows, four barriers, tanh and exp in FP64) on one block per CU, and
+// the 143 KB of BF16 weights each block takes from L2 per coupling, 2,240 cycles at 64
+// bytes a cycle.  A coupling's fragments are therefore loaded one coupling
+// ahead, each into its registers as soon as their product has run, so that the
+// loads pass under the rest of the chain; NW waves share a coupling's
+// columns.  4096 rows, 8 couplings: 68 us with each coupling's loads at its own start, its
+// arguments read one by one, row-major activations stored for nobody and 4 waves; 36 us now
+// (24 with the weights loaded once: what is left of the loads is 12).
+template <int H, int NW, bool KEEP>
+__global__ __launch_bounds__(64 * NW) void layer_kernel(LayerChain c)
 {
     __shared__ __align__(16) uint16_t h1s[kLayerRows][H + 8];
     __shared__ __align__(16) uint16_t h2s[kLayerRows][H + 8];
     __shared__ __align__(16) uint16_t xin[kLayerRows][kInPad];
     __shared__ float outs[kLayerRows][kOutPad];
-    __shared__ double sdet[kLayerRows][16];
-    constexpr int NT = H / 64;            // 16-column tiles per wave
+    __shared__ __align__(16) double sdet[kLayerRows][16];
+    constexpr int NT = H / 16 / NW;       // 16-column tiles per wave
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r0 = blockIdx.x * kLayerRows;
     const int lr = lane & 15, g = lane >> 4;
-    const int c0 = wave * (H / 4);
-    const int crr = tid >> 4, ci = tid & 15;   // the coupling's (row, dimension)
+    const int c0 = wave * (H / NW);
+    const int crr = (tid >> 4) & 15, ci = tid & 15;   // the coupling's (row, dimension): threads 0-255
+    const bool own = tid < 256;
     const bf16x8_t zero8 = {};
-    const int n = c.layer[0].n, dim = c.layer[0].dim;
+    const int n = c.n, dim = c.dim, n_out = 2 * dim;
     const bool row_ok = r0 + lr < n;
     const ChainEnds &e = c.e;
+    const int ocol = 16 * (wave & 1) + lr;
     // the rows' inputs of the first coupling, loaded first (rows clamped to
     // valid ones), and its masked BF16 input rows formed from them
     const int64_t oc = (int64_t)min(r0 + crr, n - 1) * dim + min(ci, dim - 1);
-    double yv = c.layer[0].a[oc];
+    double yv = c.a[oc];
+    // the first coupling's operands (output columns past 2 dim repeat the last one,
+    // never read; lane groups 2 and 3 hold the zero padding of K from kInPad to
+    // 32 in the input rows, so W1's fragments there may repeat real ones)
+    float b1v[NT], b2v[NT], b3v = 0.f;
+    bf16x8_t w1f[NT], w2f[NT][H / 32], w3f[H / 32];
+    auto load_w1 = [&](int l) {
+        const uint16_t *w = c.w1p + l * c.wT_stride;
+        const float *b = c.b1 + l * c.b_stride;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            b1v[t] = b[c0 + 16 * t + lr];
+            w1f[t] = ld_bf16x8(w + (int64_t)(c0 + 16 * t + lr) * kInPad + 8 * (g & 1));
+        }
+    };
+    auto load_w2 = [&](int l) {
+        const float *b = c.b2 + l * c.b_stride;
+        load_square_frags<H, NW>(w2f, c.w2 + l * c.w_stride, c0, lane);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) b2v[t] = b[c0 + 16 * t + lr];
+    };
+    auto load_w3 = [&](int l) {           // waves 0 and 1, a 16-column tile each
+        if (wave < 2) {
+            const uint16_t *w = c.w3 + l * c.w_stride + (int64_t)min(ocol, n_out - 1) * H + 8 * g;
+            b3v = (c.b3 + l * c.b_stride)[min(ocol, n_out - 1)];
+#pragma unroll
+            for (int k = 0; k < H / 32; ++k) w3f[k] = ld_bf16x8(w + 32 * k);
+        }
+    };
+    load_w1(c.first);
+    load_w2(c.first);
+    load_w3(c.first);
     double srow;                                     // used by threads 0-15
     if (e.affine_in) {
         const int k = min(ci, dim - 1);
@@ -629,48 +683,18 @@ __global__ __launch_bounds__(256) void layer_kernel(LayerChain c)
         for (int j = 0; j < dim; ++j) acc += e.log_sigma[j];
         srow = 0.0 + acc;
     } else {
-        srow = e.init_sum ? 0.0 : c.layer[0].sum_s[min(r0 + (tid & 15), n - 1)];
+        srow = e.init_sum ? 0.0 : c.sum_s[min(r0 + (tid & 15), n - 1)];
     }
-    {
-        const uint16_t x0 = (r0 + crr < n && ci < dim && ((c.layer[0].cond >> ci) & 1u)) ? f32_to_bf16((float)yv)
-                                                                                         : (uint16_t)0;
-        xin[crr][ci] = x0;
-        if (e.affine_in && e.in_mask.xm && r0 + crr < n) {
-            e.in_mask.xm[(int64_t)(r0 + crr) * kInPad + ci] = x0;
-            if (e.in_mask.xmT) e.in_mask.xmT[ci * e.in_mask.ldT + r0 + crr] = x0;
-        }
-    }
+    if (own)
+        xin[crr][ci] = (r0 + crr < n && ci < dim && ((c.cond[0] >> ci) & 1u)) ? f32_to_bf16((float)yv) : (uint16_t)0;
     __syncthreads();
     for (int li = 0; li < c.count; ++li) {
-        const LayerArgs &p = c.layer[li];
-        // Every operand of the coupling is loaded now, unconditionally
-        // (clamped to valid rows), in the order of use: the loads complete in
-        // order, so that a use waits only for its own load and those before
-        // it, and a load under a branch would make the wave wait for all of
-        // them.  The biases, W1's fragments, then W2's, then W3's.
-        const int n_out = 2 * dim;
-        const int ocol = 16 * (wave & 1) + lr;
-        float b1v[NT], b2v[NT];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            b1v[t] = p.b1[c0 + 16 * t + lr];
-            b2v[t] = p.b2[c0 + 16 * t + lr];
-        }
-        const float b3v = p.b3[min(ocol, n_out - 1)];
-        // lane groups 2 and 3 hold the zero padding of K from kInPad to 32 (in
-        // the input rows, so W1's fragments there may repeat real ones)
-        bf16x8_t w1f[NT];
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-            w1f[t] = ld_bf16x8(p.w1p + (int64_t)(c0 + 16 * t + lr) * kInPad + 8 * (g & 1));
-        bf16x8_t w2f[NT][H / 32];
-        load_square_frags<H>(w2f, p.w2, c0, g, lr);
-        // output columns past 2 dim repeat the last one (never read)
-        bf16x8_t w3f[H / 32];
-#pragma unroll
-        for (int k = 0; k < H / 32; ++k)
-            w3f[k] = ld_bf16x8(p.w3 + (int64_t)min(ocol, n_out - 1) * H + 32 * k + 8 * g);
-        __builtin_amdgcn_sched_barrier(0);   // all loads issued before the first product waits on its own
+        const int l = c.first + c.step * li;
+        const int l_next = li + 1 < c.count ? l + c.step : l;
+        const unsigned cond = c.cond[li], cond_next = c.cond[li + 1];
+        if (KEEP && tid < 4 * kInPad)
+            *reinterpret_cast<uint2 *>(c.xmT + ((int64_t)l * kInPad + (tid >> 2)) * c.ldT + r0 + 4 * (tid & 3)) =
+                column4(xin, tid >> 2, tid & 3);
         // h1 = relu(xm W1^T + b1), K = kInPad padded to 32 by zeros
         const bf16x8_t xs = *reinterpret_cast<const bf16x8_t *>(&xin[lr][8 * (g & 1)]);
         const bf16x8_t xa = (g < 2 && row_ok) ? xs : zero8;
@@ -678,82 +702,82 @@ __global__ __launch_bounds__(256) void layer_kernel(LayerChain c)
 #pragma unroll
         for (int t = 0; t < NT; ++t)
             acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, w1f[t], float4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-        store_hidden<H>(p, h1s, p.h1, p.h1T, acc, b1v, r0, c0, g, lr);
+        store_hidden<H, NW, KEEP>(h1s, c.h1T + (int64_t)l * H * c.ldT, c.ldT, acc, b1v, r0, c0, g, lr);
+        load_w1(l_next);
         __syncthreads();
         // h2 = relu(h1 W2^T + b2), K = H
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[t] = float4_t{0.f, 0.f, 0.f, 0.f};
-        products_from_lds<H>(acc, h1s, w2f, g, lr);
-        store_hidden<H>(p, h2s, p.h2, p.h2T, acc, b2v, r0, c0, g, lr);
+        products_from_lds<H, NW>(acc, h1s, w2f, g, lr);
+        store_hidden<H, NW, KEEP>(h2s, c.h2T + (int64_t)l * H * c.ldT, c.ldT, acc, b2v, r0, c0, g, lr);
+        __builtin_amdgcn_sched_barrier(0);
+        load_w2(l_next);
+        __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
-        // out = h2 W3^T + b3: 2 dim <= 32 columns, one 16-column tile for each of waves 0 and 1
+        // out = h2 W3^T + b3: 2 dim <= 32 columns
         if (wave < 2) {
-            const int col = ocol;
             float4_t o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int k = 0; k < H / 32; ++k) {
                 const bf16x8_t av = *reinterpret_cast<const bf16x8_t *>(&h2s[lr][32 * k + 8 * g]);
                 o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, w3f[k], o, 0, 0, 0);
             }
-            const float bc = col < n_out ? b3v : 0.f;
+            const float bc = ocol < n_out ? b3v : 0.f;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) outs[4 * g + r][col] = o[r] + bc;
+            for (int r = 0; r < 4; ++r) outs[4 * g + r][ocol] = o[r] + bc;
         }
+        __builtin_amdgcn_sched_barrier(0);
+        load_w3(l_next);
         __syncthreads();
         // the coupling: thread (row, i) = (tid / 16, tid % 16) takes dimension
         // i of a row, then each row's log-determinant terms are added in
-        // dimension order by one thread (the order of the row-at-a-time kernel)
-        {
-            const int rr = crr, i = ci;
-            const int b = r0 + rr;
+        // dimension order by one thread
+        if (own) {
             double sv = 0.0;
             uint16_t xv = 0;
-            if (b < n && i < dim) {
+            if (r0 + crr < n && ci < dim) {
                 const double ai = yv;
                 double yi = ai;
-                if (!((p.cond >> i) & 1u)) {
-                    const double r = (double)outs[rr][i];
-                    const double t = (double)outs[rr][dim + i];
+                if (!((cond >> ci) & 1u)) {
+                    const double r = (double)outs[crr][ci];
+                    const double t = (double)outs[crr][dim + ci];
                     sv = 3.0 * tanh(r / 3.0);
-                    yi = p.dir > 0 ? ai * exp(sv) + t : (ai - t) * exp(-sv);
+                    yi = c.dir > 0 ? ai * exp(sv) + t : (ai - t) * exp(-sv);
                 }
-                p.y[(int64_t)b * dim + i] = yi;
-                if (p.s_out) p.s_out[(int64_t)b * dim + i] = sv;
-                xv = ((p.nm.cond >> i) & 1u) ? f32_to_bf16((float)yi) : (uint16_t)0;
-                if (p.nm.xm) {
-                    p.nm.xm[(int64_t)b * kInPad + i] = xv;
-                    if (p.nm.xmT) p.nm.xmT[i * p.nm.ldT + b] = xv;
+                if constexpr (KEEP) {
+                    // inverse direction: coupling l's output is boundary l
+                    c.bound[l * c.row_stride + oc] = yi;
+                    c.s_out[l * c.row_stride + oc] = sv;
                 }
+                xv = ((cond_next >> ci) & 1u) ? f32_to_bf16((float)yi) : (uint16_t)0;
                 yv = yi;
-            } else if (b < n && p.nm.xm) {
-                p.nm.xm[(int64_t)b * kInPad + i] = 0;         // dimensions past dim of the next input
-                if (p.nm.xmT) p.nm.xmT[i * p.nm.ldT + b] = 0;
             }
-            sdet[rr][i] = sv;
-            xin[rr][i] = xv;                                  // the next coupling's input row
+            sdet[crr][ci] = sv;
+            xin[crr][ci] = xv;                                // the next coupling's input row
         }
         __syncthreads();
         if (tid < kLayerRows) {
-            double acc_s = 0.0;
-            for (int i = 0; i < dim; ++i)
-                if (!((p.cond >> i) & 1u)) acc_s += sdet[tid][i];
+            double acc_s = 0.0;                               // conditioning dimensions hold zero
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc_s += sdet[tid][i];
             srow += acc_s;
         }
     }
+    const bool mine = own && r0 + crr < n && ci < dim;
+    if (c.y_out && mine) c.y_out[oc] = yv;
     if (e.affine_out) {
-        if (r0 + crr < n && ci < dim)
-            e.affine_out[(int64_t)(r0 + crr) * dim + ci] = e.mu[ci] + exp(e.log_sigma[ci]) * yv;
+        if (mine) e.affine_out[oc] = e.mu[ci] + exp(e.log_sigma[ci]) * yv;
         double acc = 0.0;
         for (int j = 0; j < dim; ++j) acc += e.log_sigma[j];
         srow = srow + acc;
     }
-    if (tid < kLayerRows && r0 + tid < n) c.layer[0].sum_s[r0 + tid] = srow;
+    if (tid < kLayerRows && r0 + tid < n) c.sum_s[r0 + tid] = srow;
     if (e.density) {
         // z_i to LDS, then each row's |z|^2 in dimension order by one thread
         const double zi = e.z_in ? e.z_in[oc] : yv;
-        if (e.g && r0 + crr < n && ci < dim) e.g[(int64_t)(r0 + crr) * dim + ci] = zi / (double)n;
+        if (e.g && mine) e.g[oc] = zi / (double)n;
         __syncthreads();                             // the last coupling's sums have read sdet
-        sdet[crr][ci] = zi;
+        if (own) sdet[crr][ci] = zi;
         __syncthreads();
         if (tid < kLayerRows && r0 + tid < n) {
             double zz = 0.0;
@@ -833,122 +857,131 @@ __global__ __launch_bounds__(256) void base_density_kernel(int n, int dim, const
 // kernel writes their transposed BF16 operands (doutT, dpreT, dpre2T) and the
 // bias gradients' partial sums over its rows (FP64, fixed order) into
 // bpart: [block][H] for b1 and b2 (at bp1, bp2), [block][2 dim] for b3.
-struct BackArgs {
-    int n, dim;
-    unsigned cond;
-    const double *g, *x, *s;              // d loss / d x, x = the coupling's output (inverse direction), s
-    double *gy;                           // d loss / d y
-    const uint16_t *h1T, *h2T;            // [H][ldT] activations of the forward pass, transposed
-    const uint16_t *w1t, *w2t, *w3t;      // W1^T [D][H], W2^T [H][H], W3^T [H][kOutPad]
-    uint16_t *doutT, *dpreT, *dpre2T;     // transposed operands of the weight gradients (row length ldT)
+//
+// The couplings of a chain in the order of the backward pass, l = first .. first +
+// count - 1, arrays by base and layer stride as in LayerChain: one block per 16
+// rows carries d loss / d y of a coupling on as the next one's d loss / d x, in LDS
+// between them (the direct part from the head, then the MLP's part on the
+// conditioning dimensions added to it).
+struct BackChain {
+    int n, dim, first, count;
+    unsigned cond[kMaxChain];
+    const double *g;                      // d loss / d x of the first coupling
+    double *gy;                           // d loss / d y of the last
+    const double *bound, *s_store;        // x = the coupling's output (inverse direction: boundary l), and s
+    int64_t row_stride;
+    uint16_t *h1T, *h2T;                  // [layer][H][ldT] activations of the forward pass, transposed
+    const uint16_t *wt;                   // W1^T [D][H], W2^T [H][H], W3^T [H][kOutPad] of layer 0
+    int64_t wt_stride;
+    uint16_t *doutT, *dpreT, *dpre2T;     // [layer][..][ldT] transposed operands of the weight gradients
     int64_t ldT;
-    double *bp1, *bp2, *bp3;              // bias partials [block][H], [block][H], [block][2 dim]
+    double *bp;                           // bias partials of layer 0: b1, b2 [rb_cap][H], b3 [rb_cap][2 dim]
+    int64_t bp_stride, rb_cap;
 };
+static_assert(sizeof(BackChain) <= 4096, "a chain is passed by value as the kernel's arguments (4 KiB at most)");
 
-template <int H>
-__device__ __forceinline__ void masked_hidden(const BackArgs &p, uint16_t (*ds)[H + 8], uint16_t *dT, double *bp,
-                                              const float4_t (&acc)[H / 64], const uint2 (&h4)[H / 64], int r0,
-                                              int c0, int g, int lr)
+// v of the block's rows where the activation's sign (h4) is positive, as BF16 to LDS
+// and the transposed copy, and the columns' sums over the rows.
+template <int H, int NW>
+__device__ __forceinline__ void masked_hidden(int n, uint16_t (*ds)[H + 8], uint16_t *dT, int64_t ldT, double *bp,
+                                              const float4_t (&acc)[H / 16 / NW], const uint2 (&h4)[H / 16 / NW],
+                                              int r0, int c0, int g, int lr)
 {
 #pragma unroll
-    for (int t = 0; t < H / 64; ++t) {
+    for (int t = 0; t < H / 16 / NW; ++t) {
         const int j = c0 + 16 * t + lr;
         uint16_t q[4];
         double cs = 0.0;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int i = r0 + 4 * g + r;
             float v = acc[t][r];
-            if (i < p.n) {
-                const uint32_t w = r < 2 ? h4[t].x : h4[t].y;
-                const uint16_t hv = (uint16_t)(r % 2 == 0 ? w & 0xffffu : w >> 16);
-                v = ((hv & 0x7fffu) != 0 && !(hv & 0x8000u)) ? v : 0.f;
-            } else {
-                v = 0.f;
-            }
+            const uint32_t w = r < 2 ? h4[t].x : h4[t].y;
+            const uint16_t hv = (uint16_t)(r % 2 == 0 ? w & 0xffffu : w >> 16);
+            v = (r0 + 4 * g + r < n && (hv & 0x7fffu) != 0 && !(hv & 0x8000u)) ? v : 0.f;
             q[r] = f32_to_bf16(v);
             ds[4 * g + r][j] = q[r];
             cs += (double)v;
         }
-        uint16_t *t4 = dT + (int64_t)j * p.ldT + r0 + 4 * g;
-        if (r0 + 4 * g + 3 < p.n) {
-            *reinterpret_cast<uint2 *>(t4) = make_uint2((uint32_t)q[0] | ((uint32_t)q[1] << 16),
-                                                        (uint32_t)q[2] | ((uint32_t)q[3] << 16));
-        } else {
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (r0 + 4 * g + r < p.n) t4[r] = q[r];
-        }
+        *reinterpret_cast<uint2 *>(dT + (int64_t)j * ldT + r0 + 4 * g) =
+            make_uint2((uint32_t)q[0] | ((uint32_t)q[1] << 16), (uint32_t)q[2] | ((uint32_t)q[3] << 16));
         // the column's sum over the block's 16 rows: each lane's 4, then the 4 lane groups
         cs += __shfl_xor(cs, 16);
         cs += __shfl_xor(cs, 32);
-        if (g == 0) bp[(int64_t)blockIdx.x * H + j] = cs;
+        if (g == 0) bp[j] = cs;
     }
 }
 
-// The backward couplings of a chain, in the order of c.layer[], carried
-// through by one block per 16 rows as in layer_kernel: coupling li + 1 takes
-// d loss / d y of coupling li as its d loss / d x, kept in LDS between them
-// (the direct part from the head, then the MLP's part on the conditioning
-// dimensions added to it).  Every coupling still writes its transposed
-// operands of the weight gradients and its bias partials to global memory;
-// the last one also writes d loss / d y.  The couplings share n and dim.
-struct BackChain {
-    BackArgs layer[kMaxChain];
-    int count;
-};
-static_assert(sizeof(BackChain) <= 4096, "a chain is passed by value as the kernel's arguments (4 KiB at most)");
-
-template <int H>
-__global__ __launch_bounds__(256) void layer_back_kernel(BackChain c)
+// Bound as layer_kernel is, and its operands loaded one coupling ahead in the same
+// way.  4096 rows, 8 couplings: 86 us -> 43 us.
+template <int H, int NW>
+__global__ __launch_bounds__(64 * NW) void layer_back_kernel(BackChain c)
 {
     __shared__ float dos[kLayerRows][kOutPad];
     __shared__ __align__(16) uint16_t d2s[kLayerRows][H + 8];
     __shared__ __align__(16) uint16_t d1s[kLayerRows][H + 8];
     __shared__ double gys[kLayerRows][16];
-    constexpr int NT = H / 64;
+    constexpr int NT = H / 16 / NW;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r0 = blockIdx.x * kLayerRows;
     const int lr = lane & 15, g = lane >> 4;
-    const int c0 = wave * (H / 4);
-    const int n = c.layer[0].n, D = c.layer[0].dim;
-    const int rr = tid >> 4, i = tid & 15;   // the head's (row, dimension)
+    const int c0 = wave * (H / NW);
+    const int n = c.n, D = c.dim;
+    const int rr = (tid >> 4) & 15, i = tid & 15;   // the head's (row, dimension): threads 0-255
+    const bool own = tid < 256;
     const int64_t oc = (int64_t)min(r0 + rr, n - 1) * D + min(i, D - 1);
-    double gv = c.layer[0].g[oc];            // d loss / d x of the first coupling, loaded first
-    for (int li = 0; li < c.count; ++li) {
-        const BackArgs &p = c.layer[li];
-        // Every operand is loaded now, unconditionally (clamped to valid
-        // rows), in the order of use (the loads complete in order; a load
-        // under a branch would make the wave wait for all of them): this
-        // thread's element of the head, the activations' signs for the two
-        // ReLU masks (4 rows of a column in 8 bytes of the transposed copies),
-        // then the weight fragments of the three products (W1's rows past dim
-        // repeat the last, never read).
-        const double xv = p.x[oc], sv = p.s[oc];
-        uint2 m2[NT], m1[NT];
+    const int64_t at0 = (int64_t)(c0 + lr) * c.ldT + r0 + 4 * g;
+    // this thread's element of the head, the activations' signs for the two ReLU
+    // masks (4 rows of a column in 8 bytes of the transposed copies) and the weight
+    // fragments of the three products (W1's rows past dim repeat the last, never read)
+    double xv, sv;
+    uint2 m2[NT], m1[NT];
+    bf16x8_t w3f[NT], w2f[NT][H / 32], w1f[H / 32];
+    auto load_head = [&](int l) {
+        xv = c.bound[l * c.row_stride + oc];
+        sv = c.s_store[l * c.row_stride + oc];
+    };
+    auto load_mask = [&](uint2 (&m)[NT], const uint16_t *hT, int l) {
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const int64_t at = (int64_t)(c0 + 16 * t + lr) * p.ldT + r0 + 4 * g;
-            m2[t] = *reinterpret_cast<const uint2 *>(p.h2T + at);
-            m1[t] = *reinterpret_cast<const uint2 *>(p.h1T + at);
+        for (int t = 0; t < NT; ++t)
+            m[t] = *reinterpret_cast<const uint2 *>(hT + (int64_t)l * H * c.ldT + at0 + (int64_t)(16 * t) * c.ldT);
+    };
+    auto load_w3 = [&](int l) {
+        const uint16_t *w = c.wt + l * c.wt_stride + (int64_t)D * H + (int64_t)H * H;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) w3f[t] = ld_bf16x8(w + (int64_t)(c0 + 16 * t + lr) * kOutPad + 8 * g);
+    };
+    auto load_w2 = [&](int l) {
+        load_square_frags<H, NW>(w2f, c.wt + l * c.wt_stride + (int64_t)D * H, c0, lane);
+    };
+    auto load_w1 = [&](int l) {           // wave 0 alone
+        if (wave == 0) {
+            const uint16_t *w = c.wt + l * c.wt_stride + (int64_t)min(lr, D - 1) * H + 8 * g;
+#pragma unroll
+            for (int k = 0; k < H / 32; ++k) w1f[k] = ld_bf16x8(w + 32 * k);
         }
-        bf16x8_t w3f[NT], w2f[NT][H / 32], w1f[H / 32];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) w3f[t] = ld_bf16x8(p.w3t + (int64_t)(c0 + 16 * t + lr) * kOutPad + 8 * g);
-        load_square_frags<H>(w2f, p.w2t, c0, g, lr);
-#pragma unroll
-        for (int k = 0; k < H / 32; ++k) w1f[k] = ld_bf16x8(p.w1t + (int64_t)min(lr, D - 1) * H + 32 * k + 8 * g);
+    };
+    double gv = c.g[oc];                     // d loss / d x of the first coupling, loaded first
+    load_head(c.first);
+    load_w3(c.first);
+    load_mask(m2, c.h2T, c.first);
+    load_w2(c.first);
+    load_mask(m1, c.h1T, c.first);
+    load_w1(c.first);
+    for (int k = tid; k < kLayerRows * kOutPad; k += 64 * NW) (&dos[0][0])[k] = 0.f;   // columns past 2 dim stay zero
+    __syncthreads();
+    for (int li = 0; li < c.count; ++li) {
+        const int l = c.first + li;
+        const int l_next = li + 1 < c.count ? l + 1 : l;
+        const unsigned cond = c.cond[li];
+        double *const bp = c.bp + l * c.bp_stride;
         // the inverse coupling's backward: thread (row, i) = (tid / 16, tid % 16)
         // takes dimension i of a row (dout columns i and D + i)
-        {
-            const int b = r0 + rr;
-            dos[rr][i] = 0.f;
-            dos[rr][16 + i] = 0.f;
+        if (own) {
             if (li > 0) gv = gys[rr][i];     // the previous coupling's d loss / d y
-            __syncthreads();
             double gd = 0.0;                 // the direct part of d loss / d y
-            if (b < n && i < D) {
-                if ((p.cond >> i) & 1u) {
+            float dr_f = 0.f, dt_f = 0.f;
+            if (r0 + rr < n && i < D) {
+                if ((cond >> i) & 1u) {
                     gd = gv;
                 } else {
                     const double inv_n = 1.0 / (double)n;
@@ -957,23 +990,18 @@ __global__ __launch_bounds__(256) void layer_back_kernel(BackChain c)
                     const double ds = -gv * xv + inv_n;
                     const double dr = ds * (1.0 - (si / 3.0) * (si / 3.0));
                     gd = gv * e;
-                    dos[rr][i] = (float)dr;
-                    dos[rr][D + i] = (float)dt;
+                    dr_f = (float)dr;
+                    dt_f = (float)dt;
                 }
             }
-            gys[rr][i] = gd;
-            __syncthreads();
-            if (b < n) {
-                p.doutT[(int64_t)i * p.ldT + b] = f32_to_bf16(dos[rr][i]);
-                p.doutT[(int64_t)(16 + i) * p.ldT + b] = f32_to_bf16(dos[rr][16 + i]);
+            if (i < D) {
+                dos[rr][i] = dr_f;
+                dos[rr][D + i] = dt_f;
             }
+            gys[rr][i] = gd;
         }
+        load_head(l_next);
         __syncthreads();
-        if (tid < 2 * D) {
-            double t = 0.0;
-            for (int r = 0; r < kLayerRows; ++r) t += (double)dos[r][tid];
-            p.bp3[(int64_t)blockIdx.x * 2 * D + tid] = t;
-        }
         // dh2 = dout W3 (K = 2 dim <= 32 in one step), masked by h2 > 0
         float4_t acc[NT];
         {
@@ -984,13 +1012,21 @@ __global__ __launch_bounds__(256) void layer_back_kernel(BackChain c)
             for (int t = 0; t < NT; ++t)
                 acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, w3f[t], float4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
         }
-        masked_hidden<H>(p, d2s, p.dpreT, p.bp2, acc, m2, r0, c0, g, lr);
+        masked_hidden<H, NW>(n, d2s, c.dpreT + (int64_t)l * H * c.ldT, c.ldT,
+                             bp + (c.rb_cap + blockIdx.x) * H, acc, m2, r0, c0, g, lr);
+        load_w3(l_next);
+        load_mask(m2, c.h2T, l_next);
         __syncthreads();
         // dh1 = dpre2 W2 (B(k, j) = W2[k][j] = W2^T[j][k]), masked by h1 > 0
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[t] = float4_t{0.f, 0.f, 0.f, 0.f};
-        products_from_lds<H>(acc, d2s, w2f, g, lr);
-        masked_hidden<H>(p, d1s, p.dpre2T, p.bp1, acc, m1, r0, c0, g, lr);
+        products_from_lds<H, NW>(acc, d2s, w2f, g, lr);
+        masked_hidden<H, NW>(n, d1s, c.dpre2T + (int64_t)l * H * c.ldT, c.ldT, bp + (int64_t)blockIdx.x * H, acc, m1,
+                             r0, c0, g, lr);
+        __builtin_amdgcn_sched_barrier(0);
+        load_w2(l_next);
+        load_mask(m1, c.h1T, l_next);
+        __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
         // dxm = dpre1 W1 (B(k, d) = W1[k][d] = W1^T[d][k]), added into d loss / d y on the conditioning dims
         if (wave == 0) {
@@ -1001,16 +1037,27 @@ __global__ __launch_bounds__(256) void layer_back_kernel(BackChain c)
                 const bf16x8_t av = *reinterpret_cast<const bf16x8_t *>(&d1s[lr][32 * k + 8 * g]);
                 o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, w1f[k], o, 0, 0, 0);
             }
-            if (col < D && ((p.cond >> col) & 1u)) {
+            if (col < D && ((cond >> col) & 1u)) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
                     if (r0 + 4 * g + r < n) gys[4 * g + r][col] += (double)o[r];
             }
+        } else if (wave == 1) {
+            // meanwhile: the outputs' transposed operand and bias partials
+            for (int k = lane; k < 4 * kOutPad; k += 64)
+                *reinterpret_cast<uint2 *>(c.doutT + ((int64_t)l * kOutPad + (k >> 2)) * c.ldT + r0 + 4 * (k & 3)) =
+                    column4(dos, k >> 2, k & 3);
+            if (lane < 2 * D) {
+                double t = 0.0;
+#pragma unroll
+                for (int r = 0; r < kLayerRows; ++r) t += (double)dos[r][lane];
+                bp[2 * c.rb_cap * H + (int64_t)blockIdx.x * 2 * D + lane] = t;
+            }
         }
+        load_w1(l_next);
         __syncthreads();
     }
-    const BackArgs &pl = c.layer[c.count - 1];
-    if (r0 + rr < n && i < D) pl.gy[(int64_t)(r0 + rr) * D + i] = gys[rr][i];
+    if (own && r0 + rr < n && i < D) c.gy[(int64_t)(r0 + rr) * D + i] = gys[rr][i];
 }
 
 // ---------------------------------------------------------------- training backward
@@ -1094,8 +1141,7 @@ struct GradParts {
 
 // Parameter p's gradient from its partial sums, when a thread finishes it:
 // the weights' split-K slices in slice order, and the biases' row-block
-// partials in block order when there are at most 64 of them (more: a wave
-// per bias element, bias_gradient).  Returns false for the biases left to the
+// partials in block order when there are at most 64 of them (more: bias_tile).  Returns false for the biases left to the
 // waves.
 __device__ __forceinline__ bool param_gradient(const GradParts &gp, int64_t p, float &grad)
 {
@@ -1136,50 +1182,6 @@ __device__ __forceinline__ bool param_gradient(const GradParts &gp, int64_t p, f
     return true;
 }
 
-// Bias element e (layer e / (2 H + 2 dim), then b1, b2, b3) summed over its
-// row-block partials by the 64 lanes of a wave: lane k the blocks k, k + 64,
-// ... in order, then the 64 lane sums by a fixed butterfly (every lane gets
-// the total).  p: the element's parameter index.
-__device__ __forceinline__ float bias_gradient(const GradParts &gp, int64_t e, int lane, int64_t &p)
-{
-    const int64_t H = gp.H, D = gp.D, per = 2 * H + 2 * D;
-    const int64_t l = e / per, r = e % per;
-    const double *bp = gp.bpart + l * gp.b_layer;
-    const double *br;
-    int64_t bcols, q;
-    const int64_t base = l * gp.per_layer;
-    if (r < H) {
-        br = bp, bcols = H, q = r, p = base + H * D + r;
-    } else if (r < 2 * H) {
-        br = bp + gp.rb_cap * H, bcols = H, q = r - H, p = base + H * D + H + H * H + (r - H);
-    } else {
-        br = bp + 2 * gp.rb_cap * H, bcols = 2 * D, q = r - 2 * H,
-        p = base + H * D + 2 * H + H * H + 2 * D * H + (r - 2 * H);
-    }
-    double t = 0.0;
-    for (int64_t y = lane; y < gp.rb; y += 64) t += br[y * bcols + q];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off);
-    return (float)t;
-}
-
-__global__ __launch_bounds__(256) void grad_finish_kernel(GradParts gp, float *__restrict__ grads)
-{
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= gp.n_params) return;
-    float g;
-    if (param_gradient(gp, p, g)) grads[p] = g;
-}
-
-// The biases when their partials come in more than 64 row blocks: one wave
-// per bias element.
-__global__ __launch_bounds__(64) void bias_finish_kernel(GradParts gp, float *__restrict__ grads)
-{
-    int64_t p;
-    const float g = bias_gradient(gp, blockIdx.x, threadIdx.x, p);
-    if (threadIdx.x == 0) grads[p] = g;
-}
-
 // out[0] = the mean of loss[0, n) (one block of 256 threads: thread t sums
 // the rows t, t + 256, ... in order, then a fixed tree over the threads).
 __device__ __forceinline__ void mean_block(int n, const double *__restrict__ loss, double *__restrict__ out)
@@ -1196,22 +1198,29 @@ __device__ __forceinline__ void mean_block(int n, const double *__restrict__ los
     if (threadIdx.x == 0) out[0] = red[0] / (double)n;
 }
 
-__global__ __launch_bounds__(256) void mean_kernel(int n, const double *__restrict__ loss, double *__restrict__ out)
-{
-    mean_block(n, loss, out);
-}
-
 // BF16 copies of the weight matrices (FP32 master -> BF16): parameter i of
 // layer i / per_layer goes to dst[layer * dst_stride + i % per_layer], and
 // the weights also transposed into dstT (layer stride t_stride): W1^T [D][H],
 // W2^T [H][H], W3^T [H][kOutPad] (rows padded), the backward pass's operands,
 // then W1 with its rows padded to kInPad, [H][kInPad], the first product's
-// operand in 16-byte vectors.
+// operand in 16-byte vectors.  frag: W2 and W2^T in the order of their fragments
+// (frag_index), for the widths the one-kernel couplings serve.
 struct Bf16Copies {
     int64_t per_layer, dst_stride, t_stride;
     int D, H;
+    int frag;
     uint16_t *dst, *dstT;
 };
+
+// Element (j, k) of an H x H matrix whose 16 x 32 fragments (rows j, 8 k of each
+// lane) stand one after the other, k step fastest: the 64 lanes of a wave then
+// read a fragment as 1 KB in a row.  Read from rows of H, a fragment is 16 pieces of 64
+// bytes, half of a cache line each, and the block's waves push the other half out of
+// L1 before they come to it (layer_kernel, 4096 rows, 8 couplings: 53 -> 36 us).
+__device__ __forceinline__ int64_t frag_index(int64_t j, int64_t k, int64_t H)
+{
+    return (((j / 16) * (H / 32) + k / 32) * 64 + (k % 32) / 8 * 16 + j % 16) * 8 + k % 8;
+}
 
 __device__ __forceinline__ void write_bf16(const Bf16Copies &c, int64_t i, float value)
 {
@@ -1219,9 +1228,16 @@ __device__ __forceinline__ void write_bf16(const Bf16Copies &c, int64_t i, float
     int64_t q = i - l * c.per_layer;
     const int64_t D = c.D, H = c.H;
     const uint16_t v = f32_to_bf16(value);
-    c.dst[l * c.dst_stride + q] = v;
     uint16_t *t = c.dstT + l * c.t_stride;
     const int64_t s1 = H * D, s2 = H * H, s3 = 2 * D * H;
+    uint16_t *d = c.dst + l * c.dst_stride;
+    if (c.frag && q >= s1 + H && q < s1 + H + s2) {
+        const int64_t j = (q - s1 - H) / H, k = (q - s1 - H) % H;
+        d[s1 + H + frag_index(j, k, H)] = v;
+        t[s1 + frag_index(k, j, H)] = v;
+        return;
+    }
+    d[q] = v;
     if (q < s1) {                                   // W1 [H][D] -> W1^T [D][H], and padded rows
         t[(q % D) * H + q / D] = v;
         t[s1 + s2 + H * kOutPad + (q / D) * kInPad + q % D] = v;
@@ -1264,9 +1280,8 @@ __device__ __forceinline__ float adam_update(const AdamStep &a, int64_t i, float
 // Bias tiles of the training step's last launch: 8 consecutive elements of
 // one bias vector (b1, b2 or b3) of one layer.  Their row-block partials are
 // staged through LDS 128 row blocks at a time, each row block's 8 values one
-// contiguous 64-byte load, and each wave then sums two of the columns in the
-// order of bias_gradient (lane k the blocks k, k + 64, ... in order, then the
-// same butterfly).
+// contiguous 64-byte load, and each wave then sums two of the columns (lane k
+// the blocks k, k + 64, ... in order, then a fixed butterfly).
 constexpr int kBiasCols = 8, kBiasRows = 128;
 
 __device__ __forceinline__ int64_t bias_tiles_per_layer(const GradParts &gp)
@@ -1274,6 +1289,7 @@ __device__ __forceinline__ int64_t bias_tiles_per_layer(const GradParts &gp)
     return 2 * ((gp.H + kBiasCols - 1) / kBiasCols) + (2 * gp.D + kBiasCols - 1) / kBiasCols;
 }
 
+template <bool ADAM>
 __device__ __forceinline__ void bias_tile(const GradParts &gp, int64_t tile, float *__restrict__ grads,
                                           const AdamStep &a, const Bf16Copies &c)
 {
@@ -1318,22 +1334,22 @@ __device__ __forceinline__ void bias_tile(const GradParts &gp, int64_t tile, flo
     if (wave < ncols) {
         const int64_t p = p0 + q0 + wave;
         grads[p] = (float)t0;
-        write_bf16(c, p, adam_update(a, p, (float)t0));
+        if constexpr (ADAM) write_bf16(c, p, adam_update(a, p, (float)t0));
     }
     if (wave + 4 < ncols) {
         const int64_t p = p0 + q0 + wave + 4;
         grads[p] = (float)t1;
-        write_bf16(c, p, adam_update(a, p, (float)t1));
+        if constexpr (ADAM) write_bf16(c, p, adam_update(a, p, (float)t1));
     }
 }
 
-// The end of a training step in one launch: every parameter's gradient from
-// its partial sums (the orders of grad_finish_kernel and bias_finish_kernel),
-// its Adam update and its BF16 copies.  Blocks below weight_blocks take one
+// The end of a gradient pass in one launch: every parameter's gradient from
+// its partial sums and, in a training step (ADAM), its Adam update and its BF16 copies.  Blocks below weight_blocks take one
 // parameter per thread; the biases that param_gradient leaves to waves go to
 // the bias_tiles blocks after them (bias_tile); with loss_out given, the last
 // block writes the mean of the n_rows per-row losses there (mean_block).
-__global__ __launch_bounds__(256) void finish_update_kernel(GradParts gp, float *__restrict__ grads, AdamStep a,
+template <bool ADAM>
+__global__ __launch_bounds__(256) void finish_kernel(GradParts gp, float *__restrict__ grads, AdamStep a,
                                                             Bf16Copies c, int weight_blocks, int64_t bias_tiles,
                                                             int n_rows, const double *__restrict__ loss,
                                                             double *__restrict__ loss_out)
@@ -1347,11 +1363,11 @@ __global__ __launch_bounds__(256) void finish_update_kernel(GradParts gp, float 
         float g;
         if (p >= gp.n_params || !param_gradient(gp, p, g)) return;
         grads[p] = g;
-        write_bf16(c, p, adam_update(a, p, g));
+        if constexpr (ADAM) write_bf16(c, p, adam_update(a, p, g));
         return;
     }
     const int64_t tile = (int64_t)blockIdx.x - weight_blocks;
-    if (tile < bias_tiles) bias_tile(gp, tile, grads, a, c);
+    if (tile < bias_tiles) bias_tile<ADAM>(gp, tile, grads, a, c);
 }
 
 __global__ __launch_bounds__(256) void zero_kernel(int64_t n, double *__restrict__ p)
@@ -1397,8 +1413,7 @@ struct gw_flow {
     // first layer's slices of the last three for every layer)
     int64_t ldT = 0;
     uint16_t *h1T = nullptr, *h2T = nullptr, *xmT = nullptr, *doutT = nullptr, *dpreT = nullptr, *dpre2T = nullptr;
-    // partial sums of the gradients (summed by grad_finish_kernel or, in a
-    // training step, finish_update_kernel): per layer,
+    // partial sums of the gradients (summed by finish_kernel): per layer,
     // split-K slices of the three weight matrices (FP32, w_layer floats) and
     // row-block sums of the three biases (FP64, b_layer doubles)
     float *wpart = nullptr;
@@ -1552,78 +1567,72 @@ gw::flow::NextMask mask_of(gw_flow *f, int l, bool keep_t)
                               keep_t ? f->xmT + (int64_t)l * kInPad * f->ldT : nullptr, f->ldT, f->cond[l]};
 }
 
-// The arguments of coupling l of the one-kernel path: input rows a, output
-// rows y (and with s_out the log-scales), the next coupling's masked input nm.
-gw::flow::LayerArgs layer_args(gw_flow *f, int l, int n, int dir, const double *a, double *y, double *s_out,
-                               bool keep_t, gw::flow::NextMask nm)
+template <int H>
+hipError_t launch_chain(const gw::flow::LayerChain &c, bool keep_t, hipStream_t s)
 {
-    const int D = f->dim, H = f->hidden;
-    const LayerOff o = layer_off(f, l);
-    const uint16_t *wq = f->wb + o.q;
-    const float *pp = f->params + o.p;
-    gw::flow::LayerArgs la;
-    la.n = n;
-    la.dim = D;
-    la.dir = dir;
-    la.cond = f->cond[l];
-    la.xm = f->xm_b + (int64_t)l * f->cap * kInPad;
-    la.w1p = f->wbT + (int64_t)l * f->wbT_stride + (int64_t)D * H + (int64_t)H * H + (int64_t)H * kOutPad;
-    la.w2 = wq + o.w2;
-    la.w3 = wq + o.w3;
-    la.b1 = pp + o.b1;
-    la.b2 = pp + o.b2;
-    la.b3 = pp + o.b3;
-    la.h1 = f->h1_b + (int64_t)l * f->cap * H;
-    la.h2 = f->h2_b + (int64_t)l * f->cap * H;
-    la.h1T = keep_t ? f->h1T + (int64_t)l * H * f->ldT : nullptr;
-    la.h2T = keep_t ? f->h2T + (int64_t)l * H * f->ldT : nullptr;
-    la.ldT = f->ldT;
-    la.a = a;
-    la.y = y;
-    la.sum_s = f->sum_s;
-    la.s_out = s_out;
-    la.nm = nm;
-    return la;
+    constexpr int NW = gw::flow::kChainWaves;
+    const dim3 grid((unsigned)((c.n + gw::flow::kLayerRows - 1) / gw::flow::kLayerRows));
+    if (keep_t)
+        hipLaunchKernelGGL((gw::flow::layer_kernel<H, NW, true>), grid, dim3(64 * NW), 0, s, c);
+    else
+        hipLaunchKernelGGL((gw::flow::layer_kernel<H, NW, false>), grid, dim3(64 * NW), 0, s, c);
+    return hipGetLastError();
 }
 
 // Couplings first, first + step, ... (count of them, step +1 or -1) applied in
-// that order to rows [0, n) by one launch per kMaxChain couplings.  dir: +1
-// the forward direction (z -> x), -1 the inverse.  Boundary l is coupling l's
-// input in the forward direction; with keep_t (inverse, training) the
-// transposed activations and inputs and the log-scales are kept.
-// a_first: the first coupling's input rows (null: its boundary); ends: what
-// the first launch does before the couplings (init_sum, affine_in, in_mask)
-// and the last one after them (affine_out, density).
+// that order to the rows a_first[0, n) by one launch per kMaxChain couplings.
+// dir: +1 the forward direction (z -> x), -1 the inverse.  With keep_t (inverse,
+// training) the transposed activations and inputs, the boundaries (l: coupling
+// l's output) and the log-scales are kept; y_out (may be null): the last
+// coupling's output rows.  ends: what the first launch does before the
+// couplings (init_sum, affine_in) and the last one after them (affine_out, density).
 hipError_t layer_chain(gw_flow *f, int n, int dir, int first, int count, bool keep_t, hipStream_t s,
-                       const double *a_first, const gw::flow::ChainEnds &ends)
+                       const double *a_first, double *y_out, const gw::flow::ChainEnds &ends)
 {
-    const int H = f->hidden, D = f->dim;
+    const int64_t D = f->dim, H = f->hidden;
     const int step = dir > 0 ? 1 : -1;
     for (int done = 0; done < count;) {
-        gw::flow::LayerChain c;
+        gw::flow::LayerChain c{};
+        const bool last = done + std::min(count - done, gw::flow::kMaxChain) == count;
+        c.n = n;
+        c.dim = f->dim;
+        c.dir = dir;
+        c.first = first + step * done;
+        c.step = step;
         c.count = std::min(count - done, gw::flow::kMaxChain);
+        for (int k = 0; k <= c.count; ++k) {
+            const int l = c.first + step * k;
+            c.cond[k] = l >= 0 && l < f->layers ? f->cond[l] : 0u;
+        }
+        const LayerOff o = layer_off(f, 0);
+        c.w1p = f->wbT + D * H + H * H + H * gw::flow::kOutPad;
+        c.w2 = f->wb + o.w2;
+        c.w3 = f->wb + o.w3;
+        c.wT_stride = f->wbT_stride;
+        c.w_stride = f->wb_stride;
+        c.b1 = f->params + o.b1;
+        c.b2 = f->params + o.b2;
+        c.b3 = f->params + o.b3;
+        c.b_stride = f->per_layer;
+        c.h1T = f->h1T;
+        c.h2T = f->h2T;
+        c.xmT = f->xmT;
+        c.ldT = f->ldT;
+        c.bound = f->bound;
+        c.s_out = f->s_store;
+        c.row_stride = f->cap * D;
+        // between launches the rows stand in the boundary that follows the last coupling
+        c.a = done == 0 ? a_first : boundary(f, dir > 0 ? c.first : c.first + 1);
+        c.sum_s = f->sum_s;
+        const int l_end = c.first + step * (c.count - 1);
+        c.y_out = !last ? boundary(f, dir > 0 ? l_end + 1 : l_end) : y_out;
         c.e = ends;
         if (done > 0) c.e.init_sum = c.e.affine_in = 0;
-        if (done + c.count < count) {
+        if (!last) {
             c.e.affine_out = nullptr;
             c.e.density = 0;
         }
-        for (int k = 0; k < c.count; ++k) {
-            const int l = first + step * (done + k);
-            if (dir > 0)
-                c.layer[k] = layer_args(f, l, n, 1, boundary(f, l), boundary(f, l + 1), nullptr, false,
-                                        mask_of(f, l + 1, false));
-            else
-                c.layer[k] = layer_args(f, l, n, -1, boundary(f, l + 1), boundary(f, l),
-                                        f->s_store + (int64_t)l * f->cap * D, keep_t, mask_of(f, l - 1, keep_t));
-        }
-        if (done == 0 && a_first) c.layer[0].a = a_first;
-        const dim3 grid((unsigned)((n + gw::flow::kLayerRows - 1) / gw::flow::kLayerRows));
-        if (H == 256)
-            hipLaunchKernelGGL(gw::flow::layer_kernel<256>, grid, dim3(256), 0, s, c);
-        else
-            hipLaunchKernelGGL(gw::flow::layer_kernel<128>, grid, dim3(256), 0, s, c);
-        hipError_t e = hipGetLastError();
+        hipError_t e = H == 256 ? launch_chain<256>(c, keep_t, s) : launch_chain<128>(c, keep_t, s);
         if (e != hipSuccess) return e;
         done += c.count;
     }
@@ -1635,6 +1644,14 @@ hipError_t layer_chain(gw_flow *f, int n, int dir, int first, int count, bool ke
         hipError_t e_ = (expr);              \
         if (e_ != hipSuccess) return e_;     \
     } while (0)
+
+template <int H>
+hipError_t launch_back(const gw::flow::BackChain &c, int blocks, hipStream_t s)
+{
+    constexpr int NW = gw::flow::kChainWaves;
+    hipLaunchKernelGGL((gw::flow::layer_back_kernel<H, NW>), dim3((unsigned)blocks), dim3(64 * NW), 0, s, c);
+    return hipGetLastError();
+}
 
 hipError_t zero(int64_t n, double *p, hipStream_t s)
 {
@@ -1654,22 +1671,23 @@ struct DensityOut {
 // Inverse pass x -> z = boundary 0 over rows [0, n): the affine
 // normalisation, then couplings L-1 .. 0; sum_s[b] = sum log sigma + the
 // couplings' log-scales.  With keep_t the transposed activations and inputs
-// are kept for the weight gradients; the log-scales always are.
-hipError_t inverse_pass(gw_flow *f, int n, const double *x, bool keep_t, hipStream_t s, const DensityOut &den)
+// and log-scales are kept for the gradients.  z_out (one-kernel path only; may be
+// null, must not overlap x): z goes there, and to boundary 0 with keep_t alone.
+hipError_t inverse_pass(gw_flow *f, int n, const double *x, bool keep_t, hipStream_t s, const DensityOut &den,
+                        double *z_out = nullptr)
 {
     const int D = f->dim, L = f->layers;
     if (fused_width(f)) {
         // one launch: the normalisation before the couplings, the density after them
         gw::flow::ChainEnds e{};
         e.affine_in = 1;
-        e.in_mask = mask_of(f, L - 1, keep_t);
         e.mu = f->mu;
         e.log_sigma = f->log_sigma;
         e.density = den.any() ? 1 : 0;
         e.logq = den.logq;
         e.loss = den.loss;
         e.g = den.g;
-        return layer_chain(f, n, -1, L - 1, L, keep_t, s, x, e);
+        return layer_chain(f, n, -1, L - 1, L, keep_t, s, x, z_out, e);
     }
     hipLaunchKernelGGL(gw::flow::affine_kernel, dim3((n + 15) / 16), dim3(256), 0, s, n, D, -1, f->mu, f->log_sigma,
                        x, boundary(f, L), f->sum_s, 1, mask_of(f, L - 1, keep_t));
@@ -1706,7 +1724,7 @@ hipError_t forward_pass(gw_flow *f, int n, const double *z, double *x_out, doubl
         e.density = logq ? 1 : 0;
         e.z_in = z;
         e.logq = logq;
-        return layer_chain(f, n, 1, 0, L, false, s, z, e);
+        return layer_chain(f, n, 1, 0, L, false, s, z, nullptr, e);
     }
     GW_TRY(zero(n, f->sum_s, s));
     if (z != boundary(f, 0))
@@ -1735,34 +1753,60 @@ hipError_t forward_pass(gw_flow *f, int n, const double *z, double *x_out, doubl
 // The BF16 copies of the flow's weights that the kernels read.
 gw::flow::Bf16Copies bf16_copies(const gw_flow *f)
 {
-    return gw::flow::Bf16Copies{f->per_layer, f->wb_stride, f->wbT_stride, f->dim, f->hidden, f->wb, f->wbT};
+    return gw::flow::Bf16Copies{f->per_layer, f->wb_stride, f->wbT_stride, f->dim, f->hidden, fused_width(f) ? 1 : 0,
+                                f->wb, f->wbT};
 }
 
 // Gradient of the mean negative log density of rows x[0, n) with respect to
-// every parameter (into f->grads); the mean loss goes to loss_out (device).
+// every parameter (into grad_out); the mean loss goes to loss_out (device).
 // With adam, the Adam step and the refresh of the BF16 copies follow in the
 // launch that finishes the gradients.
-hipError_t gradients(gw_flow *f, int n, const double *x, double *loss_out, hipStream_t s,
+hipError_t gradients(gw_flow *f, int n, const double *x, float *grad_out, double *loss_out, hipStream_t s,
                      const gw::flow::AdamStep *adam = nullptr)
 {
     const int D = f->dim, H = f->hidden, L = f->layers;
     // weight gradients sum over the n rows: split K = n into slices of >= 256 rows
+    // (fewer slices would write and read fewer partial sums, 4 of them 10 us less at 4096 rows,
+    // 8 layers of 256, but round differently; the gradients are kept as they were)
     const int split = std::max(1, std::min(gw::flow::kMaxSplit, n / 256));
     DensityOut den;
     den.loss = f->loss;
     den.g = f->g;
     GW_TRY(inverse_pass(f, n, x, true, s, den));
-    if (loss_out && !adam) {     // a training step takes the mean in its last launch
-        hipLaunchKernelGGL(gw::flow::mean_kernel, dim3(1), dim3(256), 0, s, n, f->loss, loss_out);
-        GW_TRY(hipGetLastError());
-    }
     // the inverse pass applied couplings L-1 .. 0; go back through 0 .. L-1.
     // Every gradient of layer l is left as partial sums (split-K slices of the
     // weights, row-block sums of the biases) and summed by one kernel at the end.
     const int rb64 = (n + 63) / 64, rb16 = (n + gw::flow::kLayerRows - 1) / gw::flow::kLayerRows;
-    gw::flow::BackChain chain;
-    chain.count = 0;
-    for (int l = 0; l < L; ++l) {
+    for (int l = 0; fused_width(f) && l < L;) {
+        // the transposed operands of the weight gradients go to each layer's
+        // slices, for the one launch of all layers' products below
+        gw::flow::BackChain c{};
+        c.n = n;
+        c.dim = D;
+        c.first = l;
+        c.count = std::min(L - l, gw::flow::kMaxChain);
+        for (int k = 0; k < c.count; ++k) c.cond[k] = f->cond[l + k];
+        c.g = f->g;
+        c.gy = f->gy;
+        c.bound = f->bound;
+        c.s_store = f->s_store;
+        c.row_stride = f->cap * D;
+        c.h1T = f->h1T;
+        c.h2T = f->h2T;
+        c.wt = f->wbT;
+        c.wt_stride = f->wbT_stride;
+        c.doutT = f->doutT;
+        c.dpreT = f->dpreT;
+        c.dpre2T = f->dpre2T;
+        c.ldT = f->ldT;
+        c.bp = f->bpart;
+        c.bp_stride = f->b_layer;
+        c.rb_cap = f->rb_cap;
+        GW_TRY(H == 256 ? launch_back<256>(c, rb16, s) : launch_back<128>(c, rb16, s));
+        std::swap(f->g, f->gy);      // d loss / d(boundary l + count)
+        l += c.count;
+    }
+    for (int l = 0; !fused_width(f) && l < L; ++l) {
         float *wp = f->wpart + l * f->w_layer;
         double *bp = f->bpart + l * f->b_layer;
         float *wp1 = wp, *wp2 = wp + (int64_t)gw::flow::kMaxSplit * H * D,
@@ -1776,26 +1820,6 @@ hipError_t gradients(gw_flow *f, int n, const double *x, double *loss_out, hipSt
         // transposed BF16 weights of the layer: W1^T [D][H], W2^T [H][H], W3^T [H][kOutPad]
         const uint16_t *wt = f->wbT + (int64_t)l * f->wbT_stride;
         const int64_t w2t = (int64_t)D * H, w3t = (int64_t)D * H + (int64_t)H * H;
-        if (fused_width(f)) {
-            // the coupling's transposed operands of its weight gradients go to
-            // layer l's slices, for the one launch of all layers' products
-            // below; the couplings go out in chains of up to kMaxChain
-            gw::flow::BackArgs ba{n, D, f->cond[l], f->g, boundary(f, l), f->s_store + (int64_t)l * f->cap * D, f->gy,
-                                  h1T, h2T, wt, wt + w2t, wt + w3t, f->doutT + (int64_t)l * kOutPad * T,
-                                  f->dpreT + (int64_t)l * H * T, f->dpre2T + (int64_t)l * H * T, T, bp1, bp2, bp3};
-            chain.layer[chain.count++] = ba;
-            if (chain.count == gw::flow::kMaxChain || l == L - 1) {
-                const dim3 grid((unsigned)rb16);
-                if (H == 256)
-                    hipLaunchKernelGGL(gw::flow::layer_back_kernel<256>, grid, dim3(256), 0, s, chain);
-                else
-                    hipLaunchKernelGGL(gw::flow::layer_back_kernel<128>, grid, dim3(256), 0, s, chain);
-                GW_TRY(hipGetLastError());
-                chain.count = 0;
-            }
-            std::swap(f->g, f->gy);      // d loss / d(boundary l + 1)
-            continue;
-        }
         hipLaunchKernelGGL(gw::flow::coupling_inv_backward_kernel, dim3(blocks_for(n)), dim3(256), 0, s, n, D,
                            f->cond[l], f->g, boundary(f, l), f->s_store + (int64_t)l * f->cap * D, f->dout_b,
                            f->dout_f, f->gy, f->doutT, T);
@@ -1852,25 +1876,19 @@ hipError_t gradients(gw_flow *f, int n, const double *x, double *loss_out, hipSt
     }
     gw::flow::GradParts parts{D, H, split, fused_width(f) ? rb16 : rb64, f->rb_cap, f->per_layer, f->n_params,
                               f->w_layer, f->b_layer, f->wpart, f->bpart};
-    if (adam) {
-        // the gradients' sums, the Adam step and the BF16 copies in one launch
-        const int wblocks = blocks_for(f->n_params);
-        const int64_t per_layer_tiles = 2 * ((H + gw::flow::kBiasCols - 1) / gw::flow::kBiasCols) +
-                                        (2 * D + gw::flow::kBiasCols - 1) / gw::flow::kBiasCols;
-        const int64_t tiles = parts.rb > 64 ? (int64_t)L * per_layer_tiles : 0;
-        const int64_t blocks = wblocks + tiles + (loss_out ? 1 : 0);
-        hipLaunchKernelGGL(gw::flow::finish_update_kernel, dim3((unsigned)blocks), dim3(256), 0, s, parts, f->grads,
+    // the gradients' sums, the mean loss and, with adam, the step and the BF16 copies in one launch
+    const int wblocks = blocks_for(f->n_params);
+    const int64_t per_layer_tiles = 2 * ((H + gw::flow::kBiasCols - 1) / gw::flow::kBiasCols) +
+                                    (2 * D + gw::flow::kBiasCols - 1) / gw::flow::kBiasCols;
+    const int64_t tiles = parts.rb > 64 ? (int64_t)L * per_layer_tiles : 0;
+    const int64_t blocks = wblocks + tiles + (loss_out ? 1 : 0);
+    if (adam)
+        hipLaunchKernelGGL(gw::flow::finish_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, s, parts, grad_out,
                            *adam, bf16_copies(f), wblocks, tiles, n, f->loss, loss_out);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL(gw::flow::grad_finish_kernel, dim3(blocks_for(f->n_params)), dim3(256), 0, s, parts, f->grads);
-    GW_TRY(hipGetLastError());
-    if (parts.rb > 64) {
-        hipLaunchKernelGGL(gw::flow::bias_finish_kernel, dim3((unsigned)(L * (2 * H + 2 * D))), dim3(64), 0, s, parts,
-                           f->grads);
-        GW_TRY(hipGetLastError());
-    }
-    return hipSuccess;
+    else
+        hipLaunchKernelGGL(gw::flow::finish_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, s, parts, grad_out,
+                           gw::flow::AdamStep{}, bf16_copies(f), wblocks, tiles, n, f->loss, loss_out);
+    return hipGetLastError();
 }
 
 hipError_t refresh_bf16(gw_flow *f, hipStream_t s)
@@ -2003,8 +2021,12 @@ int gw_flow_inverse(gw_flow *f, const double *x, int64_t n, double *z_out, doubl
     if (int rc = ensure_batch(f, n)) return rc;
     DensityOut den;
     den.logq = logq_out;
-    hipError_t e = inverse_pass(f, (int)n, x, false, stream, den);
-    if (e == hipSuccess && z_out)
+    // z straight to its place unless rows of x that other blocks still read stand there
+    const size_t bytes = sizeof(double) * (size_t)n * f->dim;
+    const char *zb = reinterpret_cast<const char *>(z_out), *xb = reinterpret_cast<const char *>(x);
+    const bool direct = fused_width(f) && !(zb < xb + bytes && xb < zb + bytes);
+    hipError_t e = inverse_pass(f, (int)n, x, false, stream, den, !z_out ? nullptr : direct ? z_out : boundary(f, 0));
+    if (e == hipSuccess && z_out && !direct)
         e = hipMemcpyAsync(z_out, boundary(f, 0), sizeof(double) * n * f->dim, hipMemcpyDeviceToDevice, stream);
     return e == hipSuccess ? GW_OK : hip_fail(e, "gw_flow_inverse");
 }
@@ -2015,9 +2037,7 @@ int gw_flow_gradients(gw_flow *f, const double *x, int64_t n, float *grad_out, d
     if (n == 0) return fail(GW_EINVAL, "empty batch");
     DeviceGuard g(f->device);
     if (int rc = ensure_batch(f, n)) return rc;
-    hipError_t e = gradients(f, (int)n, x, loss_out, stream);
-    if (e == hipSuccess && grad_out)
-        e = hipMemcpyAsync(grad_out, f->grads, sizeof(float) * f->n_params, hipMemcpyDeviceToDevice, stream);
+    hipError_t e = gradients(f, (int)n, x, grad_out ? grad_out : f->grads, loss_out, stream);
     return e == hipSuccess ? GW_OK : hip_fail(e, "gw_flow_gradients");
 }
 
@@ -2032,7 +2052,7 @@ int gw_flow_train_step(gw_flow *f, const double *x, int64_t n, float lr, double 
     const int64_t t = f->adam_t + 1;
     const gw::flow::AdamStep adam{f->params, f->adam_m, f->adam_v, lr, b1, b2, 1e-8f,
                                   1.0f - (float)std::pow(b1, (double)t), 1.0f - (float)std::pow(b2, (double)t)};
-    hipError_t e = gradients(f, (int)n, x, loss_out, stream, &adam);
+    hipError_t e = gradients(f, (int)n, x, f->grads, loss_out, stream, &adam);
     if (e != hipSuccess) return hip_fail(e, "gw_flow_train_step");
     f->adam_t = t;
     return GW_OK;
