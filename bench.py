@@ -306,11 +306,6 @@ def bench_ragged(args):
     if not torch.isfinite(out).all():
         raise SystemExit("non-finite lnL in the ragged batch")
     pairs = sum(c * e.grid.n_bins for c, e in zip(counts, evs))
-    flops = flops_per_pair(3, prec == "mixed") * pairs
-    # the ragged kernel runs the tile kernel's per-tile loop, so the flops the
-    # counters saw that loop execute per pair price this pass too
-    per_pair = executed_flops_per_pair(prec)
-    executed = per_pair * pairs if per_pair is not None else None
     result = {
         "metric": "lnL evals/s (256 ragged BNS events, 3 det, 512 proposals each)",
         "value": rows / rag_s, "unit": "lnL evals/s", "n_gpus": 1, "steps": steps, "warmup": 2,
@@ -320,16 +315,10 @@ def bench_ragged(args):
                    "sample_bin_pairs": pairs, "precision": prec, "tile_bins": tuning[0], "chunk_bins": tuning[1]},
         "separate_launches": {"value": rows / sep_s, "ms_per_step": sep_s * 1e3},
         "speedup_vs_separate": sep_s / rag_s,
-        "roofline": {"bound": "alu", "achieved": executed / rag_s / 1e12 if executed else None,
-                     "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
-                     "frac": executed / rag_s / 1e12 / FP64_PEAK_TFLOPS if executed else None, "traffic": None,
-                     "kernel": "whole ragged pass (graph)",
-                     "flops_source": ("executed FP64 flops per (sample, bin) of the same tile loop, from the counters "
-                                      "in " + PROFILE_SUMMARY if executed
-                                      else "no counter summary of these kernel sources"),
-                     "executed_flops_per_pair": per_pair,
-                     "frac_tally": flops / rag_s / 1e12 / FP64_PEAK_TFLOPS,
-                     "flops_per_pair_tally": flops_per_pair(3, prec == "mixed")},
+        # the pass sums over frequency nodes, whose number the device decides: no flop count of its own
+        "roofline": {"bound": "alu", "achieved": None, "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": None,
+                     "traffic": None, "kernel": "whole ragged pass (graph)",
+                     "flops_source": "the pass sums over frequency nodes; no counter summary of its kernels"},
     }
     if not args.no_cpu_baseline:
         import oracle

@@ -238,17 +238,20 @@ inline int64_t node_stat_entries(int64_t n_samples) { return (n_samples + 63) / 
 
 // A ragged call takes the nodes when its events together have that much work and
 // one of them is that long.  64 neutron-star events of 8 to 256 s, 512 rows each: 8.50 ms summing
-// every bin, 0.95 ms on nodes (0.37 of it the weighting, 0.48 the sums).
+// every bin, 0.91 ms on nodes (0.37 of it the weighting, 0.46 the sums).
 // Its events are cut into items of at least kRaggedUnits bins and nodes each,
-// kRaggedItems items per resident block where there is that much work.
-constexpr int kRaggedUnits = 64, kRaggedItems = 8;
+// kRaggedItems items per resident block where there is that much work: an item
+// costs a block about 5 us beside its sums, and fewer leave the last ones uneven (2, 3,
+// 4, 8, 16 items a block: 485, 461, 462, 483, 526 us).
+constexpr int kRaggedUnits = 64, kRaggedItems = 4;
 // Blocks of the weighting of one event of a ragged call (about four chunks each),
-// and of the node sums (the first takes the event sums).
+// and of the node sums (the first takes the event sums; with a quarter of the others
+// they took 64 us instead of 45).
 inline int ragged_spread_blocks(int64_t n_bins) { return (int)((n_bins + 4 * kSpreadBins - 1) / (4 * kSpreadBins)); }
 inline int ragged_combine_blocks(int64_t n_bins)
 {
-    const int64_t b = (n_bins + 8191) / 8192;
-    return 1 + (int)(b < 64 ? b : 64);
+    const int64_t b = (n_bins + 2047) / 2048;
+    return 1 + (int)(b < 256 ? b : 256);
 }
 // The most chunks an event of a ragged call of n_groups sample groups is cut
 // into (the chunks' partial sums take 64 MB or less over the call).
