@@ -279,8 +279,10 @@ typedef struct {
  * preparation, the persistent kernel per detector count, final reduction) is
  * captured once in a HIP graph and replayed while the events, pointers and
  * precision stay the same; any other call on the workspace, or a change of
- * those, rebuilds it (waiting for `stream`).  Events with n_samples == 0 are
- * skipped.
+ * those, rebuilds it (waiting for `stream`).  On a pinned workspace (one that a
+ * call was captured from) every call builds and launches its pass anew, since
+ * the captured graph's replays may have written over it.  Events with
+ * n_samples == 0 are skipped.
  *   events          host [n_events].
  *   data_packed     device complex, event e at data_offset_e, [n_det_e][n_bins_e].
  *   psd_packed      device doubles, same offsets as data_packed.

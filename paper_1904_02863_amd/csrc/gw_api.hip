@@ -890,8 +890,11 @@ int ragged_run(gw_workspace *ws, int n_events, const gw_event *events, const std
     const int na = (int)active.size();
     const gw_event *ev = active.data();
 
+    // On a pinned workspace nothing in the arena outlives a call: replays of the graph that
+    // pinned it write their sections over the events, the maps and the bin tables
+    // without this library seeing it.
     std::vector<unsigned char> key = ragged_key(na, ev, data, psd, theta, n_param, lnl, mixed, flags);
-    if (ws->ragged_exec && key == ws->ragged_key) {
+    if (ws->ragged_exec && !ws->pinned && key == ws->ragged_key) {
         hipError_t e = hipGraphLaunch(ws->ragged_exec, stream);
         return e == hipSuccess ? GW_OK : hip_fail(e, "hipGraphLaunch");
     }
@@ -940,6 +943,10 @@ int ragged_run(gw_workspace *ws, int n_events, const gw_event *events, const std
         return rc;
     hipError_t e = hipStreamSynchronize(ws->capture_stream);
     if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
+    if (ws->pinned) {
+        e = gw::launch_ragged(plan.launch, stream);
+        return e == hipSuccess ? GW_OK : hip_fail(e, "ragged pass");
+    }
 
     // capture the pass on the workspace's stream, replay it on the caller's
     e = hipStreamBeginCapture(ws->capture_stream, hipStreamCaptureModeThreadLocal);
