@@ -236,7 +236,8 @@ int gw_lnl_batch(gw_workspace *ws, const gw_grid *grid, int n_det, const gw_dete
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * Arguments, results and kernels are those of gw_lnl_batch; it always runs
  * the default plan, so its values equal bit for bit those of gw_lnl_batch on
- * a workspace with plan autotuning off (gw_workspace_set_tuning), and those
+ * a workspace with plan autotuning off (gw_workspace_set_tuning) that holds or
+ * may grow to gw_lnl_batch_static_bytes, and those
  * of a tuned plan to the rounding of FP64 sums taken in another order.  Its
  * intermediate buffers live in one static device array of
  * GW_STATIC_SCRATCH_BYTES per GPU, which the library holds on every GPU it

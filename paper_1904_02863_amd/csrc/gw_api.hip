@@ -7,6 +7,7 @@
 #include <chrono>
 #include <cmath>
 #include <cstddef>
+#include <cstdint>
 #include <cstdio>
 #include <cstring>
 #include <map>
@@ -300,16 +301,25 @@ LnlLayout lnl_layout_as(int64_t n_bins, int n_det, int64_t n_samples, const gw::
 // nodes), and enough work (kNodeMinWork).  The nodes' sections must not
 // push a call out of the static array that fits it without them, and
 // gw_lnl_batch and gw_lnl_batch_static run the same kernels on the same call,
-// so the rule is the same for both.
-LnlLayout lnl_layout(int64_t n_bins, int n_det, int64_t n_samples, const gw::TilePlan &plan, unsigned flags, int n_cu)
+// so that rule is the same for both.  Nor must they push it out of `room`, the
+// bytes of a workspace that cannot grow.
+LnlLayout lnl_layout(int64_t n_bins, int n_det, int64_t n_samples, const gw::TilePlan &plan, unsigned flags, int n_cu,
+                     size_t room = SIZE_MAX)
 {
     const LnlLayout plain = lnl_layout_as(n_bins, n_det, n_samples, plan, flags, n_cu, false);
     if (gw::tile_form(flags) != gw::kFormSplit || n_bins < gw::kNodeMinBins || n_bins > 0x7fffffffLL ||
         (double)n_bins * (double)plan.n_groups < (double)gw::kNodeMinWork)
         return plain;
     const LnlLayout nodes = lnl_layout_as(n_bins, n_det, n_samples, plan, flags, n_cu, true);
-    const bool leaves_array = plain.total <= kStaticScratchBytes && nodes.total > kStaticScratchBytes;
-    return leaves_array ? plain : nodes;
+    for (const size_t limit : {kStaticScratchBytes, room})
+        if (plain.total <= limit && nodes.total > limit) return plain;
+    return nodes;
+}
+
+// Bytes a call on `stream` may lay out on the workspace: what it has when a capture forbids growing it.
+size_t workspace_room(const gw_workspace *ws, hipStream_t stream)
+{
+    return ws->pinned || capturing(stream) ? ws->capacity : SIZE_MAX;
 }
 
 template <typename T>
@@ -549,7 +559,7 @@ int lnl_one_event(gw_workspace *ws, const gw_grid &grid, int n_det, const gw::De
             return rc;
     }
     const gw::TilePlan plan = plan_tiles(ws, grid.n_bins, n_det, n_samples, mixed, form);
-    const LnlLayout l = lnl_layout(grid.n_bins, n_det, n_samples, plan, flags, ws->n_cu);
+    const LnlLayout l = lnl_layout(grid.n_bins, n_det, n_samples, plan, flags, ws->n_cu, workspace_room(ws, stream));
     if (int rc = ensure_capacity(ws, l.total, stream)) return rc;
     return lnl_enqueue(ws, static_cast<char *>(ws->base), l, plan, grid, n_det, geom, data, psd, theta, n_param,
                        n_samples, lnl_out, mixed, flags, ws->n_cu, stream);
@@ -638,11 +648,10 @@ int64_t ragged_pairs(int n_events, const gw_event *events)
 // fills the host arrays; device pointers are relative to `base`.
 RaggedPlan ragged_plan(gw_workspace *ws, int n_events, const gw_event *events, const gw_c128 *data,
                        const double *psd, const double *theta, int n_param, double *lnl, bool mixed, unsigned flags,
-                       int tile_bins, int64_t chunk_bins, char *base)
+                       bool nodes, int tile_bins, int64_t chunk_bins, char *base)
 {
     const bool direct = (flags & GW_FLAG_DIRECT) != 0, isco = (flags & GW_FLAG_TERM_ISCO) != 0;
     const int form = gw::tile_form(flags);
-    const bool nodes = ragged_nodes(n_events, events, flags);
     RaggedPlan p;
     Carver c;
     p.events.resize(n_events);
@@ -789,17 +798,17 @@ RaggedPlan ragged_plan(gw_workspace *ws, int n_events, const gw_event *events, c
 // in use by earlier work there).
 int ragged_materialise(gw_workspace *ws, int n_events, const gw_event *events, const std::vector<gw::DetGeom> &geoms,
                        const gw_c128 *data, const double *psd, const double *theta, int n_param, double *lnl,
-                       bool mixed, unsigned flags, int tile_bins, int64_t chunk_bins, hipStream_t stream,
+                       bool mixed, unsigned flags, bool nodes, int tile_bins, int64_t chunk_bins, hipStream_t stream,
                        RaggedPlan *out)
 {
     hipError_t e = hipStreamSynchronize(stream);
     if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-    RaggedPlan sizing = ragged_plan(ws, n_events, events, data, psd, theta, n_param, lnl, mixed, flags, tile_bins,
-                                    chunk_bins, nullptr);
+    RaggedPlan sizing = ragged_plan(ws, n_events, events, data, psd, theta, n_param, lnl, mixed, flags, nodes,
+                                    tile_bins, chunk_bins, nullptr);
     if (int rc = ensure_capacity(ws, sizing.total, stream)) return rc;
     ws->tables_valid = false;            // the ragged layout overwrites the arena
-    *out = ragged_plan(ws, n_events, events, data, psd, theta, n_param, lnl, mixed, flags, tile_bins, chunk_bins,
-                       static_cast<char *>(ws->base));
+    *out = ragged_plan(ws, n_events, events, data, psd, theta, n_param, lnl, mixed, flags, nodes, tile_bins,
+                       chunk_bins, static_cast<char *>(ws->base));
     char *base = static_cast<char *>(ws->base);
     struct Copy { size_t off; const void *src; size_t bytes; };
     const Copy copies[] = {
@@ -907,12 +916,16 @@ int ragged_run(gw_workspace *ws, int n_events, const gw_event *events, const std
     // tile shape: autotuned once per (detectors, precision and form, size bucket)
     const int64_t pairs = ragged_pairs(na, ev);
     const int bucket = pairs > 0 ? (int)std::floor(std::log2((double)pairs)) : 0;
-    const auto tkey = std::make_tuple(max_det, (mixed ? 1 : 0) + 2 * form + (ragged_nodes(na, ev, flags) ? 2 * gw::kForms : 0), bucket);
+    // nodes, unless their sections alone (whose size no tile shape changes) leave a workspace that cannot grow
+    const bool on_nodes =
+        ragged_nodes(na, ev, flags) &&
+        (!ws->pinned || ragged_plan(ws, na, ev, data, psd, theta, n_param, lnl, mixed, flags, true, kTuneTiles[0],
+                                    kTuneChunks[0], nullptr).total <= ws->capacity);
+    const auto tkey = std::make_tuple(max_det, (mixed ? 1 : 0) + 2 * form + (on_nodes ? 2 * gw::kForms : 0), bucket);
     auto it = ws->ragged_tuning.find(tkey);
     int tile_bins = 0;
     int64_t chunk_bins = 0;
     RaggedPlan plan;
-    const bool on_nodes = ragged_nodes(na, ev, flags);
     if (it == ws->ragged_tuning.end()) {
         float best = 0.0f;
         for (int tb : kTuneTiles) {
@@ -920,7 +933,7 @@ int ragged_run(gw_workspace *ws, int n_events, const gw_event *events, const std
             for (int64_t cb : kTuneChunks) {
                 if (on_nodes && cb != kTuneChunks[0]) break;     // the device sizes the items
                 if (int rc = ragged_materialise(ws, na, ev, active_geoms, data, psd, theta, n_param, lnl, mixed, flags,
-                                                tb, cb, ws->capture_stream, &plan))
+                                                on_nodes, tb, cb, ws->capture_stream, &plan))
                     return rc;
                 float ms = 0.0f;
                 if (int rc = time_ragged(ws, plan, &ms)) return rc;
@@ -939,7 +952,7 @@ int ragged_run(gw_workspace *ws, int n_events, const gw_event *events, const std
     ws->last_tile_bins = tile_bins;
     ws->last_chunk_bins = chunk_bins;
     if (int rc = ragged_materialise(ws, na, ev, active_geoms, data, psd, theta, n_param, lnl, mixed, flags,
-                                    tile_bins, chunk_bins, stream, &plan))
+                                    on_nodes, tile_bins, chunk_bins, stream, &plan))
         return rc;
     hipError_t e = hipStreamSynchronize(ws->capture_stream);
     if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
