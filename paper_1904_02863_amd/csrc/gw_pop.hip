@@ -203,9 +203,11 @@ struct ExpTable {
     double hi[256], lo[256];
 };
 
-// Entry j as the product of its bits' factors in two doubles each.
+// Entry j as the product of its bits' factors in two doubles each.  Without contraction:
+// p fused into the sum that follows it would enter its own rounding error twice.
 __device__ __forceinline__ void fill_exp_table(ExpTable &t, int j)
 {
+#pragma clang fp contract(off)
     constexpr double fh[8] = {1.0027112750502025, 1.0054299011128027, 1.0108892860517005, 1.0218971486541166,
                               1.0442737824274138, 1.0905077326652577, 1.189207115002721, 1.4142135623730951};
     constexpr double fl[8] = {-3.636615928692264e-17, 9.499186535455032e-17, -1.5234778603368577e-17,
@@ -249,10 +251,14 @@ __device__ __forceinline__ Steps split_steps(double x, double most)
     return s;
 }
 
-// (e^r - 1) / r, its Taylor polynomial of degree 3 (next term of the exponential below 4e-17).
+// (e^r - 1) / r by its Taylor polynomial: of degree 3 where 1 is added to it (the
+// exponential's next term is below 4e-17), of degree 4 where it stands alone (next
+// term below 1e-17 of it).
+template <int DEGREE>
 __device__ __forceinline__ double step_poly(double r)
 {
-    double p = __builtin_fma(r, 1.0 / 24.0, 1.0 / 6.0);
+    double p = DEGREE == 4 ? __builtin_fma(r, 1.0 / 120.0, 1.0 / 24.0) : 1.0 / 24.0;
+    p = __builtin_fma(p, r, 1.0 / 6.0);
     p = __builtin_fma(p, r, 0.5);
     return __builtin_fma(p, r, 1.0);
 }
@@ -262,17 +268,19 @@ __device__ __forceinline__ double table_exp(double x, const ExpTable &t)
 {
     const Steps s = split_steps(x, 710.0);
     const double h = t.hi[s.k & 255];
-    return __builtin_ldexp(__builtin_fma(h * s.r, step_poly(s.r), h), s.k >> 8);
+    return __builtin_ldexp(__builtin_fma(h * s.r, step_poly<3>(s.r), h), s.k >> 8);
 }
 
-// e^x - 1 with no digits lost near 0: 2^k - 1 is exact up to the entry's own
-// rounding, which is in the table too.  The clamp keeps 2^k finite.
+// e^x - 1 to a few units in the last place: within a step of 0 it is r times the
+// polynomial, elsewhere 2^k - 1 is exact up to the entry's own rounding, which is
+// in the table too.  (With the polynomial of e^x the error was up to 2.8e-14 of the
+// result, at |x| of half a step.)  The clamp keeps 2^k finite.
 __device__ __forceinline__ double table_expm1(double x, const ExpTable &t)
 {
     const Steps s = split_steps(x, 709.7);
     const int j = s.k & 255, e = s.k >> 8;
     const double h = __builtin_ldexp(t.hi[j], e), l = __builtin_ldexp(t.lo[j], e);
-    return (h - 1.0) + __builtin_fma(h * s.r, step_poly(s.r), l);
+    return (h - 1.0) + __builtin_fma(h * s.r, step_poly<4>(s.r), l);
 }
 
 // p(theta | Lambda) / p(theta | 0) of one sample is c.num n / d: d the integral of
@@ -311,7 +319,7 @@ __device__ __forceinline__ double reciprocal(double x)
 // Lambda of slice y each wave writes the sum of its samples' weights to
 // partials[(k * n_events + event) * n_slots + chunk * kWaves + wave].
 //
-// Bound by instruction issue: 109 vector instructions per sample and Lambda, three
+// Bound by instruction issue: 110 vector instructions per sample and Lambda, three
 // exponentials, one expm1 and half a division among them, at about 0.9 of the issue
 // slots.  200 events x 20,000 samples x 64 points, the whole call: 1131 us with the
 // library's expm1 and a division per sample (150 instructions), 779 us now.  4 samples per thread: 6 and 8

@@ -1,0 +1,55 @@
+"""gw_pop_lnl on single samples, against 40-digit arithmetic, where the mass ratio's
+normalisation (1 - q_min^(1 + beta)) / (1 + beta) is a small difference.
+
+The hyper-parameters leave every other factor simple (a flat primary mass, spin
+magnitudes with a density of 1, isotropic tilts, q = 1, m_min = 1 so that ln m_min = 0),
+and the sample's prior brings the weight near 1.  The kernel's result then takes about 16
+roundings, each of a quantity of at most 2 beside what it is added to: 16 * 2 * 2^-53, and
+the bar is 4e-15.
+"""
+import mpmath as mp
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+BAR = 4e-15
+
+
+def _run(samples, hyper):
+    import torch
+    import paper_1904_02863_amd as gw
+    s = torch.from_numpy(np.ascontiguousarray(samples)).to("cuda:0")
+    h = torch.from_numpy(np.ascontiguousarray(hyper)).to("cuda:0")
+    got = gw.pop_lnl(s, h).cpu().numpy()
+    np.testing.assert_array_equal(gw.pop_lnl(gw.pop_prepare(s), h).cpu().numpy(), got)
+    return got
+
+
+def _sample(m1, ln_prior, q=1.0):
+    return np.array([m1, q, 0.5, 0.5, 0.3, -0.2, ln_prior]).reshape(7, 1, 1)
+
+
+def _hyper(beta, mmax=60.0):
+    return np.array([[0.0, beta, 1.0, mmax, 0.0, 10.0, 5.0, 1.0, 1.0, 0.0, 1.0, 1.0]])
+
+
+def _ref(m1, ln_prior, beta, mmax=60.0, q=1.0):
+    with mp.workdps(40):
+        m1, ln_prior, b1 = mp.mpf(m1), mp.mpf(ln_prior), 1 + mp.mpf(beta)
+        norm = -mp.expm1(-b1 * mp.log(m1)) / b1
+        return mp.mpf(q) ** mp.mpf(beta) / (4 * (mp.mpf(mmax) - 1) * norm) * mp.exp(-ln_prior)
+
+
+# (m1, 1 + beta): the argument (1 + beta) ln q_min of expm1 is about the product's size
+POINTS = ([(2.0, s * x / np.log(2.0)) for s in (1.0, -1.0) for x in (1e-4, 4e-4, 8e-4, 1e-3, 1.3e-3, 5e-3, 1e-2, 4e-2)]
+          + [(1.0 + x, b) for b in (1.0, 0.5, 3.0) for x in (1e-4, 4e-4, 1.25e-3, 8e-3, 3e-2)])
+
+
+@pytest.mark.parametrize("m1,one_p_beta", POINTS)
+def test_small_normalisation(m1, one_p_beta):
+    beta = one_p_beta - 1.0
+    ln_prior = float(mp.log(_ref(m1, 0.0, beta)))
+    got = _run(_sample(m1, ln_prior), _hyper(beta))[0]
+    err = abs(mp.mpf(float(got)) - mp.log(_ref(m1, ln_prior, beta)))
+    assert err <= BAR, float(err)
