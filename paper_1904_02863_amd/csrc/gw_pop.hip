@@ -271,13 +271,14 @@ __device__ __forceinline__ double table_exp(double x, const ExpTable &t)
     return __builtin_ldexp(__builtin_fma(h * s.r, step_poly<3>(s.r), h), s.k >> 8);
 }
 
-// e^x - 1 to a few units in the last place: within a step of 0 it is r times the
-// polynomial, elsewhere 2^k - 1 is exact up to the entry's own rounding, which is
-// in the table too.  (With the polynomial of e^x the error was up to 2.8e-14 of the
-// result, at |x| of half a step.)  The clamp keeps 2^k finite.
+// e^x - 1 to a few units in the last place, for x up to kExpm1Most (past it 2^k leaves
+// the range): within a step of 0 it is r times the polynomial, elsewhere 2^k - 1 is exact up
+// to the entry's own rounding, which is in the table too.  (With the polynomial of
+// e^x the error was up to 2.8e-14 of the result, at |x| of half a step.)
+constexpr double kExpm1Most = 709.7;
 __device__ __forceinline__ double table_expm1(double x, const ExpTable &t)
 {
-    const Steps s = split_steps(x, 709.7);
+    const Steps s = split_steps(x, kExpm1Most);
     const int j = s.k & 255, e = s.k >> 8;
     const double h = __builtin_ldexp(t.hi[j], e), l = __builtin_ldexp(t.lo[j], e);
     return (h - 1.0) + __builtin_fma(h * s.r, step_poly<4>(s.r), l);
@@ -357,11 +358,17 @@ __global__ __launch_bounds__(kThreads, 2) void weights_kernel(int64_t n_events, 
 #pragma unroll
                 for (int i = 0; i < kPerThread; i += 2)
                     w = __builtin_fma(__builtin_fma(n[i], d[i + 1], n[i + 1] * d[i]), reciprocal(d[i] * d[i + 1]), w);
+                w *= c.num;
             } else {
+                // beta far below -1 takes the normalisation past the table's expm1, where it is e^y
+                // and at 709.79 infinite (the library's expm1 here costs a wave per SIMD in registers)
 #pragma unroll
-                for (int i = 0; i < kPerThread; ++i) w += n[i] / d[i];
+                for (int i = 0; i < kPerThread; ++i) {
+                    const double y = c.one_p_beta * (c.ln_mmin - x[i].ln_m1);
+                    const double den = y > kExpm1Most ? 2.0 * table_exp(y - 0.6931471805599453, t_exp) : d[i];
+                    w = __builtin_fma(n[i], c.num / den, w);
+                }
             }
-            w *= c.num;
         }
         w = wave_sum(w);
         if (lane == 0) partials[(k * n_events + event) * n_slots + chunk * kWaves + wave] = w;

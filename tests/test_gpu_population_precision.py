@@ -53,3 +53,22 @@ def test_small_normalisation(m1, one_p_beta):
     got = _run(_sample(m1, ln_prior), _hyper(beta))[0]
     err = abs(mp.mpf(float(got)) - mp.log(_ref(m1, ln_prior, beta)))
     assert err <= BAR, float(err)
+
+
+# (1 + beta) ln q_min for beta far below -1: finite up to ln of the largest double, 709.7827
+@pytest.mark.parametrize("x", [500.0, 709.5, 709.75, 709.78])
+def test_large_normalisation(x):
+    """The exponents are of size x: 8 roundings of it."""
+    m1 = 50.0
+    beta = -1.0 - x / np.log(m1)
+    got = _run(_sample(m1, 0.0), _hyper(beta))[0]
+    assert abs(got - float(mp.log(_ref(m1, 0.0, beta)))) <= 8 * x * 2.0 ** -53
+
+
+def test_overflowing_normalisation():
+    """Beyond it the normalisation is infinite and a sample of finite density weighs nothing."""
+    from oracle import population as pop
+    s, h = _sample(50.0, 0.0, q=0.1), _hyper(-200.0)
+    with np.errstate(over="ignore"):
+        assert pop.lnl(s, h)[0] == -np.inf
+    assert _run(s, h)[0] == -np.inf
