@@ -61,8 +61,9 @@ struct HyperC {
     int pairs, pad;                       // two samples may share a division (kPairsMin)
 };
 
-// Two samples' weights n0 / d0 + n1 / d1 are one quotient over d0 d1.  The
-// product must not leave the range: |d| <= 1 for beta > -1 (and a logarithm
+// Two samples' weights n0 / d0 + n1 / d1 take one division: r = 1 / (d0 d1), n0 (d1 r) +
+// n1 (d0 r) (not (n0 d1 + n1 d0) r: n0 d1 can leave the range where n0 / d0 does not).
+// d0 d1 must not leave it: |d| <= 1 for beta > -1 (and a logarithm
 // for beta = -1), and this far above -1 it stays above 1e-38.
 constexpr double kPairsMin = 1e-3;
 
@@ -320,7 +321,7 @@ __device__ __forceinline__ double reciprocal(double x)
 // Lambda of slice y each wave writes the sum of its samples' weights to
 // partials[(k * n_events + event) * n_slots + chunk * kWaves + wave].
 //
-// Bound by instruction issue: 110 vector instructions per sample and Lambda, three
+// Bound by instruction issue: 111 vector instructions per sample and Lambda, three
 // exponentials, one expm1 and half a division among them, at about 0.9 of the issue
 // slots.  200 events x 20,000 samples x 64 points, the whole call: 1131 us with the
 // library's expm1 and a division per sample (150 instructions), 779 us now.  4 samples per thread: 6 and 8
@@ -356,9 +357,11 @@ __global__ __launch_bounds__(kThreads, 2) void weights_kernel(int64_t n_events, 
             for (int i = 0; i < kPerThread; ++i) weight(x[i], c, t_exp, n[i], d[i]);
             if (c.pairs) {
 #pragma unroll
-                for (int i = 0; i < kPerThread; i += 2)
-                    w = __builtin_fma(__builtin_fma(n[i], d[i + 1], n[i + 1] * d[i]), reciprocal(d[i] * d[i + 1]), w);
-                w *= c.num;
+                for (int i = 0; i < kPerThread; i += 2) {
+                    const double r = c.num * reciprocal(d[i] * d[i + 1]);
+                    w = __builtin_fma(n[i], d[i + 1] * r, w);
+                    w = __builtin_fma(n[i + 1], d[i] * r, w);
+                }
             } else {
                 // beta far below -1 takes the normalisation past the table's expm1, where it is e^y
                 // and at 709.79 infinite (the library's expm1 here costs a wave per SIMD in registers)

@@ -72,3 +72,13 @@ def test_overflowing_normalisation():
     with np.errstate(over="ignore"):
         assert pop.lnl(s, h)[0] == -np.inf
     assert _run(s, h)[0] == -np.inf
+
+
+@pytest.mark.parametrize("gap", [1e-6, 1e-13])
+def test_weight_near_the_bottom_of_the_range(gap):
+    """A weight of 1e-304 keeps its digits beside a sample whose normalisation is small:
+    samples 256 apart may share a division.  (Exponents of 700: 8 roundings of them.)"""
+    s = np.tile(_sample(0.5, 0.0), (1, 1, 512))          # below m_min: no weight
+    s[:, 0, 0], s[:, 0, 256] = _sample(2.0, 698.0).ravel(), _sample(1.0 + gap, 3000.0).ravel()
+    ref = float(mp.log(_ref(2.0, 698.0, 0.0) / 512))
+    assert abs(_run(s, _hyper(0.0))[0] - ref) <= 8 * 700 * 2.0 ** -53
