@@ -164,7 +164,8 @@ int64_t gw_workspace_bytes(const gw_workspace *ws);
 
 /* Plan autotuning of gw_lnl_batch on this workspace.  While it is on (the
  * default), the first call of a size class (detector count, precision,
- * template end, floor(log2 n_bins), floor(log2 n_samples)) with at least 2^24
+ * template end, floor(log2 n_bins), floor(log2 n_samples), and whether the call is
+ * large enough to sum over frequency nodes) with at least 2^24
  * (sample, bin) pairs times the call under each candidate plan (the largest
  * LDS tile and half of it; 0, 4, 6 or 8 work-queue rounds, 0 only with the
  * ISCO end), writing lnl_out once per candidate and waiting for the stream,

@@ -29,7 +29,7 @@ struct gw_workspace {
     int device = 0;
     int n_cu = 0;
     OccupancyCache occupancy;
-    // single-event plans chosen by timing, by (detectors, precision and form,
+    // single-event plans chosen by timing, by (detectors, precision, form and nodes,
     // log2 bins, log2 samples): (tile bins, work-queue rounds)
     bool tune_single = true;
     std::map<std::tuple<int, int, int, int>, std::pair<int, int>> single_tuning;
@@ -243,9 +243,20 @@ gw::TilePlan plan_tiles_on(int n_cu, OccupancyCache &occ, int64_t n_bins, int n_
 
 int log2_bucket(int64_t n) { return n > 0 ? (int)std::floor(std::log2((double)n)) : 0; }
 
+// Whether a call of this size and form sums over frequency nodes (kNodeMinWork).
+bool on_nodes(int64_t n_bins, int64_t n_samples, int form)
+{
+    const int64_t groups = (n_samples + gw::kBlock - 1) / gw::kBlock;
+    return form == gw::kFormSplit && n_bins >= gw::kNodeMinBins && n_bins <= 0x7fffffffLL &&
+           (double)n_bins * (double)groups >= (double)gw::kNodeMinWork;
+}
+
+// The size class whose calls share a plan.  Calls on nodes have classes of
+// their own: the same bins and samples are far less work there.
 std::tuple<int, int, int, int> tuning_key(int64_t n_bins, int n_det, int64_t n_samples, bool mixed, int form)
 {
-    return std::make_tuple(n_det, (mixed ? 1 : 0) + 2 * form, log2_bucket(n_bins), log2_bucket(n_samples));
+    return std::make_tuple(n_det, (mixed ? 1 : 0) + 2 * form + (on_nodes(n_bins, n_samples, form) ? 2 * gw::kForms : 0),
+                           log2_bucket(n_bins), log2_bucket(n_samples));
 }
 
 // The plan gw_lnl_batch uses on this workspace: the tuned one of the size
@@ -307,9 +318,7 @@ LnlLayout lnl_layout(int64_t n_bins, int n_det, int64_t n_samples, const gw::Til
                      size_t room = SIZE_MAX)
 {
     const LnlLayout plain = lnl_layout_as(n_bins, n_det, n_samples, plan, flags, n_cu, false);
-    if (gw::tile_form(flags) != gw::kFormSplit || n_bins < gw::kNodeMinBins || n_bins > 0x7fffffffLL ||
-        (double)n_bins * (double)plan.n_groups < (double)gw::kNodeMinWork)
-        return plain;
+    if (!on_nodes(n_bins, n_samples, gw::tile_form(flags))) return plain;
     const LnlLayout nodes = lnl_layout_as(n_bins, n_det, n_samples, plan, flags, n_cu, true);
     for (const size_t limit : {kStaticScratchBytes, room})
         if (plain.total <= limit && nodes.total > limit) return plain;
@@ -917,11 +926,11 @@ int ragged_run(gw_workspace *ws, int n_events, const gw_event *events, const std
     const int64_t pairs = ragged_pairs(na, ev);
     const int bucket = pairs > 0 ? (int)std::floor(std::log2((double)pairs)) : 0;
     // nodes, unless their sections alone (whose size no tile shape changes) leave a workspace that cannot grow
-    const bool on_nodes =
+    const bool nodes =
         ragged_nodes(na, ev, flags) &&
         (!ws->pinned || ragged_plan(ws, na, ev, data, psd, theta, n_param, lnl, mixed, flags, true, kTuneTiles[0],
                                     kTuneChunks[0], nullptr).total <= ws->capacity);
-    const auto tkey = std::make_tuple(max_det, (mixed ? 1 : 0) + 2 * form + (on_nodes ? 2 * gw::kForms : 0), bucket);
+    const auto tkey = std::make_tuple(max_det, (mixed ? 1 : 0) + 2 * form + (nodes ? 2 * gw::kForms : 0), bucket);
     auto it = ws->ragged_tuning.find(tkey);
     int tile_bins = 0;
     int64_t chunk_bins = 0;
@@ -931,9 +940,9 @@ int ragged_run(gw_workspace *ws, int n_events, const gw_event *events, const std
         for (int tb : kTuneTiles) {
             if (gw::lnl_tile_lds_bytes(max_det, tb, form, mixed) > 80 * 1024) continue;
             for (int64_t cb : kTuneChunks) {
-                if (on_nodes && cb != kTuneChunks[0]) break;     // the device sizes the items
+                if (nodes && cb != kTuneChunks[0]) break;     // the device sizes the items
                 if (int rc = ragged_materialise(ws, na, ev, active_geoms, data, psd, theta, n_param, lnl, mixed, flags,
-                                                on_nodes, tb, cb, ws->capture_stream, &plan))
+                                                nodes, tb, cb, ws->capture_stream, &plan))
                     return rc;
                 float ms = 0.0f;
                 if (int rc = time_ragged(ws, plan, &ms)) return rc;
@@ -952,7 +961,7 @@ int ragged_run(gw_workspace *ws, int n_events, const gw_event *events, const std
     ws->last_tile_bins = tile_bins;
     ws->last_chunk_bins = chunk_bins;
     if (int rc = ragged_materialise(ws, na, ev, active_geoms, data, psd, theta, n_param, lnl, mixed, flags,
-                                    on_nodes, tile_bins, chunk_bins, stream, &plan))
+                                    nodes, tile_bins, chunk_bins, stream, &plan))
         return rc;
     hipError_t e = hipStreamSynchronize(ws->capture_stream);
     if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
