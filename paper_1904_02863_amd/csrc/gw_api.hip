@@ -746,7 +746,10 @@ RaggedPlan ragged_plan(gw_workspace *ws, int n_events, const gw_event *events, c
         rc.n_det = d;
         rc.n_events = (int)(p.members.size() - m0);
         rc.n_spread = (int)(p.spread_map.size() - b0);
-        rc.grid = ws->n_cu * gw::ragged_node_blocks_per_cu(d, tile_bins);
+        for (int pass = 0; pass < 2; ++pass) {
+            rc.pass_tile[pass] = gw::ragged_pass_tile(d, tile_bins, mixed, pass);
+            rc.pass_grid[pass] = ws->n_cu * gw::ragged_node_blocks_per_cu(d, rc.pass_tile[pass], mixed, pass);
+        }
         member_begin.push_back(m0);
         spread_begin.push_back(b0);
         first_begin.push_back(n_first);

@@ -109,6 +109,9 @@ struct RaggedClass {
     int n_det;
     int n_items;
     int grid;                 // persistent blocks
+    // on frequency nodes, of the passes over the bins (FP64: of everything) and over the nodes
+    // (mixed precision): persistent blocks, and bins staged in LDS at a time
+    int pass_grid[2], pass_tile[2];
     const WorkItem *items;    // device, sorted by decreasing cost
     unsigned *counter;        // device; on frequency nodes two, one per pass
     // on frequency nodes: the class's events, the first item of each event in
@@ -222,7 +225,8 @@ hipError_t launch_fill_c128(int64_t n, double re, double im, gw_c128 *out, int n
 hipError_t launch_ragged_tables(const RaggedLaunch &r, hipStream_t stream);
 hipError_t launch_ragged(const RaggedLaunch &r, hipStream_t stream);
 int lnl_ragged_blocks_per_cu(int n_det, int tile_bins, bool mixed, int form);
-int ragged_node_blocks_per_cu(int n_det, int tile_bins);
+// The pass `pass` of a ragged call on frequency nodes (RaggedClass).
+int ragged_node_blocks_per_cu(int n_det, int tile_bins, bool mixed, int pass);
 
 // Population likelihood (gw_pop.hip): workspace bytes, weight-kernel blocks
 // and the launch of the hyper-parameter, weights and finalize kernels.

@@ -1060,7 +1060,7 @@ __device__ __forceinline__ int64_t pass_units(const RaggedEvent &re, bool mixed,
 // chunks (split), the first item of each (first, [2][n + 1]) and zero counters.
 __global__ __launch_bounds__(kBlock) void ragged_split_kernel(const RaggedEvent *__restrict__ events,
                                                               const int *__restrict__ members, int n, int mixed,
-                                                              int grid, unsigned *__restrict__ first,
+                                                              int2 grids, unsigned *__restrict__ first,
                                                               unsigned *__restrict__ counter)
 {
     __shared__ double red[kBlock];
@@ -1074,6 +1074,7 @@ __global__ __launch_bounds__(kBlock) void ragged_split_kernel(const RaggedEvent 
             work += (double)(pass_units(re, mixed != 0, pass) * groups_of(re));
         }
         work = block_sum(work, red);
+        const int grid = pass == 0 ? grids.x : grids.y;
         const int64_t size = max((int64_t)kRaggedUnits, (int64_t)ceil(work / ((double)kRaggedItems * (double)grid)));
         double items = 0.0;
         for (int i = i0; i < i1; ++i) {
@@ -1470,9 +1471,13 @@ int lnl_ragged_blocks_per_cu(int n_det, int tile_bins, bool mixed, int form)
     return occupancy(kernel_for(true, n_det, mixed, form), tile_lds_bytes(n_det, tile_bins, form, mixed));
 }
 
-int ragged_node_blocks_per_cu(int n_det, int tile_bins)
+static NodeMode ragged_mode(bool mixed, int pass) { return !mixed ? kBinsAndNodes : pass == 0 ? kNodeBins : kNodesOnly; }
+
+int ragged_node_blocks_per_cu(int n_det, int tile_bins, bool mixed, int pass)
 {
-    return occupancy(ragged_node_kernel_for(n_det, kBinsAndNodes), tile_lds_bytes(n_det, tile_bins, kFormSplit, false));
+    const NodeMode mode = ragged_mode(mixed, pass);
+    return occupancy(ragged_node_kernel_for(n_det, mode),
+                     tile_lds_bytes(n_det, tile_bins, kFormSplit, mode == kNodeBins));
 }
 
 hipError_t launch_lnl_tiles(const gw_grid &grid, int n_det, int64_t n_samples, const TilePlan &plan, bool mixed,
@@ -1527,7 +1532,7 @@ static hipError_t launch_ragged_nodes(const RaggedLaunch &r, hipStream_t stream)
     for (int i = 0; i < r.n_classes; ++i) {
         const RaggedClass &c = r.classes[i];
         hipLaunchKernelGGL(ragged_split_kernel, dim3(1), dim3(kBlock), 0, stream, r.events, c.events, c.n_events,
-                           r.mixed ? 1 : 0, c.grid, c.first, c.counter);
+                           r.mixed ? 1 : 0, make_int2(c.pass_grid[0], c.pass_grid[1]), c.first, c.counter);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if ((e = launch_ragged_spread(r, stream)) != hipSuccess) return e;
@@ -1538,13 +1543,14 @@ static hipError_t launch_ragged_nodes(const RaggedLaunch &r, hipStream_t stream)
         const int *members = c.events;
         const unsigned *first = c.first;
         unsigned *counter = c.counter;
-        int n = c.n_events, tile_bins = r.tile_bins;
+        int n = c.n_events, tile_bins = 0;
         void *args[] = {&events, &members, &n, &first, &counter, &tile_bins};
-        for (const NodeMode mode : {kNodeBins, kNodesOnly, kBinsAndNodes}) {
-            if ((mode != kBinsAndNodes) != r.mixed) continue;
+        for (int pass = 0; pass < (r.mixed ? 2 : 1); ++pass) {
+            const NodeMode mode = ragged_mode(r.mixed, pass);
             const void *fn = ragged_node_kernel_for(c.n_det, mode);
             if (!fn) return hipErrorInvalidValue;
-            e = hipLaunchKernel(fn, dim3(c.grid), dim3(kBlock), args,
+            tile_bins = c.pass_tile[pass];
+            e = hipLaunchKernel(fn, dim3(c.pass_grid[pass]), dim3(kBlock), args,
                                 tile_lds_bytes(c.n_det, tile_bins, kFormSplit, mode == kNodeBins), stream);
             if (e != hipSuccess) return e;
         }

@@ -69,6 +69,13 @@ inline int tile_bins_for(int n_det, int form, bool mixed)
     return t;
 }
 
+// Tile of pass `pass` of a ragged call on frequency nodes with tiles of
+// tile_bins: the mixed path's second pass takes FP64 phasors, whose table leaves less of the budget.
+inline int ragged_pass_tile(int n_det, int tile_bins, bool mixed, int pass)
+{
+    return mixed && pass == 1 ? std::min(tile_bins, tile_bins_for(n_det, kFormSplit, false)) : tile_bins;
+}
+
 // resident: blocks of this kernel that fit on the device at once; rounds:
 // work-queue rounds (0: one block per item), GW_TILE_ROUNDS by default.
 inline TilePlan plan_single_event(int64_t n_bins, int64_t n_samples, int form, int tile_bins, int64_t resident,
