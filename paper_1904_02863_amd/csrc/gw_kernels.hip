@@ -1056,7 +1056,7 @@ __device__ __forceinline__ int64_t pass_units(const RaggedEvent &re, bool mixed,
 // One block: the items of one detector count's events.  An event's units are known only now, and
 // differ by far more than its bins do (a short event keeps its bins, a long one
 // is nearly all nodes), so the items' size is set here: about kRaggedItems
-// items per resident block, each kRaggedUnits units or more.  Writes every event's
+// items per resident block (ragged_item_units).  Writes every event's
 // chunks (split), the first item of each (first, [2][n + 1]) and zero counters.
 __global__ __launch_bounds__(kBlock) void ragged_split_kernel(const RaggedEvent *__restrict__ events,
                                                               const int *__restrict__ members, int n, int mixed,
@@ -1075,7 +1075,7 @@ __global__ __launch_bounds__(kBlock) void ragged_split_kernel(const RaggedEvent 
         }
         work = block_sum(work, red);
         const int grid = pass == 0 ? grids.x : grids.y;
-        const int64_t size = max((int64_t)kRaggedUnits, (int64_t)ceil(work / ((double)kRaggedItems * (double)grid)));
+        const int64_t size = ragged_item_units(work, grid);
         double items = 0.0;
         for (int i = i0; i < i1; ++i) {
             const RaggedEvent &re = events[members[i]];

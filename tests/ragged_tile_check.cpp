@@ -2,9 +2,12 @@
 // built and run by tests/test_ragged_tile_host.py: for every detector count, precision
 // and tile the autotuner may time, each pass's block fits 80 KB (two blocks per
 // compute unit), no pass has a larger tile than was asked for, and a tile is at
-// least 64 bins.  Prints "ok <cases>" or the first failure.
+// least 64 bins; and the items a call is cut into are neither so short that they
+// cost more than their sums nor so long that the last ones run alone.  Prints
+// "ok <cases>" or the first failure.
 #include <cstdio>
 
+#include "gw_nodes.h"
 #include "gw_plan.h"
 
 namespace gw {
@@ -33,6 +36,15 @@ int main()
                     ++cases;
                 }
             }
+    for (int grid : {1, 256, 512, 768})
+        for (double work = 0.0; work < 1e9; work = work * 1.7 + 1.0) {
+            const int64_t u = gw::ragged_item_units(work, grid);
+            if (u < 64 || u > 1024 || (u > 64 && u < 1024 && (double)u * 4.0 * grid < work)) {
+                std::printf("FAIL work %g on %d blocks: items of %lld\n", work, grid, (long long)u);
+                return 1;
+            }
+            ++cases;
+        }
     std::printf("ok %d\n", cases);
     return 0;
 }
