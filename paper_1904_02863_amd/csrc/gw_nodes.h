@@ -26,6 +26,7 @@
 // R q delta_f <= GW_RESAMPLE_BAND.  Bins below every K(q) are summed one by one.
 #pragma once
 
+#include <cmath>
 #include <cstdint>
 
 #include <hip/hip_runtime.h>
@@ -116,14 +117,117 @@ __host__ __device__ inline bool node_room_ok(const NodeLevel &v)
     return node_slots(v) + 3 * (int64_t)node_count(v) <= v.k1 - v.k0;
 }
 
+// Half the batch's range of every phase coefficient about the reference, as
+// what it adds to |dx/df| (see node_rate).
+struct RateBound {
+    double tau, c7, c6, c6l, c5l, c4, c3, c2, c0;
+};
+
+// Bound on |dx_d/df| (turns per Hz) of x_d less the reference's phase at
+// frequency u^3, over every evaluated sample and detector: the derivative of
+//   x = tau f + c7 u^2 + (c6 + c6l L) u + (c5 + c5l L) + c4/u + c3/u^2 + c2/u^3 + c0/u^5
+// term by term, each coefficient at the end of its range (the log of the c6 term
+// at its largest magnitude, folded into r.c6).  Every term falls with f, so the bound does.
+__host__ __device__ inline double node_rate(const RateBound &r, double u)
+{
+    const double v = 1.0 / u;
+    double p = 5.0 * r.c0 * v * v + 3.0 * r.c2;
+    p = p * v + 2.0 * r.c3;
+    p = p * v + r.c4;
+    p = p * v + r.c5l;
+    p = p + u * (r.c6 + 2.0 * r.c7 * u);
+    return r.tau + p * v * v * v * (1.0 / 3.0);
+}
+
+// Reference of a coefficient that runs from lo to hi over the batch, and half its
+// range about it: the middle where the range keeps one sign and spans at most a
+// factor 4, else 0.  Then no sample's difference from the reference is more than
+// 1.5 times the coefficient itself, and one far-off row of a batch cannot cost the
+// others their digits.
+__host__ __device__ inline void node_middle(double lo, double hi, double &mid, double &half)
+{
+    mid = half = 0.0;
+    if (!(lo <= hi)) return;                     // no sample is evaluated
+    const double a = fmin(fabs(lo), fabs(hi)), b = fmax(fabs(lo), fabs(hi));
+    if ((lo > 0.0) == (hi > 0.0) && 4.0 * a >= b) mid = 0.5 * lo + 0.5 * hi;
+    half = fmax(fabs(lo - mid), fabs(hi - mid));
+}
+
+// The band as the plan sees it: the bound is tried at kBlock frequencies from
+// half of f_low up, even in u (about 1% apart in f), the last one the top of the
+// band.  Nodes stand up to 16 cells past its ends.
+struct NodeBand {
+    double f_low, df, u_low, u_high, du;
+    double l_most;        // the largest |ln u| + 1 at any node
+    int64_t n_bins;
+};
+
+__host__ __device__ inline NodeBand node_band(double f_low, double df, int64_t n_bins)
+{
+    NodeBand b;
+    const double f_high = f_low + (double)(n_bins - 1) * df;
+    const double f_past = f_high + 2.0 * kTaps * node_spacing(kNodeSpacings - 1) * df;
+    b.f_low = f_low;
+    b.df = df;
+    b.n_bins = n_bins;
+    b.u_low = cbrt(0.5 * f_low);
+    b.u_high = cbrt(f_high);
+    b.du = (b.u_high - b.u_low) * (1.0 / (kBlock - 1));
+    b.l_most = fmax(fabs(log(0.5 * f_low)), fabs(log(f_past))) * (1.0 / 3.0) + 1.0;
+    return b;
+}
+
+__host__ __device__ inline double node_probe(const NodeBand &b, int t)
+{
+    return t == kBlock - 1 ? b.u_high : b.u_low + b.du * (double)t;
+}
+
+// half[j]: half the range of pair j (kStatPairs).
+__host__ __device__ inline RateBound node_bound(const double *half, const NodeBand &b)
+{
+    RateBound r;
+    r.tau = half[0];
+    r.c7 = half[1];
+    r.c6l = half[3];
+    r.c5l = half[4];
+    r.c4 = half[5];
+    r.c3 = half[6];
+    r.c2 = half[7];
+    r.c0 = half[8];
+    r.c6 = half[2] + half[3] * b.l_most;         // |d/du of (c6 + c6l L) u| = |c6 + c6l (L + 1)|
+    return r;
+}
+
+// How many spacings a rate allows (spacings rise with their index).
+__host__ __device__ inline int node_allowed(double rate, double df)
+{
+    int n = 0;
+#pragma unroll
+    for (int g = 0; g < kNodeSpacings; ++g) n += rate * ((double)node_spacing(g) * df) <= GW_RESAMPLE_BAND;
+    return n;
+}
+
+// First bin of spacing g when `failing` of the kBlock probes, which are the lowest
+// ones since the bound falls with f, do not allow it (n_bins: it cannot be used).
+__host__ __device__ inline int node_first_bin(const NodeBand &b, int g, int failing)
+{
+    const double reach = (double)((kTapsBelow + 1) * node_spacing(g)) * b.df;   // a bin's nodes reach this far down
+    const double u = node_probe(b, failing);
+    const double k = ceil((fmax(u * u * u, b.f_low - reach) + reach - b.f_low) / b.df);
+    return failing == kBlock || !(k < (double)b.n_bins) ? (int)b.n_bins : (int)fmax(k, 0.0);
+}
+
 // Levels for first bins k_first[i] of spacing node_spacing(i) (n_bins where a
 // spacing cannot be used), from the widest down; what no level takes is left
-// to single bins.  node_pick returns how many levels there are and where the
-// single bins end, and fills v with level number `want` counted from the widest
-// (so that the kernels can have one thread per level).
-__host__ __device__ inline int node_pick(const int *k_first, int n_bins, int n_det, int want, NodeLevel &v, int &k_bin)
+// to single bins.  node_pick returns how many levels there are, where the
+// single bins end, and of level number `want`, counted from the widest, and those below
+// it their chunks and nodes together; it fills v with level `want` (so that the
+// kernels can have one thread per level).
+__host__ __device__ inline int node_pick(const int *k_first, int n_bins, int n_det, int want, NodeLevel &v, int &k_bin,
+                                         int &chunks, int &nodes)
 {
     int end = n_bins, n = 0, last = kNodeSpacings;
+    chunks = nodes = 0;
     v.q = 0;
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
@@ -132,11 +236,17 @@ __host__ __device__ inline int node_pick(const int *k_first, int n_bins, int n_d
         for (int i = kNodeSpacings - 1; i >= 0; --i) {
             const int k = k_first[i], q = node_spacing(i);
             if (i < last && k < end && end - k >= (pass == 0 ? kNodeMinCells : kNodeLowCells) * q) {
-                if (n == want) {
-                    v.k0 = k;
-                    v.k1 = end;
-                    v.q = q;
+                NodeLevel w;
+                w.k0 = k;
+                w.k1 = end;
+                w.q = q;
+                w.cells = (int)(((unsigned)(end - k) + (unsigned)q - 1u) / (unsigned)q);
+                node_chunks(n_det, w);
+                if (n >= want) {
+                    chunks += w.n_chunks;
+                    nodes += node_count(w);
                 }
+                if (n == want) v = w;
                 ++n;
                 end = k;
                 last = i;
@@ -144,31 +254,29 @@ __host__ __device__ inline int node_pick(const int *k_first, int n_bins, int n_d
         }
     }
     k_bin = end;
-    if (v.q > 0) {
-        v.cells = (int)(((unsigned)(v.k1 - v.k0) + (unsigned)v.q - 1u) / (unsigned)v.q);
-        node_chunks(n_det, v);
-    }
+    v.chunk0 = (k_bin + kSpreadBins - 1) / kSpreadBins + chunks - (v.q > 0 ? v.n_chunks : 0);
+    v.node0 = nodes - (v.q > 0 ? node_count(v) : 0);
     return n;
 }
 
+// A plan's counts, from `chunks` and `nodes` of all its levels (node_pick, want 0).
+__host__ __device__ inline void node_totals(int n_levels, int k_bin, int chunks, int nodes, NodePlan &p)
+{
+    p.k_bin = k_bin;
+    p.n_levels = n_levels;
+    p.n_nodes = nodes;
+    p.bin_chunks = (k_bin + kSpreadBins - 1) / kSpreadBins;
+    p.n_chunks = p.bin_chunks + chunks;
+}
+
+// The plan's levels and counts one level at a time (the device has a thread per level).
 inline void node_levels(const int *k_first, int n_bins, int n_det, NodePlan &p)
 {
     NodeLevel v;
-    int k_bin = 0;
-    p.n_levels = node_pick(k_first, n_bins, n_det, 0, v, k_bin);
-    p.k_bin = k_bin;
-    p.bin_chunks = (k_bin + kSpreadBins - 1) / kSpreadBins;
-    int chunk = p.bin_chunks, node = 0;
-    for (int l = 0; l < p.n_levels; ++l) {
-        NodeLevel &w = p.level[l];
-        node_pick(k_first, n_bins, n_det, p.n_levels - 1 - l, w, k_bin);
-        w.chunk0 = chunk;
-        w.node0 = node;
-        chunk += w.n_chunks;
-        node += node_count(w);
-    }
-    p.n_chunks = chunk;
-    p.n_nodes = node;
+    int k_bin = 0, chunks = 0, nodes = 0;
+    const int n = node_pick(k_first, n_bins, n_det, 0, v, k_bin, chunks, nodes);
+    node_totals(n, k_bin, chunks, nodes, p);
+    for (int l = 0; l < n; ++l) node_pick(k_first, n_bins, n_det, n - 1 - l, p.level[l], k_bin, chunks, nodes);
 }
 
 // Chunks of the weighting that any plan of n_bins bins can have: a chunk of a

@@ -26,36 +26,8 @@ static __constant__ double resample_coef[GW_RESAMPLE_DEGREE + 1][kTaps / 2] = {G
 static_assert(GW_RESAMPLE_DEGREE % 2 == 1, "even and odd parts of equal length");
 
 // ---------------------------------------------------------------- the plan
-// Half the batch's range of every phase coefficient about the reference, as
-// what it adds to |dx/df| (see node_rate).
-struct RateBound {
-    double tau, c7, c6, c6l, c5l, c4, c3, c2, c0;
-};
-
-// Bound on |dx_d/df| (turns per Hz) of x_d less the reference's phase at
-// frequency u^3, over every evaluated sample and detector: the derivative of
-//   x = tau f + c7 u^2 + (c6 + c6l L) u + (c5 + c5l L) + c4/u + c3/u^2 + c2/u^3 + c0/u^5
-// term by term, each coefficient at the end of its range (the log of the c6 term
-// at its largest magnitude, folded into r.c6 by the caller).  Every term
-// falls with f, so the bound does.
-__device__ __forceinline__ double node_rate(const RateBound &r, double u)
-{
-    const double v = 1.0 / u;
-    double p = 5.0 * r.c0 * v * v + 3.0 * r.c2;
-    p = p * v + 2.0 * r.c3;
-    p = p * v + r.c4;
-    p = p * v + r.c5l;
-    p = p + u * (r.c6 + 2.0 * r.c7 * u);
-    return r.tau + p * v * v * v * (1.0 / 3.0);
-}
-
 // The plan of a batch from the ranges of its phase coefficients, written to
 // `p` (LDS).  All kBlock threads call it; `red` holds kPlanScratch doubles.
-//
-// Reference: the middle of a coefficient's range where the range keeps one sign
-// and spans at most a factor 4, else 0.  Then no sample's difference from the
-// reference is more than 1.5 times the coefficient itself, and one far-off row of
-// a batch cannot cost the others their digits.
 constexpr int kPlanSlices = kBlock / kStats;                       // 14 slices of the entries
 constexpr int kPlanScratch = kPlanSlices * kStats + 2 * kStatPairs + 3 * kNodeSpacings;   // 5 kNodeSpacings ints at the end
 
@@ -66,13 +38,7 @@ __device__ __forceinline__ void make_node_plan(double f_low, double df, int64_t 
     double *const half = red + kPlanSlices * kStats, *const mid = half + kStatPairs;
     int *const first = reinterpret_cast<int *>(mid + kStatPairs);
     const int t = threadIdx.x;
-    // frequencies first: they do not wait for the ranges.  Nodes stand up to 16
-    // cells past the band's ends
-    const double f_high = f_low + (double)(n_bins - 1) * df;
-    const double f_past = f_high + 2.0 * kTaps * node_spacing(kNodeSpacings - 1) * df;
-    const double u_low = cbrt(0.5 * f_low), u_high = cbrt(f_high);
-    const double du = (u_high - u_low) * (1.0 / (kBlock - 1));
-    const double l_most = fmax(fabs(log(0.5 * f_low)), fabs(log(f_past))) * (1.0 / 3.0) + 1.0;
+    const NodeBand band = node_band(f_low, df, n_bins);      // does not wait for the ranges
     if (t < kPlanSlices * kStats) {
         const int j = t % kStats;
         double m = j % 2 == 0 ? INFINITY : -INFINITY;
@@ -89,34 +55,15 @@ __device__ __forceinline__ void make_node_plan(double f_low, double df, int64_t 
             lo = fmin(lo, red[e * kStats + 2 * t]);
             hi = fmax(hi, red[e * kStats + 2 * t + 1]);
         }
-        double m = 0.0, h = 0.0;
-        if (lo <= hi) {
-            const double a = fmin(fabs(lo), fabs(hi)), b = fmax(fabs(lo), fabs(hi));
-            if ((lo > 0.0) == (hi > 0.0) && 4.0 * a >= b) m = 0.5 * lo + 0.5 * hi;
-            h = fmax(fabs(lo - m), fabs(hi - m));
-        }
+        double m, h;
+        node_middle(lo, hi, m, h);
         mid[t] = m;
         half[t] = h;
     }
     __syncthreads();
-    RateBound r;
-    r.tau = half[0];
-    r.c7 = half[1];
-    r.c6l = half[3];
-    r.c5l = half[4];
-    r.c4 = half[5];
-    r.c3 = half[6];
-    r.c2 = half[7];
-    r.c0 = half[8];
-    r.c6 = half[2] + half[3] * l_most;               // |d/du of (c6 + c6l L) u| = |c6 + c6l (L + 1)|
-    // first bin of every spacing: the bound at kBlock frequencies from half of
-    // f_low up, even in u (about 1% apart in f); thread t finds the widest
-    // spacing its frequency allows, and since the bound falls with f, the first
-    // frequency that allows spacing g is the number of threads that do not
-    const double rate = node_rate(r, t == kBlock - 1 ? u_high : u_low + du * (double)t);
-    int widest = 0;                  // spacings allowed
-#pragma unroll
-    for (int g = 0; g < kNodeSpacings; ++g) widest += rate * ((double)node_spacing(g) * df) <= GW_RESAMPLE_BAND;
+    const RateBound r = node_bound(half, band);
+    // probe t: the spacings that the bound at its frequency allows; then those that fail, per spacing
+    const int widest = node_allowed(node_rate(r, node_probe(band, t)), df);
     int *const failing = first + kNodeSpacings;
 #pragma unroll
     for (int g = 0; g < kNodeSpacings; ++g) {
@@ -124,44 +71,20 @@ __device__ __forceinline__ void make_node_plan(double f_low, double df, int64_t 
         if (t % 64 == g) failing[(t / 64) * kNodeSpacings + g] = n;
     }
     __syncthreads();
-    if (t < kNodeSpacings) {
-        const int n = failing[t] + failing[kNodeSpacings + t] + failing[2 * kNodeSpacings + t] +
-                      failing[3 * kNodeSpacings + t];
-        const double reach = (double)((kTapsBelow + 1) * node_spacing(t)) * df;   // a bin's nodes reach this far down
-        const double u = n == kBlock - 1 ? u_high : u_low + du * (double)n;
-        const double k = ceil((fmax(u * u * u, f_low - reach) + reach - f_low) / df);
-        first[t] = n == kBlock || !(k < (double)n_bins) ? (int)n_bins : (int)fmax(k, 0.0);
-    }
+    if (t < kNodeSpacings)
+        first[t] = node_first_bin(band, t, failing[t] + failing[kNodeSpacings + t] + failing[2 * kNodeSpacings + t] +
+                                               failing[3 * kNodeSpacings + t]);
     __syncthreads();
     if (t < 64) {
         int k_first[kNodeSpacings];
 #pragma unroll
         for (int i = 0; i < kNodeSpacings; ++i) k_first[i] = first[i];
         NodeLevel v{};
-        int k_bin = 0;
+        int k_bin = 0, chunks = 0, nodes = 0;
         // lane t holds level t from the widest spacing, i.e. from the top of the band
-        const int n = node_pick(k_first, (int)n_bins, n_det, t, v, k_bin);
-        int chunks = t < n ? v.n_chunks : 0, nodes = t < n ? node_count(v) : 0;
-        const int own_chunks = chunks, own_nodes = nodes;
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) {             // inclusive sums over the levels below
-            const int c = __shfl_down(chunks, off, 64), m = __shfl_down(nodes, off, 64);
-            chunks += c;
-            nodes += m;
-        }
-        const int bin_chunks = (k_bin + kSpreadBins - 1) / kSpreadBins;
-        if (t < n) {
-            v.chunk0 = bin_chunks + chunks - own_chunks;
-            v.node0 = nodes - own_nodes;
-            p.level[n - 1 - t] = v;
-        }
-        if (t == 0) {
-            p.k_bin = k_bin;
-            p.n_levels = n;
-            p.n_nodes = nodes;
-            p.bin_chunks = bin_chunks;
-            p.n_chunks = bin_chunks + chunks;
-        }
+        const int n = node_pick(k_first, (int)n_bins, n_det, t, v, k_bin, chunks, nodes);
+        if (t < n) p.level[n - 1 - t] = v;
+        if (t == 0) node_totals(n, k_bin, chunks, nodes, p);
         if (t < kMids) {
             // kRecC8 .. kRecC0 from the pairs' order; the constant kRecC5 needs no reference
             constexpr int pair[kMids] = {0, 1, 2, 3, -1, 4, 5, 6, 7, 8};
