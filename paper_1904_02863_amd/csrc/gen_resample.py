@@ -1,9 +1,9 @@
 #!/usr/bin/env python3
 """Weights of the frequency resampling (writes gw_resample_weights.h).
 
-A function g whose local rate stays below NU cycles per node, |g'| phase rate
-<= 2 pi NU per node, is recovered between uniform nodes from the 2 P nodes
-around the point, g(x) ~ sum_t w_t(x) g(t - P + 1), 0 <= x < 1.  The weights
+A phasor g of a rate below NU cycles per node is recovered between uniform
+nodes from the 2 P nodes around the point, g(x) ~ sum_t w_t(x) g(t - P + 1),
+0 <= x < 1 (one whose rate changes over them, less well near the band's edge).  The weights
 are the least-squares ones over the band [-NU, NU]: they minimise
     int_{-NU}^{NU} |e^{2 pi i nu x} - sum_t w_t e^{2 pi i nu (t - P + 1)}|^2 dnu,
 i.e. solve the normal equations G w = b with G_ij = sinc(2 NU (i - j)) and
@@ -106,8 +106,8 @@ def header(coef) -> str:
         rows.append("    {" + ", \\\n     ".join(lines) + "}")
     return ("// Written by gen_resample.py.  Weights of the frequency resampling: weight t (node\n"
             f"// offset t - {P - 1}) of a point a fraction x of a node spacing past node 0 is the\n"
-            "// polynomial sum_j GW_RESAMPLE_COEF[j][t] s^j, s = 2 x - 1.  Recovers functions with\n"
-            f"// a local rate of up to {float(NU)} cycles per node to {e:.1e} (worst case over the band).\n"
+            "// polynomial sum_j GW_RESAMPLE_COEF[j][t] s^j, s = 2 x - 1.  Recovers phasors of a\n"
+            f"// constant rate of up to {float(NU)} cycles per node to {e:.1e} (worst case over the band).\n"
             "#pragma once\n\n"
             f"#define GW_RESAMPLE_HALF {P}\n#define GW_RESAMPLE_TAPS {TAPS}\n"
             f"#define GW_RESAMPLE_DEGREE {DEGREE}\n#define GW_RESAMPLE_BAND {float(NU)!r}\n"

@@ -8,14 +8,21 @@
 // template are far from independent: its phase turns by its local time,
 // |dx_d/df|, a fraction of a second over most of the band, against bins
 // delta_f = 1/T apart.  So the phasor of a bin is interpolated from nodes q
-// bins apart (32 weights of gw_resample_weights.h, exact to 4e-16 while the
-// phase turns by at most GW_RESAMPLE_BAND per node), the weights are applied
-// to the data once for all samples,
+// bins apart (32 weights of gw_resample_weights.h, for phases that turn by at
+// most GW_RESAMPLE_BAND per node), the weights are applied to the data once for all
+// samples,
 //     nu_d,n = sum_k w_n(k) D_d,k,        Z_d = sum_n nu_d,n e^{-2 pi i x_d(f_n)},
 // and the per-sample sum runs over the nodes: 1,652 instead of 259,585
 // frequencies for 4096 heavy binaries in 128 s, 17,900 instead of 1,040,897
-// for neutron stars from 15 Hz in 512 s.  The sums agree with the direct ones to FP64
-// rounding.
+// for neutron stars from 15 Hz in 512 s.
+//
+// A phasor of constant rate is interpolated to 4e-16.  A chirp's rate falls over a bin's 32
+// nodes, and where its lowest node is at the limit the bin is off by more: in the
+// lowest cell of a level by 4e-12 while the spacing is a hundredth of the frequency,
+// by up to 2e-10 where it is as wide; five cells up by 1e-13 and less.  Averaged over a
+// level that is 4e-12 at most.  What it does to lnL: 25 batches, from priors down to a
+// millionth of their width, f_low from 3 to 20 Hz, were within 3e-16 of <d,d> of the sums over
+// every bin, those from 3 Hz within 7e-15.
 //
 // Before the weights, D is multiplied by the phasor of a reference template
 // (the middle of the batch's range in every phase coefficient), so what has to
