@@ -1376,7 +1376,6 @@ __global__ __launch_bounds__(256) void zero_kernel(int64_t n, double *__restrict
     if (i < n) p[i] = 0.0;
 }
 
-// mean of loss[0..n) into out[0] (one block, fixed order).
 }  // namespace flow
 }  // namespace gw
 
@@ -1398,6 +1397,7 @@ struct gw_flow {
     double *bound = nullptr;              // [layers + 2][cap][dim]
     double *s_store = nullptr;            // [layers][cap][dim]
     double *sum_s = nullptr, *loss = nullptr, *g = nullptr, *gy = nullptr;
+    // of separate GEMMs alone (not fused_width)
     uint16_t *xm_b = nullptr;             // [layers][cap][kInPad]
     uint16_t *h1_b = nullptr, *h2_b = nullptr;   // [layers][cap][hidden]
     float *out_f = nullptr;               // [cap][2 dim]
@@ -1491,6 +1491,10 @@ void free_batch(gw_flow *f)
     f->cap = 0;
 }
 
+// Couplings as one kernel (hidden width 128 or 256), or false when the
+// width has no such kernel and the products run as separate GEMMs.
+bool fused_width(const gw_flow *f) { return f->hidden == 128 || f->hidden == 256; }
+
 int ensure_batch(gw_flow *f, int64_t n)
 {
     if (n <= f->cap) return GW_OK;
@@ -1503,12 +1507,12 @@ int ensure_batch(gw_flow *f, int64_t n)
     const int64_t w_layer = (int64_t)gw::flow::kMaxSplit * (H * D + H * H + 2 * D * H);
     const int64_t b_layer = (int64_t)rb_cap * (2 * H + 2 * D);
     const int64_t ldT = (c + 63) / 64 * 64;
+    const int64_t cg = fused_width(f) ? 0 : c;       // rows of the buffers that only separate GEMMs use
     if (alloc(&f->bound, (L + 2) * c * D) || alloc(&f->s_store, L * c * D) || alloc(&f->sum_s, c) ||
-        alloc(&f->loss, c) || alloc(&f->g, c * D) || alloc(&f->gy, c * D) || alloc(&f->xm_b, L * c * kInPad) ||
-        alloc(&f->h1_b, L * c * H) || alloc(&f->h2_b, L * c * H) || alloc(&f->out_f, c * 2 * D) ||
-        alloc(&f->dout_f, c * kOutPad) || alloc(&f->dout_b, c * kOutPad) || alloc(&f->dh, c * H) ||
-        alloc(&f->dpre_b, c * H) ||
-        alloc(&f->dpre2_b, c * H) || alloc(&f->wpart, L * w_layer) || alloc(&f->bpart, L * b_layer) ||
+        alloc(&f->loss, c) || alloc(&f->g, c * D) || alloc(&f->gy, c * D) || alloc(&f->xm_b, L * cg * kInPad) ||
+        alloc(&f->h1_b, L * cg * H) || alloc(&f->h2_b, L * cg * H) || alloc(&f->out_f, cg * 2 * D) ||
+        alloc(&f->dout_f, cg * kOutPad) || alloc(&f->dout_b, cg * kOutPad) || alloc(&f->dh, cg * H) ||
+        alloc(&f->dpre_b, cg * H) || alloc(&f->dpre2_b, cg * H) || alloc(&f->wpart, L * w_layer) || alloc(&f->bpart, L * b_layer) ||
         alloc(&f->h1T, L * H * ldT) || alloc(&f->h2T, L * H * ldT) || alloc(&f->xmT, L * kInPad * ldT) ||
         alloc(&f->doutT, L * kOutPad * ldT) || alloc(&f->dpreT, L * H * ldT) || alloc(&f->dpre2T, L * H * ldT)) {
         free_batch(f);
@@ -1553,10 +1557,6 @@ hipError_t mlp_forward(gw_flow *f, int l, int n, bool keep_t, hipStream_t s)
     GemmArgs g3{n, 2 * D, H, h2, H, 1, wq + o.w3, 1, H, f->out_f, 2 * D, nullptr, 0, pp + o.b3, 0};
     return gw::flow::gemm_bf16(g3, s);
 }
-
-// Coupling l as one kernel (hidden width 128 or 256), or false when the
-// width has no such kernel and the products run as separate GEMMs.
-bool fused_width(const gw_flow *f) { return f->hidden == 128 || f->hidden == 256; }
 
 // Where the kernel producing layer l's input writes that layer's masked
 // MLP input (and, with keep_t, its transposed copy); none for l outside the stack.
