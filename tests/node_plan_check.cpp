@@ -32,7 +32,7 @@ int main()
 {
     std::mt19937_64 rng(11);
     auto uni = [&](double a, double b) { return std::uniform_real_distribution<double>(a, b)(rng); };
-    int q = 0, with_levels = 0, with_bins = 0;
+    int q = 0, with_levels = 0, with_bins = 0, without = 0;
     const int n_cases = 3000;
     for (int it = 0; it < n_cases; ++it) {
         const double f_low = std::exp(uni(std::log(2.0), std::log(40.0))), df = std::exp(uni(std::log(1e-3), std::log(1.0)));
@@ -63,6 +63,11 @@ int main()
         for (int g = 0; g < gw::kNodeSpacings; ++g) first[g] = gw::node_first_bin(band, g, failing[g]);
         gw::NodePlan p{};
         gw::node_levels(first, (int)n_bins, n_det, p);
+        // what the device takes as "no nodes" before it looks for levels
+        if (gw::node_allowed(gw::node_rate(r, band.u_high), df) == 0) {
+            REQUIRE(p.n_levels == 0 && p.k_bin == n_bins);
+            ++without;
+        }
         // the samples' slopes
         for (int s = 0; s < 8; ++s) {
             double c[gw::kStatPairs];
@@ -96,7 +101,7 @@ int main()
         with_bins += p.k_bin > 0;
     }
     const int it = n_cases;
-    REQUIRE(with_levels > n_cases / 10 && with_bins > n_cases / 10);
+    REQUIRE(with_levels > n_cases / 10 && with_bins > n_cases / 10 && without > n_cases / 50);
     std::printf("ok %d\n", n_cases);
     return 0;
 }
