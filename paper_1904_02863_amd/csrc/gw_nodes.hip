@@ -62,15 +62,6 @@ __device__ __forceinline__ void make_node_plan(double f_low, double df, int64_t 
     }
     __syncthreads();
     const RateBound r = node_bound(half, band);
-    if (node_allowed(node_rate(r, band.u_high), df) == 0) {
-        // no spacing serves even the top of the band: every bin is summed as it is, and the rest
-        // of the plan and the reference's phasors are left out (1 detector x 32,768 bins x 1024
-        // rows with arrival times all over the segment: 64.4 -> 61.0 us)
-        if (t == 0) node_totals(0, (int)n_bins, 0, 0, p);
-        if (t < kMids) p.mid[t] = 0.0;
-        __syncthreads();
-        return;
-    }
     // probe t: the spacings that the bound at its frequency allows; then those that fail, per spacing
     const int widest = node_allowed(node_rate(r, node_probe(band, t)), df);
     int *const failing = first + kNodeSpacings;
@@ -80,6 +71,14 @@ __device__ __forceinline__ void make_node_plan(double f_low, double df, int64_t 
         if (t % 64 == g) failing[(t / 64) * kNodeSpacings + g] = n;
     }
     __syncthreads();
+    if (failing[0] + failing[kNodeSpacings] + failing[2 * kNodeSpacings] + failing[3 * kNodeSpacings] == kBlock) {
+        // no spacing serves even the top of the band: every bin is summed as it is (1 detector x
+        // 32,768 bins x 1024 rows with arrival times all over the segment: 64.4 -> 62.5 us)
+        if (t == 0) node_totals(0, (int)n_bins, 0, 0, p);
+        if (t < kMids) p.mid[t] = 0.0;
+        __syncthreads();
+        return;
+    }
     if (t < kNodeSpacings)
         first[t] = node_first_bin(band, t, failing[t] + failing[kNodeSpacings + t] + failing[2 * kNodeSpacings + t] +
                                                failing[3 * kNodeSpacings + t]);
@@ -180,8 +179,8 @@ __device__ __forceinline__ void spread_chunk(const NodeEvent &ev, const NodePlan
             psd[d] = ev.psd[(int64_t)d * n_bins + at];
             x[d] = ev.data[(int64_t)d * n_bins + at];
         }
-        double er = 1.0, ei = 0.0;                   // without nodes there is no reference
-        if (plan.n_levels > 0) gw_phasor_turns(turns_phase(ref, t1), er, ei);
+        double er, ei;
+        gw_phasor_turns(turns_phase(ref, t1), er, ei);
 #pragma unroll
         for (int d = 0; d < NDET; ++d) {
             const double w = (psd[d] > 0.0 && psd[d] < INFINITY) ? 1.0 / psd[d] : NAN;
