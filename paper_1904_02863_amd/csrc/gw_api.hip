@@ -243,20 +243,21 @@ gw::TilePlan plan_tiles_on(int n_cu, OccupancyCache &occ, int64_t n_bins, int n_
 
 int log2_bucket(int64_t n) { return n > 0 ? (int)std::floor(std::log2((double)n)) : 0; }
 
-// Whether a call of this size and form sums over frequency nodes (kNodeMinWork).
-bool on_nodes(int64_t n_bins, int64_t n_samples, int form)
+// Whether a call of this size and form sums over frequency nodes (node_min_work).
+bool on_nodes(int64_t n_bins, int n_det, int64_t n_samples, bool mixed, int form)
 {
     const int64_t groups = (n_samples + gw::kBlock - 1) / gw::kBlock;
     return form == gw::kFormSplit && n_bins >= gw::kNodeMinBins && n_bins <= 0x7fffffffLL &&
-           (double)n_bins * (double)groups >= (double)gw::kNodeMinWork;
+           (double)n_bins * (double)groups >= (double)gw::node_min_work(n_bins, n_det, mixed);
 }
 
 // The size class whose calls share a plan.  Calls on nodes have classes of
 // their own: the same bins and samples are far less work there.
 std::tuple<int, int, int, int> tuning_key(int64_t n_bins, int n_det, int64_t n_samples, bool mixed, int form)
 {
-    return std::make_tuple(n_det, (mixed ? 1 : 0) + 2 * form + (on_nodes(n_bins, n_samples, form) ? 2 * gw::kForms : 0),
-                           log2_bucket(n_bins), log2_bucket(n_samples));
+    const bool nodes = on_nodes(n_bins, n_det, n_samples, mixed, form);
+    return std::make_tuple(n_det, (mixed ? 1 : 0) + 2 * form + (nodes ? 2 * gw::kForms : 0), log2_bucket(n_bins),
+                           log2_bucket(n_samples));
 }
 
 // The plan gw_lnl_batch uses on this workspace: the tuned one of the size
@@ -309,16 +310,16 @@ LnlLayout lnl_layout_as(int64_t n_bins, int n_det, int64_t n_samples, const gw::
 
 // The sections of a call, with those of the frequency nodes when the call
 // takes them: split form without a template end (whose samples would end between
-// nodes), and enough work (kNodeMinWork).  The nodes' sections must not
+// nodes), and enough work (node_min_work).  The nodes' sections must not
 // push a call out of the static array that fits it without them, and
 // gw_lnl_batch and gw_lnl_batch_static run the same kernels on the same call,
 // so that rule is the same for both.  Nor must they push it out of `room`, the
 // bytes of a workspace that cannot grow.
-LnlLayout lnl_layout(int64_t n_bins, int n_det, int64_t n_samples, const gw::TilePlan &plan, unsigned flags, int n_cu,
-                     size_t room = SIZE_MAX)
+LnlLayout lnl_layout(int64_t n_bins, int n_det, int64_t n_samples, const gw::TilePlan &plan, bool mixed,
+                     unsigned flags, int n_cu, size_t room = SIZE_MAX)
 {
     const LnlLayout plain = lnl_layout_as(n_bins, n_det, n_samples, plan, flags, n_cu, false);
-    if (!on_nodes(n_bins, n_samples, gw::tile_form(flags))) return plain;
+    if (!on_nodes(n_bins, n_det, n_samples, mixed, gw::tile_form(flags))) return plain;
     const LnlLayout nodes = lnl_layout_as(n_bins, n_det, n_samples, plan, flags, n_cu, true);
     for (const size_t limit : {kStaticScratchBytes, room})
         if (plain.total <= limit && nodes.total > limit) return plain;
@@ -508,7 +509,8 @@ int tune_single_event(gw_workspace *ws, const gw_grid &grid, int n_det, const gw
     const int form = gw::tile_form(flags);
     const std::vector<gw::TilePlan> plans = tuning_candidates(ws, grid.n_bins, n_det, n_samples, mixed, form);
     size_t need = 0;
-    for (const gw::TilePlan &p : plans) need = std::max(need, lnl_layout(grid.n_bins, n_det, n_samples, p, flags, ws->n_cu).total);
+    for (const gw::TilePlan &p : plans)
+        need = std::max(need, lnl_layout(grid.n_bins, n_det, n_samples, p, mixed, flags, ws->n_cu).total);
     if (int rc = ensure_capacity(ws, need, stream)) return rc;
     const bool timing = ws->timing;
     ws->timing = false;                  // the trial calls are not measurements of the caller's
@@ -524,7 +526,7 @@ int tune_single_event(gw_workspace *ws, const gw_grid &grid, int n_det, const gw
     for (int pass = -1; pass < 2 && rc == GW_OK; ++pass) {
         for (size_t i = 0; i < plans.size() && rc == GW_OK; ++i) {
             if (pass < 0 && i > 0) break;    // one warm-up call lets the clock settle
-            const LnlLayout l = lnl_layout(grid.n_bins, n_det, n_samples, plans[i], flags, ws->n_cu);
+            const LnlLayout l = lnl_layout(grid.n_bins, n_det, n_samples, plans[i], mixed, flags, ws->n_cu);
             if ((e = hipEventRecord(ev[0], stream)) != hipSuccess) { rc = hip_fail(e, "hipEventRecord"); break; }
             if ((rc = lnl_enqueue(ws, static_cast<char *>(ws->base), l, plans[i], grid, n_det, geom, data, psd, theta,
                                   n_param, n_samples, lnl_out, mixed, flags, ws->n_cu, stream)) != GW_OK)
@@ -568,7 +570,8 @@ int lnl_one_event(gw_workspace *ws, const gw_grid &grid, int n_det, const gw::De
             return rc;
     }
     const gw::TilePlan plan = plan_tiles(ws, grid.n_bins, n_det, n_samples, mixed, form);
-    const LnlLayout l = lnl_layout(grid.n_bins, n_det, n_samples, plan, flags, ws->n_cu, workspace_room(ws, stream));
+    const LnlLayout l =
+        lnl_layout(grid.n_bins, n_det, n_samples, plan, mixed, flags, ws->n_cu, workspace_room(ws, stream));
     if (int rc = ensure_capacity(ws, l.total, stream)) return rc;
     return lnl_enqueue(ws, static_cast<char *>(ws->base), l, plan, grid, n_det, geom, data, psd, theta, n_param,
                        n_samples, lnl_out, mixed, flags, ws->n_cu, stream);
@@ -633,7 +636,7 @@ struct RaggedPlan {
 };
 
 // Whether a ragged pass sums over frequency nodes: the rule of one event's call (lnl_layout).
-bool ragged_nodes(int n_events, const gw_event *events, unsigned flags)
+bool ragged_nodes(int n_events, const gw_event *events, bool mixed, unsigned flags)
 {
     if (gw::tile_form(flags) != gw::kFormSplit) return false;
     double work = 0.0;
@@ -641,9 +644,10 @@ bool ragged_nodes(int n_events, const gw_event *events, unsigned flags)
     for (int i = 0; i < n_events; ++i) {
         const int64_t m = events[i].grid.n_bins;
         longest = std::max(longest, m);
-        work += (double)m * (double)((events[i].n_samples + gw::kBlock - 1) / gw::kBlock);
+        work += (double)m * (double)((events[i].n_samples + gw::kBlock - 1) / gw::kBlock) /
+                (double)gw::node_min_work(m, events[i].n_det, mixed);
     }
-    return longest >= gw::kNodeMinBins && longest <= 0x7fffffffLL && work >= (double)gw::kNodeMinWork;
+    return longest >= gw::kNodeMinBins && longest <= 0x7fffffffLL && work >= 1.0;
 }
 
 int64_t ragged_pairs(int n_events, const gw_event *events)
@@ -930,7 +934,7 @@ int ragged_run(gw_workspace *ws, int n_events, const gw_event *events, const std
     const int bucket = pairs > 0 ? (int)std::floor(std::log2((double)pairs)) : 0;
     // nodes, unless their sections alone (whose size no tile shape changes) leave a workspace that cannot grow
     const bool nodes =
-        ragged_nodes(na, ev, flags) &&
+        ragged_nodes(na, ev, mixed, flags) &&
         (!ws->pinned || ragged_plan(ws, na, ev, data, psd, theta, n_param, lnl, mixed, flags, true, kTuneTiles[0],
                                     kTuneChunks[0], nullptr).total <= ws->capacity);
     const auto tkey = std::make_tuple(max_det, (mixed ? 1 : 0) + 2 * form + (nodes ? 2 * gw::kForms : 0), bucket);
@@ -1221,7 +1225,7 @@ int64_t gw_lnl_batch_static_bytes(const gw_grid *grid, int n_det, int64_t n_samp
     if (int rc = static_device(device, &d)) return rc;
     const gw::TilePlan plan = plan_tiles_on(d->n_cu, d->occupancy, grid->n_bins, n_det, n_samples,
                                             precision == GW_PREC_MIXED, gw::tile_form(flags));
-    return (int64_t)lnl_layout(grid->n_bins, n_det, n_samples, plan, flags, d->n_cu).total;
+    return (int64_t)lnl_layout(grid->n_bins, n_det, n_samples, plan, precision == GW_PREC_MIXED, flags, d->n_cu).total;
 }
 
 int gw_lnl_batch_static(const gw_grid *grid, int n_det, const gw_detector *dets, const gw_c128 *data,
@@ -1249,7 +1253,7 @@ int gw_lnl_batch_static(const gw_grid *grid, int n_det, const gw_detector *dets,
     if (int rc = static_device(device, &d)) return rc;
     const gw::TilePlan plan = plan_tiles_on(d->n_cu, d->occupancy, grid->n_bins, n_det, n_samples, mixed,
                                             gw::tile_form(flags));
-    const LnlLayout l = lnl_layout(grid->n_bins, n_det, n_samples, plan, flags, d->n_cu);
+    const LnlLayout l = lnl_layout(grid->n_bins, n_det, n_samples, plan, mixed, flags, d->n_cu);
     if (l.total > kStaticScratchBytes)
         return fail(GW_EINVAL, "gw_lnl_batch_static: this call needs " + std::to_string(l.total) +
                                    " bytes of scratch, more than the library's static " +

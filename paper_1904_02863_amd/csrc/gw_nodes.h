@@ -342,17 +342,34 @@ struct NodeEvent {
 };
 
 // A call takes the nodes (how many, the batch decides) when its direct sum has
-// at least this many (bin, group of 256 samples) pairs: the nodes' kernels take
-// about 15 us more than the event preparation they replace, a small direct sum
-// less than that.  Measured, 3 detectors: 8,192 bins x 8 groups 46.0 us direct, 49.3 us on
-// nodes; 16,384 x 8 71.7 us and 50.2 us.
-constexpr int64_t kNodeMinBins = 8192, kNodeMinWork = 98304;
+// at least this many (bin, group of 256 samples) pairs.  The nodes' kernels take 10 to 15 us
+// more than the event preparation they replace: a small direct sum takes less than that,
+// and a batch that turns out to need every bin pays them on top.  Both grow with the
+// detectors as the direct sum does, so that FP64 calls of 1 to 8 share a line.
+// Measured, us, direct / nodes of a batch near one point / of arrival times all over the segment:
+//                      65,536 pairs         131,072               262,144
+//   FP64   1 detector  33.1 / 35.6 / 46.0   47.8 / 34.3 / 61.1    80.5 / 32.8 / 94.8
+//          3           43.3 / 47.8 / 54.4   68.6 / 42.5 / 79.8     121 / 40.3 /  130
+//          8           76.1 / 77.3 / 92.4    131 / 67.2 /  145     241 / 63.3 /  261
+//   mixed  1           28.5 / 39.2 / 40.9   39.7 / 44.5 / 53.4    64.1 / 36.7 / 74.9
+//          3           40.2 / 51.5 / 55.5   60.9 / 53.4 / 74.5     105 / 46.2 /  117
+//          8           68.2 / 87.6 / 84.5    116 / 77.1 /  131     212 / 70.2 /  239
+// (16,384, 32,768 and 65,536 bins x 1024 rows.)  The line lies above the point where near
+// batches begin to gain, where the others lose 20 to 30%; from four times there on
+// they lose 4 to 14%, 3 detectors x 259,585 bins x 4096 rows 0.5%.  Longer segments leave fewer of
+// their bins single: 65,536 bins x 1 group, 3 detectors, 49.9 / 41.2 / 64.1 and, mixed,
+// 51.3 / 45.0 / 66.1, so that the mixed path takes the FP64 line there.
+constexpr int64_t kNodeMinBins = 8192;
+__host__ __device__ constexpr int64_t node_min_work(int64_t n_bins, int n_det, bool mixed)
+{
+    return mixed && n_bins < 65536 ? (n_det <= 2 ? 163840 : 122880) : 98304;
+}
 
 // Stats entries the sample kernel writes: one per block of 64 samples.
 inline int64_t node_stat_entries(int64_t n_samples) { return (n_samples + 63) / 64; }
 
-// A ragged call takes the nodes when its events together have that much work and
-// one of them is that long.  64 neutron-star events of 8 to 256 s, 512 rows each: 8.50 ms summing
+// A ragged call takes the nodes when its events together have that much work (each in
+// its own measure) and one of them is that long.  64 neutron-star events of 8 to 256 s, 512 rows each: 8.50 ms summing
 // every bin, 0.91 ms on nodes (0.37 of it the weighting, 0.46 the sums).
 // Its events are cut into items of at least kRaggedUnits bins and nodes each,
 // kRaggedItems items per resident block where there is that much work: an item
