@@ -326,12 +326,6 @@ LnlLayout lnl_layout(int64_t n_bins, int n_det, int64_t n_samples, const gw::Til
     return nodes;
 }
 
-// Bytes a call on `stream` may lay out on the workspace: what it has when a capture forbids growing it.
-size_t workspace_room(const gw_workspace *ws, hipStream_t stream)
-{
-    return ws->pinned || capturing(stream) ? ws->capacity : SIZE_MAX;
-}
-
 template <typename T>
 T *at(gw_workspace *ws, size_t offset)
 {
@@ -570,8 +564,9 @@ int lnl_one_event(gw_workspace *ws, const gw_grid &grid, int n_det, const gw::De
             return rc;
     }
     const gw::TilePlan plan = plan_tiles(ws, grid.n_bins, n_det, n_samples, mixed, form);
-    const LnlLayout l =
-        lnl_layout(grid.n_bins, n_det, n_samples, plan, mixed, flags, ws->n_cu, workspace_room(ws, stream));
+    LnlLayout l = lnl_layout(grid.n_bins, n_det, n_samples, plan, mixed, flags, ws->n_cu);
+    if (l.nodes && l.total > ws->capacity && (ws->pinned || capturing(stream)))
+        l = lnl_layout(grid.n_bins, n_det, n_samples, plan, mixed, flags, ws->n_cu, ws->capacity);
     if (int rc = ensure_capacity(ws, l.total, stream)) return rc;
     return lnl_enqueue(ws, static_cast<char *>(ws->base), l, plan, grid, n_det, geom, data, psd, theta, n_param,
                        n_samples, lnl_out, mixed, flags, ws->n_cu, stream);

@@ -12,9 +12,9 @@
 // most GW_RESAMPLE_BAND per node), the weights are applied to the data once for all
 // samples,
 //     nu_d,n = sum_k w_n(k) D_d,k,        Z_d = sum_n nu_d,n e^{-2 pi i x_d(f_n)},
-// and the per-sample sum runs over the nodes: 1,652 instead of 259,585
-// frequencies for 4096 heavy binaries in 128 s, 17,900 instead of 1,040,897
-// for neutron stars from 15 Hz in 512 s.
+// and the per-sample sum runs over the nodes: 1,656 instead of 259,585
+// frequencies for 4096 heavy binaries in 128 s, 18,691 (14,704 of them single
+// bins below 44 Hz) instead of 1,040,897 for neutron stars from 15 Hz in 512 s.
 //
 // A phasor of constant rate is interpolated to 4e-16.  A chirp's rate falls over a bin's 32
 // nodes, and where its lowest node is at the limit the bin is off by more: in the
@@ -45,8 +45,10 @@ namespace gw {
 
 constexpr int kTaps = GW_RESAMPLE_TAPS;              // nodes a bin is interpolated from
 constexpr int kTapsBelow = GW_RESAMPLE_HALF - 1;     // of them below the bin's own cell
-// Node spacings, in bins, about a factor 1.4 apart; below 8 bins the 31
-// nodes a level needs beyond its ends and the weighting cost what it saves.
+// Node spacings, in bins, about a factor 1.4 apart.  Each costs 31 nodes beyond its
+// level's ends.  Spacings of 4 and 6 would serve more bins (neutron stars from 15 Hz in
+// 512 s: 9,497 single bins and 5,156 nodes, against 14,704 and 3,987), but a level of
+// them has no room in its part of D for its partials, nodes and tables (node_room_ok).
 constexpr int kNodeSpacings = 15;
 __host__ __device__ constexpr int node_spacing(int i)
 {
