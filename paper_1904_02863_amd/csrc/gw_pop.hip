@@ -323,9 +323,10 @@ __device__ __forceinline__ double reciprocal(double x)
 //
 // Bound by instruction issue: 111 vector instructions per sample and Lambda, three
 // exponentials, one expm1 and half a division among them, at about 0.9 of the issue
-// slots.  200 events x 20,000 samples x 64 points, the whole call: 1131 us with the
-// library's expm1 and a division per sample (150 instructions), 779 us now.  4 samples per thread: 6 and 8
-// measured 2 to 3% less (2: 15% more), but events of a few hundred samples fill fewer lanes.
+// slots.  200 events x 20,000 samples x 64 points, the whole call: 1001 us with the
+// library's expm1 and a division per sample (150 instructions), 780 us now (1077 and 878 us in
+// a longer run, where the clock falls).  4 samples per thread: 6 and 8 measured 2 to 3%
+// less (2: 15% more), but events of a few hundred samples fill fewer lanes.
 template <bool PREPARED>
 __global__ __launch_bounds__(kThreads, 2) void weights_kernel(int64_t n_events, int64_t n_per, int64_t chunks,
                                                            const double *__restrict__ s, int64_t n_hyper,
@@ -453,7 +454,7 @@ hipError_t launch(int64_t n_events, int64_t n_per, const double *samples, bool p
     const int64_t n_slots = slots_per_event(n_per);
     if (t_start && (e = hipEventRecord(t_start, stream)) != hipSuccess) return e;
     // With few blocks the points are shared out as well: 10 events x 500 samples x 64 points
-    // 114 us with every point in the 10 blocks, 20 us; 100 x 1000 x 64 151 and 42 us.
+    // 111 us with every point in the 10 blocks, 19 us; 100 x 1000 x 64 149 and 41 us.
     const int64_t blocks = chunks * n_events;
     const unsigned slices = (unsigned)std::max<int64_t>(1, std::min(n_hyper, kFillBlocks / blocks));
     if (prepared)
